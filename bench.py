@@ -35,10 +35,10 @@ WORKLOADS = {
 }
 PEAK_HBM_GBS = 8000.0
 # stages timed around exactly one kernel launch, and that kernel
-KERNEL_SYMBOL = {"init_keys": "k_init_keys", "scan_faces": "k_scan_small<0, false>",
-                 "scan_edges": "k_scan_small<1, false>", "scan_vertices": "k_scan_small<2, false>",
-                 "scan_faces_big": "k_scan_big<0, false, false>", "scan_edges_big": "k_scan_big<1, false, false>",
-                 "scan_vertices_big": "k_scan_big<2, false, false>", "sign": "k_sign", "backward": "k_backward"}
+KERNEL_SYMBOL = {"init_keys": "k_init_keys", "scan_faces": "k_scan_small<1, false>",
+                 "scan_edges": "k_scan_small<2, false>", "scan_vertices": "k_scan_small<4, false>",
+                 "scan_faces_big": "k_scan_over<1, false>", "scan_edges_big": "k_scan_over<4, false>",
+                 "scan_vertices_big": "k_scan_over<16, false>", "sign": "k_sign", "backward": "k_backward"}
 SINGLE_KERNEL_STAGES = list(KERNEL_SYMBOL)
 # scan launches and their tags in csc_scan_record_atomics, with their index in the atomic counts
 SCAN_LAUNCHES = {"scan_faces": 0, "scan_edges": 1, "scan_vertices": 2, "scan_faces_big": 3, "scan_edges_big": 4,

@@ -71,9 +71,9 @@ typedef struct csc_options {
                                1 hemispheres on both sides, 2 no extrusion (ablation only) */
   int32_t force_both_sides; /* 1: extrude every non-flat edge and every vertex on both sides */
   int32_t small_rows[3];    /* schedule (faces, edges, vertices): polyhedra with more rows than this
-                               go to an overflow pass that gives each one a whole wavefront; the
-                               rest share the rows of their wavefront. 0 = 32; values above 2^24
-                               act as 2^24. Only the speed depends on it (see the autotuner in the
+                               go to an overflow pass that cuts them into chunks of rows; the
+                               rest share the rows of their wavefront. 0 = 32 for long lists of
+                               polyhedra, more for short ones; values above 2^24 act as 2^24. Only the speed depends on it (see the autotuner in the
                                binding). */
   int32_t scan_mode;        /* 0 (default): each row of a polyhedron's box is intersected with its
                                half-spaces at once; 1: every cell of the box is tested by itself

@@ -11,10 +11,10 @@
 // feature id) into the brick store, the order-free replacement of the paper's
 // float compare-and-swap loop (Section 9).
 // Small polyhedra take one thread each (the paper's per-extrusion scheme); those
-// with more rows go to an overflow list that a second kernel walks with one
-// wavefront per polyhedron, its lanes splitting the rows (the role of the
-// dynamic-parallelism hybrid of Section 9.1). Item counts are read on the
-// device, so the whole sequence runs without host synchronisation.
+// with more rows go to an overflow list that a second kernel cuts into chunks of
+// rows, one chunk per lane (the role of the dynamic-parallelism hybrid of Section
+// 9.1). Item counts are read on the device, so the whole sequence runs without
+// host synchronisation.
 #include "geometry.h"
 #include "internal.h"
 #include "wave.h"
@@ -43,16 +43,18 @@ struct ScanArgs {
   unsigned long long* keys;
   unsigned long long* counter;  // optional: number of atomicMin issued (diagnostics)
   // overflow list: polyhedra of this kind (item indices) with more than small_rows
-  // rows from the front, wide ones from the back; their rows are cut into
-  // chunks of OV_CHUNK, numbered in list order (ov_chunk0: an entry's first)
+  // rows, and wide ones, in OV_SHARDS parts of ov_shard entries; part s takes the
+  // items of every OV_SHARDS-th run of 64, the wide ones from its back. Their
+  // rows are cut into chunks of OV_CHUNK, numbered in list order per part
+  // (ov_chunk0: an entry's first)
   int32_t* ov_items;
-  int32_t* ov_chunk0;
-  unsigned long long* ov_ctr;   // [0] front: entries << 36 | chunks, [1] back (wide) the same
-  int64_t ov_cap;               // entries the two ends share
+  uint32_t* ov_chunk0;
+  unsigned long long* ov_ctr;   // ov_counter(wide, part): entries << 36 | chunks
+  int64_t ov_shard;
   int64_t* stats;               // error word (brick capacity overflow)
   int64_t cap;                  // bricks the key store holds
   int64_t nf, ne, n_items;      // totals; n_items = launch bound
-  int32_t small_rows;           // more rows: one wavefront per polyhedron
+  int32_t small_rows;           // more rows: to the overflow list (0: by the length of the item list)
   int32_t per_cell;             // 1: test every box cell by itself (Alg. 2) instead of row intervals
   int32_t grid_mode;            // one-polyhedron-per-lane pass: SCAN_GRID_* (how waves get their polyhedra)
   unsigned long long* head;     // SCAN_GRID_QUEUE: next group of 64 polyhedra to hand out
@@ -421,18 +423,10 @@ __device__ inline unsigned long long pack_cand(int lane, int t, int du, int dv) 
          (unsigned long long)dv;
 }
 
-// a value of the polyhedron held by lane L. With UNI every lane holds the same
-// polyhedron (the overflow pass): the value is read from the first active lane,
-// a scalar broadcast instead of an LDS permutation. (Taking the lane's own value
-// directly would let the compiler fuse the setup arithmetic into the distance
-// arithmetic and round differently from the one-lane-per-polyhedron pass.)
-__device__ inline int first_lane(int x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ inline float first_lane(float x) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x))); }
-
-template <bool UNI, typename T>
+// a value of the polyhedron held by lane L
+template <typename T>
 __device__ inline T from_lane(T x, int L) {
-  if constexpr (UNI) return first_lane(x);
-  else return __shfl(x, L, 64);
+  return __shfl(x, L, 64);
 }
 
 // Distance and sign code of cell (i, j, k) to the feature of a wide polyhedron
@@ -510,32 +504,32 @@ __device__ inline void log_atomic(const ScanArgs& P, uint32_t at) {
 // all lanes of the wavefront together (lane permutations), `valid` per lane.
 // WIDE (overflow pass only): the distance in FP64 (dist_wide). LOG: record the
 // atomic instruction (diagnostic instantiation).
-template <int KIND, bool UNI, bool WIDE, bool LOG>
+template <int KIND, bool WIDE, bool LOG>
 __device__ inline void finish_cand(const ScanArgs& P, const Poly& q, unsigned long long ent, bool valid,
                                    BrickCache& bc, unsigned& issued) {
   const int L = valid ? (int)(ent >> 48) : 0;
   const int t = (int)((ent >> 32) & 0xffff), du = (int)((ent >> 16) & 0xffff), dv = (int)(ent & 0xffff);
-  const int mesh = from_lane<UNI>(q.mesh, L), id = from_lane<UNI>(q.id, L);
+  const int mesh = from_lane(q.mesh, L), id = from_lane(q.id, L);
   // row axes, with the face's absorbed features above them (one lane move).
   // Every pass decides the same cells: the packed key orders equal distances by
   // sign code before feature id, so a face whose boundary cell one pass decided
   // and another left open would win or lose a tie by schedule.
-  const int axes = from_lane<UNI>(q.ra | (q.ua << 2) | (q.absorbed << 4), L);
-  const int ax = from_lane<UNI>(q.anc.x, L), ay = from_lane<UNI>(q.anc.y, L), az = from_lane<UNI>(q.anc.z, L);
-  const f3 g0 = mk(from_lane<UNI>(q.g[0], L), from_lane<UNI>(q.g[1], L), from_lane<UNI>(q.g[2], L));
+  const int axes = from_lane(q.ra | (q.ua << 2) | (q.absorbed << 4), L);
+  const int ax = from_lane(q.anc.x, L), ay = from_lane(q.anc.y, L), az = from_lane(q.anc.z, L);
+  const f3 g0 = mk(from_lane(q.g[0], L), from_lane(q.g[1], L), from_lane(q.g[2], L));
   f3 g1 = mk(0.f, 0.f, 0.f), g2 = mk(0.f, 0.f, 0.f), nn = mk(0.f, 0.f, 0.f);
   float side = 1.f;
   if constexpr (KIND == KIND_FACE) {
-    g1 = mk(from_lane<UNI>(q.g[3], L), from_lane<UNI>(q.g[4], L), from_lane<UNI>(q.g[5], L));
-    g2 = mk(from_lane<UNI>(q.g[6], L), from_lane<UNI>(q.g[7], L), from_lane<UNI>(q.g[8], L));
-    nn = mk(from_lane<UNI>(q.cone[0], L), from_lane<UNI>(q.cone[1], L), from_lane<UNI>(q.cone[2], L));
+    g1 = mk(from_lane(q.g[3], L), from_lane(q.g[4], L), from_lane(q.g[5], L));
+    g2 = mk(from_lane(q.g[6], L), from_lane(q.g[7], L), from_lane(q.g[8], L));
+    nn = mk(from_lane(q.cone[0], L), from_lane(q.cone[1], L), from_lane(q.cone[2], L));
   } else if constexpr (KIND == KIND_EDGE) {
-    g1 = mk(from_lane<UNI>(q.g[3], L), from_lane<UNI>(q.g[4], L), from_lane<UNI>(q.g[5], L));
-    nn = mk(from_lane<UNI>(q.pl[4][0], L), from_lane<UNI>(q.pl[4][1], L), from_lane<UNI>(q.pl[4][2], L));
-    side = from_lane<UNI>(q.side, L);
+    g1 = mk(from_lane(q.g[3], L), from_lane(q.g[4], L), from_lane(q.g[5], L));
+    nn = mk(from_lane(q.pl[4][0], L), from_lane(q.pl[4][1], L), from_lane(q.pl[4][2], L));
+    side = from_lane(q.side, L);
   } else {
-    nn = mk(from_lane<UNI>(q.cone[0], L), from_lane<UNI>(q.cone[1], L), from_lane<UNI>(q.cone[2], L));
-    side = from_lane<UNI>(q.side, L);
+    nn = mk(from_lane(q.cone[0], L), from_lane(q.cone[1], L), from_lane(q.cone[2], L));
+    side = from_lane(q.side, L);
   }
   if (!valid) return;
   const MeshDesc& G = P.md[mesh];
@@ -599,36 +593,6 @@ __device__ inline void finish_cand(const ScanArgs& P, const Poly& q, unsigned lo
 }
 
 
-// the row coefficients of the polyhedron held by lane L, fetched by lane
-// permutation (with the row-axis slopes when each cell is tested on its own);
-// called by all lanes together
-template <int KIND, bool UNI>
-__device__ inline Rows rows_of(const Rows& r, int L, bool per_cell) {
-  constexpr int NPL = KIND == KIND_VERT ? 1 : 5;
-  Rows o;
-#pragma unroll
-  for (int i = 0; i < NPL; i++) {
-    o.inv[i] = from_lane<UNI>(r.inv[i], L);
-    o.su[i] = from_lane<UNI>(r.su[i], L);
-    o.sv[i] = from_lane<UNI>(r.sv[i], L);
-    o.k[i] = from_lane<UNI>(r.k[i], L);
-  }
-  if (per_cell) {
-#pragma unroll
-    for (int i = 0; i < NPL; i++) o.sl[i] = from_lane<UNI>(r.sl[i], L);
-  }
-  o.nt = from_lane<UNI>(r.nt, L);
-  if constexpr (KIND == KIND_VERT) {
-    o.A[0] = from_lane<UNI>(r.A[0], L);
-    o.A[1] = from_lane<UNI>(r.A[1], L);
-    o.A[2] = from_lane<UNI>(r.A[2], L);
-    o.R2 = from_lane<UNI>(r.R2, L);
-    o.hf = from_lane<UNI>(r.hf, L);
-    o.ihf = from_lane<UNI>(r.ihf, L);
-  }
-  return o;
-}
-
 // Alg. 2 for one cell: every half-space with slack (and, for vertices, the
 // ball of radius band*h); the per-cell alternative to the row interval
 template <int KIND>
@@ -644,99 +608,6 @@ __device__ inline bool cell_in(const Rows& o, int t, int du, int dv) {
   return in;
 }
 
-// The rows of the wavefront's polyhedra (lane l holds `rows` rows of its own
-// polyhedron q) are dealt out evenly: in each round lane j takes the j-th next
-// row of the whole wavefront, finds the lane owning it (binary search over the
-// prefix sums of the row counts), computes its interval with the owner's
-// coefficients, and queues its candidate cells in ring `qb` (this wavefront's
-// own) under the owner's lane number. Lanes with many rows thus no longer hold
-// up the others. Must be called by all lanes of the wavefront.
-template <int KIND, bool UNI, bool WIDE, bool LOG>
-__device__ inline void scan_rows_wave(const ScanArgs& P, const Poly& q, const Rows& r, int rows, int row0,
-                                      unsigned long long* qb, unsigned& issued) {
-  const int lane = threadIdx.x & 63;
-  const int incl = wave_prefix_sum(rows), excl = incl - rows;
-  const int total = __builtin_amdgcn_readlane(incl, 63);
-  uint32_t head = 0, tail = 0;  // the same in every lane
-  BrickCache bc;
-  for (int base = 0; base < total; base += 64) {
-    const int g = base + lane;
-    int lo = 0, hi = 63;  // the last lane whose rows start at or before g
-    if constexpr (!UNI) {
-#pragma unroll
-      for (int s = 0; s < 6; s++) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (__shfl(excl, mid, 64) <= g) lo = mid;
-        else hi = mid - 1;
-      }
-    }
-    const int L = lo;  // with UNI lane 0 owns every row
-    const int rloc = UNI ? row0 + g : g - __shfl(excl, L, 64), nuL = from_lane<UNI>(q.nu, L);
-    const int nud = nuL > 0 ? nuL : 1;  // past the last row L may hold no polyhedron
-    const int dv = g < total ? rloc / nud : 0, du = g < total ? rloc - dv * nud : 0;
-    int t = 0, t1 = -1;
-    const Rows o = rows_of<KIND, UNI>(r, L, P.per_cell);
-    if (P.per_cell) {  // every cell of the row, each tested by itself below
-      t = 0;
-      t1 = o.nt - 1;
-    } else if (!row_range<KIND>(o, du, dv, t, t1)) {
-      t1 = -1;
-    }
-    if (g >= total) t1 = -1;
-    // vertices: the owner's cone for the per-cell discriminant
-    [[maybe_unused]] f3 cg = mk(0.f, 0.f, 0.f), cax = mk(0.f, 0.f, 0.f);
-    [[maybe_unused]] float cct = -2.f, chf = 0.f, ceps = 0.f;
-    [[maybe_unused]] int cra = 0, cua = 0;
-    if constexpr (KIND == KIND_VERT) {
-      cg = mk(from_lane<UNI>(q.g[0], L), from_lane<UNI>(q.g[1], L), from_lane<UNI>(q.g[2], L));
-      cax = mk(from_lane<UNI>(q.cone[0], L), from_lane<UNI>(q.cone[1], L), from_lane<UNI>(q.cone[2], L));
-      cct = from_lane<UNI>(q.cone[3], L);
-      chf = from_lane<UNI>(r.hf, L);
-      ceps = from_lane<UNI>(r.eps, L);
-      const int ax = from_lane<UNI>(q.ra | (q.ua << 2), L);
-      cra = ax & 3;
-      cua = (ax >> 2) & 3;
-    }
-    while (true) {
-      const bool has = t <= t1;
-      if (__ballot(has) == 0) break;
-      bool push = has && (!P.per_cell || cell_in<KIND>(o, t, du, dv));
-      if constexpr (KIND == KIND_VERT) {  // cone discriminant with slack (Eq. 10)
-        if (push && cct > -1.f) {
-          const int di = cra == 0 ? t : (cua == 0 ? du : dv);
-          const int dj = cra == 1 ? t : (cua == 1 ? du : dv);
-          const int dk = cra == 2 ? t : (cua == 2 ? du : dv);
-          const f3 rr = mk(di * chf, dj * chf, dk * chf) - cg;
-          const float te = dot(rr, cax) + ceps;
-          push = te >= 0.f && te * te >= cct * cct * dot(rr, rr);
-        }
-      }
-      const unsigned long long pm = __ballot(push);
-      if (push) qb[(tail + lanes_below(pm)) & (QCAP - 1)] = pack_cand(L, t, du, dv);
-      tail += (uint32_t)__popcll(pm);
-      if (has) t++;
-      if (tail - head >= 64) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        const unsigned long long e = qb[(head + lane) & (QCAP - 1)];
-        finish_cand<KIND, UNI, WIDE, LOG>(P, q, e, true, bc, issued);
-        head += 64;
-      }
-    }
-  }
-  if (tail != head) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const bool valid = (uint32_t)lane < tail - head;
-    const unsigned long long e = valid ? qb[(head + lane) & (QCAP - 1)] : 0ull;
-    finish_cand<KIND, UNI, WIDE, LOG>(P, q, e, valid, bc, issued);
-  }
-  // the ring is reused by the next call: finish its reads first
-  __builtin_amdgcn_wave_barrier();
-}
-
 // The row coefficients of every lane's polyhedron, staged in LDS for the
 // one-polyhedron-per-lane pass so that the lane taking a row reads its owner's
 // with a few 16-byte loads: faces and edges inv, su, sv, k, sl of their five
@@ -750,7 +621,7 @@ struct RowSlot {
 
 struct RowsOf {
   Rows o;
-  int excl, nu;
+  int excl, nu;  // excl: the row number (of the wavefront's numbering) of the owner's row 0
   f3 cax;       // vertices: cone axis in (row, u, v) order
   float cct;    // vertices: aperture cosine, or below -1 for a hemisphere
 };
@@ -803,23 +674,23 @@ __device__ inline RowsOf get_slot(const float4* sl) {
   return w;
 }
 
-// The one-polyhedron-per-lane pass: the rows of the wavefront's polyhedra (lane
-// l holds `rows` rows of its own polyhedron q, coefficients r) are dealt out
-// evenly, 64 per round, lane j taking the j-th. The owner of each row: every
-// lane marks the round position where its rows start, and a prefix maximum over
-// the positions (carrying the owner of the round's first row) gives the last
-// start at or before each. The lane computes the row's interval from the
-// owner's staged coefficients and queues its candidate cells in the
-// wavefront's ring under the owner's lane number; every 64 queued cells are
-// finished by all lanes together. Must be called by all lanes of the wavefront.
-template <int KIND, bool LOG>
-__device__ inline void scan_rows_lanes(const ScanArgs& P, const Poly& q, const Rows& r, int rows, float4* slots,
-                                       int* marks, unsigned long long* qb, unsigned& issued) {
+// The rows of the wavefront's polyhedra (lane l holds `rows` rows of its own
+// polyhedron q, from its row `row0` on, coefficients r) are dealt out evenly, 64
+// per round, lane j taking the j-th. The owner of each row: every lane marks the
+// round position where its rows start, and a prefix maximum over the positions
+// (carrying the owner of the round's first row) gives the last start at or before
+// each. The lane computes the row's interval from the owner's staged coefficients
+// and queues its candidate cells in the wavefront's ring under the owner's lane
+// number; every 64 queued cells are finished by all lanes together. Must be
+// called by all lanes of the wavefront.
+template <int KIND, bool WIDE, bool LOG>
+__device__ inline void scan_rows_lanes(const ScanArgs& P, const Poly& q, const Rows& r, int rows, int row0,
+                                       float4* slots, int* marks, unsigned long long* qb, unsigned& issued) {
   constexpr int F4 = RowSlot<KIND>::F4;
   const int lane = threadIdx.x & 63;
   const int incl = wave_prefix_sum(rows), excl = incl - rows;
   const int total = __builtin_amdgcn_readlane(incl, 63);
-  if (rows > 0) put_slot<KIND>(slots + lane * F4, r, q, excl);
+  if (rows > 0) put_slot<KIND>(slots + lane * F4, r, q, excl - row0);
   uint32_t head = 0, tail = 0;  // the same in every lane
   BrickCache bc;
   int carry = 0;
@@ -862,7 +733,7 @@ __device__ inline void scan_rows_lanes(const ScanArgs& P, const Poly& q, const R
       if (tail - head >= 64) {
         wave_sync_lds();
         const unsigned long long e = qb[(head + lane) & (QCAP - 1)];
-        finish_cand<KIND, false, false, LOG>(P, q, e, true, bc, issued);
+        finish_cand<KIND, WIDE, LOG>(P, q, e, true, bc, issued);
         head += 64;
       }
     }
@@ -871,7 +742,7 @@ __device__ inline void scan_rows_lanes(const ScanArgs& P, const Poly& q, const R
     wave_sync_lds();
     const bool valid = (uint32_t)lane < tail - head;
     const unsigned long long e = valid ? qb[(head + lane) & (QCAP - 1)] : 0ull;
-    finish_cand<KIND, false, false, LOG>(P, q, e, valid, bc, issued);
+    finish_cand<KIND, WIDE, LOG>(P, q, e, valid, bc, issued);
   }
   // the ring, slots and marks are reused by the next call: finish the reads first
   __builtin_amdgcn_wave_barrier();
@@ -889,69 +760,109 @@ __device__ inline int64_t item_count(const ScanArgs& P) {
   return P.n_items_d ? (*P.n_items_d < P.n_items ? *P.n_items_d : P.n_items) : P.n_items;
 }
 
-constexpr int OV_CHUNK = 256;  // rows of an overflow work item
+// Rows of an overflow work item (one lane's share of a step) and the most items of
+// a step. A step deals at most OV_STEP * OV_CHUNK rows, so the last steps stay
+// short: 128 rows and 64 items took 749 us on a 20-cell band (51,756 faces, 192^3)
+// and 882 us on a batch of 64 meshes, 32 and 32 take 540 and 810.
+constexpr int OV_CHUNK = 32;
+constexpr int OV_STEP = 32;
 constexpr unsigned long long OV_MASK = (1ull << 36) - 1;
+// Appends to one counter serialise (about 10 ns each on this device, 0.8 ms if
+// every wavefront of 5.2M faces appends), so each list is cut into 64 parts, one
+// for each lane of the wavefront that reads them back, each counter on a 64-byte
+// line of its own (a 360,000-face noisy torus: overflow pass 353 -> 250 us at 32 rows).
+constexpr int OV_SHARDS = 64;
+constexpr int OV_CTR_STRIDE = 8;                             // u64 per counter line
+constexpr int OV_CTRS = 2 * OV_SHARDS * OV_CTR_STRIDE;       // u64 of one kind's counters
+constexpr int OV_CTRS_ALL = 3 * OV_CTRS + 8;                 // three kinds, then the three group heads
+inline int64_t ov_shard_cap(int64_t n) { return ((n + 63) / 64 + OV_SHARDS - 1) / OV_SHARDS * 64; }
+__device__ inline unsigned long long* ov_counter(const ScanArgs& P, int wide, int shard) {
+  return P.ov_ctr + (wide * OV_SHARDS + shard) * OV_CTR_STRIDE;
+}
+// list slot of entry idx of a part
+__device__ inline int64_t ov_slot(const ScanArgs& P, int wide, int shard, int64_t idx) {
+  return wide ? (shard + 1) * P.ov_shard - 1 - idx : shard * P.ov_shard + idx;
+}
 
-// append this lane's polyhedron (if `mine`) to one end of the overflow list:
-// one 64-bit atomic per wavefront adds the entries and their chunks at once, so
-// entry order and chunk numbering agree
-__device__ inline void ov_append(const ScanArgs& P, bool mine, int end, int64_t item, int rows) {
+// append this lane's polyhedron (if `mine`) to its part of the overflow list: one
+// 64-bit atomic per wavefront adds the entries and their chunks at once, so entry
+// order and chunk numbering agree. The wavefront's items share a run of 64.
+__device__ inline void ov_append(const ScanArgs& P, bool mine, int wide, int64_t item, int rows) {
   const unsigned long long m = __ballot(mine);
   if (!m) return;
   const int c = mine ? (rows + OV_CHUNK - 1) / OV_CHUNK : 0;
   const int ci = wave_prefix_sum(c), tot = __builtin_amdgcn_readlane(ci, 63);
   const int lane = threadIdx.x & 63, leader = __ffsll((long long)m) - 1;
+  const int shard = (int)(item >> 6) & (OV_SHARDS - 1);
   unsigned long long base = 0;
-  if (lane == leader) base = atomicAdd(&P.ov_ctr[end], ((unsigned long long)__popcll(m) << 36) | (unsigned)tot);
+  if (lane == leader)
+    base = atomicAdd(ov_counter(P, wide, shard), ((unsigned long long)__popcll(m) << 36) | (unsigned)tot);
   const uint32_t blo = __shfl((uint32_t)base, leader, 64), bhi = __shfl((uint32_t)(base >> 32), leader, 64);
   base = ((unsigned long long)bhi << 32) | blo;
   if (mine) {
-    const int64_t idx = (int64_t)(base >> 36) + lanes_below(m);
-    const int64_t slot = end ? P.ov_cap - 1 - idx : idx;
+    const int64_t slot = ov_slot(P, wide, shard, (int64_t)(base >> 36) + lanes_below(m));
     P.ov_items[slot] = (int32_t)item;
-    P.ov_chunk0[slot] = (int32_t)((int64_t)(base & OV_MASK) + ci - c);
+    P.ov_chunk0[slot] = (uint32_t)((int64_t)(base & OV_MASK) + ci - c);
   }
 }
 
-// How the waves of the one-polyhedron-per-lane pass get their polyhedra (64
-// consecutive items per group): one group per wave of a grid sized to the
-// items; a persistent grid (as many waves as fit at once) striding over the
-// groups; or that grid taking groups from a device counter in the order the
-// waves ask (an atomic head over the kind's whole list, so waves that drew
-// cheap groups take more).
+// How the waves of the one-polyhedron-per-lane pass get their polyhedra (groups of
+// consecutive items): a grid sized to the items; a persistent grid (as many waves
+// as fit at once) striding over the groups; or that grid taking groups from a
+// device counter in the order the waves ask (an atomic head over the kind's whole
+// list, so waves that drew cheap groups take more).
 enum { SCAN_GRID_LAUNCH = 1, SCAN_GRID_STRIDE = 2, SCAN_GRID_QUEUE = 3 };
+
+// A group holds 64 items where the list is long. A shorter list is cut into
+// smaller groups, down to SCAN_MIN_GROUP items, so that it still gives every wave
+// of its grid one: the rows are dealt over all 64 lanes whatever the group, and
+// only the polyhedra's setup leaves lanes idle (20,480 faces, 256^3: scans of all
+// kinds 112 -> 71 us).
+constexpr int SCAN_MIN_GROUP = 8;
+// The rows above which a polyhedron goes to the overflow list when the caller sets
+// no limit: SCAN_ROWS in a group of 64, twice that in a smaller one, whose wave
+// deals fewer rows in all. (64 meshes, 1.65M faces: forward scan 819 us at 32 rows,
+// 965 at 16, 893 at 64; 20,480 faces in groups of 8: 94 us at 16 rows, 90 at 32, 70
+// at 64 and above, but 320 large faces 74 at 32, 80 at 64 and 95 at 128.)
+constexpr int SCAN_ROWS = 32;
 
 // one polyhedron per lane, the rows of a wavefront's polyhedra shared by its
 // lanes; polyhedra with more than small_rows rows go to the front of the
 // overflow list, wide ones to its back
 template <int KIND, bool LOG>
-__device__ inline void scan_group(const ScanArgs& P, int64_t item, int64_t count, float4* slots, int* marks,
+__device__ inline void scan_group(const ScanArgs& P, int64_t item, bool has, int small_rows, float4* slots, int* marks,
                                   unsigned long long* qb, unsigned& issued) {
   Poly q;  // not cleared: a lane without a polyhedron owns no row, so no lane reads it
   q.wide = 0;
-  const int nc = item < count ? build_poly<KIND>(P, item, q) : 0;
+  const int nc = has ? build_poly<KIND>(P, item, q) : 0;
   const int rows = nc > 0 ? q.nu * q.nv : 0;
-  const bool big = nc > 0 && (rows > P.small_rows || q.wide);
+  const bool big = nc > 0 && (rows > small_rows || q.wide);
   ov_append(P, big && !q.wide, 0, item, rows);
   ov_append(P, big && q.wide, 1, item, rows);
   Rows r;  // set only for lanes with rows to deal; rows past the end are dropped whatever it holds
   if (nc > 0 && !big) setup_rows<KIND, false>(q, P.md[q.mesh], r);
-  scan_rows_lanes<KIND, LOG>(P, q, r, nc > 0 && !big ? rows : 0, slots, marks, qb, issued);
+  scan_rows_lanes<KIND, false, LOG>(P, q, r, nc > 0 && !big ? rows : 0, 0, slots, marks, qb, issued);
 }
 
+// the LDS of one wavefront of the scan passes
+struct ScanLds {
+  float4 slot[64 * RowSlot<KIND_FACE>::F4];
+  unsigned long long q[QCAP];
+  int mark[64];
+};
+constexpr int SCAN_WAVES = 4;  // wavefronts per block
+
+// this block's share of one kind: block b of nb
 template <int KIND, bool LOG>
-__global__ __launch_bounds__(256) void k_scan_small(ScanArgs P) {
-  __shared__ unsigned long long s_q[256 / 64][QCAP];
-  __shared__ float4 s_slot[256 / 64][64 * RowSlot<KIND>::F4];
-  __shared__ int s_mark[256 / 64][64];
+__device__ inline void scan_kind(const ScanArgs& P, unsigned b, unsigned nb, ScanLds& S) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t count = item_count(P), groups = (count + 63) >> 6;
-  const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
+  const int64_t count = item_count(P);
+  const int64_t nw = (int64_t)nb * SCAN_WAVES;
   unsigned issued = 0;
   if (P.grid_mode == SCAN_GRID_QUEUE) {
     // Same-address atomics serialise (about 10 ns each here), so a wavefront
     // takes queue_chunk groups per pop: about two pops per wavefront in all.
-    const int64_t k = P.queue_chunk;
+    const int64_t k = P.queue_chunk, groups = (count + 63) >> 6;
     auto pop = [&]() -> int64_t {
       unsigned long long g = 0;
       if (lane == 0) g = atomicAdd(P.head, (unsigned long long)k);
@@ -960,60 +871,150 @@ __global__ __launch_bounds__(256) void k_scan_small(ScanArgs P) {
     // every wave leaves once its next chunk starts past the last group
     for (int64_t g0 = pop(); g0 < groups; g0 = pop())
       for (int64_t g = g0; g < g0 + k && g < groups; g++)
-        scan_group<KIND, LOG>(P, 64 * g + lane, count, s_slot[w], s_mark[w], s_q[w], issued);
+        scan_group<KIND, LOG>(P, 64 * g + lane, 64 * g + lane < count, P.small_rows ? P.small_rows : SCAN_ROWS, S.slot,
+                              S.mark, S.q, issued);
   } else {
-    for (int64_t g = blockIdx.x * (int64_t)(blockDim.x >> 6) + w; g < groups;
-         g = P.grid_mode == SCAN_GRID_STRIDE ? g + nw : groups)
-      scan_group<KIND, LOG>(P, 64 * g + lane, count, s_slot[w], s_mark[w], s_q[w], issued);
+    int gw = SCAN_MIN_GROUP;
+    while (gw < 64 && (int64_t)gw * nw < count) gw <<= 1;
+    const int small_rows = P.small_rows ? P.small_rows : (gw < 64 ? 2 : 1) * SCAN_ROWS;
+    // (a grid sized to 64 items per wave covers the list in one step whatever gw)
+    for (int64_t g = (int64_t)b * SCAN_WAVES + w; g * gw < count; g += nw) {
+      const int64_t item = g * gw + lane;
+      scan_group<KIND, LOG>(P, item, lane < gw && item < count, small_rows, S.slot, S.mark, S.q, issued);
+    }
   }
   add_issued(P, issued, 0);
 }
 
-// first chunk of overflow entry e (list order; the wide list fills from the back)
-template <bool WIDE>
-__device__ inline int64_t ov_first_chunk(const ScanArgs& P, int64_t e) {
-  return P.ov_chunk0[WIDE ? P.ov_cap - 1 - e : e];
+// The three kinds in one launch: a kind's blocks are [first[k], first[k + 1]).
+struct ScanKinds {
+  ScanArgs k[3];
+  unsigned first[4];
+};
+
+// KINDS: bit k for kind k. All three (7) in the scans; one alone where a stage is
+// timed or its atomics logged. Together the kinds fill the device where one
+// alone leaves it idle (a 20,480-face sphere: 80 + 240 + 80 blocks), and their
+// last waves overlap.
+template <int KINDS, bool LOG>
+__global__ __launch_bounds__(64 * SCAN_WAVES, 4) void k_scan_small(ScanKinds P) {
+  __shared__ ScanLds lds[SCAN_WAVES];
+  ScanLds& S = lds[threadIdx.x >> 6];
+  const unsigned b = blockIdx.x;
+  if constexpr ((KINDS & 1) != 0)
+    if (b < P.first[1]) scan_kind<KIND_FACE, LOG>(P.k[0], b, P.first[1], S);
+  if constexpr ((KINDS & 2) != 0)
+    if (b >= P.first[1] && b < P.first[2])
+      scan_kind<KIND_EDGE, LOG>(P.k[1], b - P.first[1], P.first[2] - P.first[1], S);
+  if constexpr ((KINDS & 4) != 0)
+    if (b >= P.first[2]) scan_kind<KIND_VERT, LOG>(P.k[2], b - P.first[2], P.first[3] - P.first[2], S);
 }
 
-// The overflow list in chunks of OV_CHUNK rows of one polyhedron per wavefront
-// and step (a persistent grid striding over the chunks: the list follows face
-// order, so neighbouring chunks are alike in cost), the chunk's rows dealt out
-// to the lanes. WIDE: the back of the list (wide polyhedra), with FP64
-// distances; otherwise the front. Every lane holds the same polyhedron. The
-// chunk's entry is the last whose first chunk is at or before it, found by a
-// 64-way search (lane j tests the j-th of 64 evenly spaced entries; chunk
-// numbers grow along the list): a few vector loads in place of a chain of
-// dependent ones, starting from the previous chunk's entry.
+// Chunks c0 .. c0 + k - 1 (k <= OV_STEP, fewer at its end) of one part of an overflow
+// list, one per lane: each lane builds its chunk's polyhedron, and the chunks' rows
+// are dealt over the wavefront like whole polyhedra's. Chunk c0's entry is the last
+// whose first chunk is at or before it, found by a 64-way search (lane j tests
+// the j-th of 64 evenly spaced entries; chunk numbers grow along the list). Every
+// entry holds at least one chunk, so the chunks lie in that entry and the 63
+// after it, and each lane finds its own as a row finds its polyhedron.
 template <int KIND, bool WIDE, bool LOG>
-__global__ __launch_bounds__(64) void k_scan_big(ScanArgs P) {
-  __shared__ unsigned long long s_q[QCAP];
-  const int lane = threadIdx.x;
-  const unsigned long long ctr = P.ov_ctr[WIDE ? 1 : 0];
+__device__ inline void scan_chunks(const ScanArgs& P, int shard, int64_t c0, int k, ScanLds& S, unsigned& issued) {
+  const int lane = threadIdx.x & 63;
+  const unsigned long long ctr = *ov_counter(P, WIDE, shard);
   const int64_t n = (int64_t)(ctr >> 36), total = (int64_t)(ctr & OV_MASK);
-  unsigned issued = 0;
-  int64_t lo = 0;  // entry 0 starts at chunk 0; later chunks lie at or after the previous one's entry
-  for (int64_t ch = blockIdx.x; ch < total; ch += gridDim.x) {
-    int64_t hi = n - 1;
-    while (lo < hi) {
-      const int64_t step = (hi - lo + 64) >> 6;  // ceil((hi - lo + 1) / 64)
-      const int64_t at = lo + lane * step;
-      const bool le = at <= hi && ov_first_chunk<WIDE>(P, at) <= ch;
-      const int last = 63 - __clzll((long long)__ballot(le));  // lane 0 always holds
-      const int64_t nlo = lo + last * step;
-      hi = nlo + step - 1 < hi ? nlo + step - 1 : hi;
-      lo = nlo;
-    }
-    const int64_t slot = WIDE ? P.ov_cap - 1 - lo : lo;
-    Poly q = {};
-    if (build_poly<KIND>(P, P.ov_items[slot], q) <= 0) continue;  // the same for every lane
-    const int r0 = (int)(ch - P.ov_chunk0[slot]) * OV_CHUNK, rows = q.nu * q.nv;
-    const int cnt = rows - r0 < OV_CHUNK ? rows - r0 : OV_CHUNK;
-    if (cnt <= 0) continue;
-    Rows r;
-    setup_rows<KIND, WIDE>(q, P.md[q.mesh], r);
-    scan_rows_wave<KIND, true, WIDE, LOG>(P, q, r, lane == 0 ? cnt : 0, r0, s_q, issued);  // lane 0: the rows
+  auto first_chunk = [&](int64_t e) -> int64_t { return (int64_t)P.ov_chunk0[ov_slot(P, WIDE, shard, e)]; };
+  int64_t lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const int64_t step = (hi - lo + 64) >> 6;  // ceil((hi - lo + 1) / 64)
+    const int64_t at = lo + lane * step;
+    const bool le = at <= hi && first_chunk(at) <= c0;
+    const int last = 63 - __clzll((long long)__ballot(le));  // lane 0 always holds
+    const int64_t nlo = lo + last * step;
+    hi = nlo + step - 1 < hi ? nlo + step - 1 : hi;
+    lo = nlo;
   }
-  add_issued(P, issued, 3);
+  const int64_t e = lo + lane;
+  const int64_t first = e < n ? first_chunk(e) : total;
+  S.mark[lane] = -1;
+  wave_sync_lds();
+  if (lane == 0) S.mark[0] = 0;
+  else if (e < n && first - c0 < 64) S.mark[first - c0] = lane;  // first > c0 past lane 0
+  wave_sync_lds();
+  const int own = wave_prefix_max(S.mark[lane]);
+  const uint32_t first_own = __shfl((uint32_t)first, own, 64);
+  wave_sync_lds();  // the marks are used again below
+  const bool has = lane < k && c0 + lane < total;
+  Poly q;  // read only under lanes that own rows
+  int cnt = 0, r0 = 0;
+  Rows r;
+  if (has && build_poly<KIND>(P, P.ov_items[ov_slot(P, WIDE, shard, lo + own)], q) > 0) {
+    r0 = (int)((uint32_t)(c0 + lane) - first_own) * OV_CHUNK;
+    cnt = q.nu * q.nv - r0;
+    cnt = cnt < OV_CHUNK ? (cnt > 0 ? cnt : 0) : OV_CHUNK;
+    setup_rows<KIND, WIDE>(q, P.md[q.mesh], r);
+  }
+  scan_rows_lanes<KIND, WIDE, LOG>(P, q, r, cnt, r0, S.slot, S.mark, S.q, issued);
+}
+
+// The overflow lists (bit 2 k + wide of LISTS: kind k, wide or not) in steps of up
+// to OV_STEP chunks of one part of a list, a persistent grid striding over the
+// steps. The chunks per step grow with the lists, from one (few polyhedra, spread
+// over as many waves as there are) to OV_STEP (each lane sets a polyhedron up).
+// Wide lists, whose distances take FP64, come first.
+template <int LISTS, bool LOG>
+__global__ __launch_bounds__(64 * SCAN_WAVES, 4) void k_scan_over(ScanKinds P) {
+  __shared__ ScanLds lds[SCAN_WAVES];
+  ScanLds& S = lds[threadIdx.x >> 6];
+  const int lane = threadIdx.x & 63;
+  const int64_t nw = (int64_t)gridDim.x * SCAN_WAVES;
+  // lane s: the chunks of part s of list l
+  auto chunks = [&](int l) -> uint32_t {
+    return (LISTS >> l) & 1 ? (uint32_t)(*ov_counter(P.k[l >> 1], l & 1, lane) & OV_MASK) : 0u;
+  };
+  int64_t all = 0;  // (parts counted up to 2^24 chunks each: enough to choose k)
+#pragma unroll
+  for (int l = 0; l < 6; l++) {
+    const uint32_t c = chunks(l);
+    all += __builtin_amdgcn_readlane(wave_prefix_sum((int)(c < (1u << 24) ? c : 1u << 24)), 63);
+  }
+  if (all == 0) return;
+  const int64_t want = (all + nw - 1) / nw;
+  // a logged run takes one chunk per step: the order of the lists varies from run to
+  // run, and the number of its rounds must not
+  const int k = LOG ? 1 : (int)(want < OV_STEP ? want : OV_STEP);
+  unsigned issued = 0;
+  for (int64_t st = (int64_t)blockIdx.x * SCAN_WAVES + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);; st += nw) {
+    // the list of step st (wide faces, edges, vertices, then the others), its part
+    // and the step within the part
+    int64_t at = st;
+    int l = -1, shard = 0;
+    for (int j = 0; j < 6 && l < 0; j++) {
+      const int c = j < 3 ? 2 * j + 1 : 2 * (j - 3);
+      if (!((LISTS >> c) & 1)) continue;
+      const int steps = (int)((chunks(c) + (uint32_t)k - 1u) / (uint32_t)k);
+      const int incl = wave_prefix_sum(steps);
+      const int tot = __builtin_amdgcn_readlane(incl, 63);
+      if (at < tot) {
+        l = c;
+        shard = __popcll(__ballot(incl <= (int)at));
+        at -= __builtin_amdgcn_readlane(incl, shard) - __builtin_amdgcn_readlane(steps, shard);
+      } else {
+        at -= tot;
+      }
+    }
+    if (l < 0) break;
+    const int64_t c0 = at * k;
+    if ((LISTS & 1) && l == 0) scan_chunks<KIND_FACE, false, LOG>(P.k[0], shard, c0, k, S, issued);
+    if ((LISTS & 2) && l == 1) scan_chunks<KIND_FACE, true, LOG>(P.k[0], shard, c0, k, S, issued);
+    if ((LISTS & 4) && l == 2) scan_chunks<KIND_EDGE, false, LOG>(P.k[1], shard, c0, k, S, issued);
+    if ((LISTS & 8) && l == 3) scan_chunks<KIND_EDGE, true, LOG>(P.k[1], shard, c0, k, S, issued);
+    if ((LISTS & 16) && l == 4) scan_chunks<KIND_VERT, false, LOG>(P.k[2], shard, c0, k, S, issued);
+    if ((LISTS & 32) && l == 5) scan_chunks<KIND_VERT, true, LOG>(P.k[2], shard, c0, k, S, issued);
+    if (P.k[l >> 1].counter) {
+      add_issued(P.k[l >> 1], issued, 3);
+      issued = 0;
+    }
+  }
 }
 
 __global__ void k_zero_i32(int32_t* p, int n) {
@@ -1028,7 +1029,8 @@ __global__ void k_zero_u64(unsigned long long* p, int n) {
 // also clears the zn counters at zero
 __global__ void k_init_keys(unsigned long long* keys, const int64_t* __restrict__ stats, int64_t cap,
                             unsigned long long* zero, int zn) {
-  if (blockIdx.x == 0 && (int)threadIdx.x < zn) zero[threadIdx.x] = 0;
+  if (blockIdx.x == 0)
+    for (int i = threadIdx.x; i < zn; i += blockDim.x) zero[i] = 0;
   const int64_t nb = stats[ST_NBRICKS] < cap ? stats[ST_NBRICKS] : cap;
   const int64_t n = nb * BRICK_CELLS;
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
@@ -1233,9 +1235,11 @@ WsLayout ws_layout(const csc_features* f, int64_t cap) {
   L.cnt = au(sizeof(unsigned long long) * (size_t)(cap * BRICK_CELLS + 1));
   L.scan = L.cnt + au(sizeof(int32_t) * (size_t)(cap + 1));
   L.big = L.scan + au(sizeof(int32_t) * (size_t)scan_tmp_ints(cap + 1));
-  // the overflow lists: 6 counters (two per kind), then per kind its entries and
-  // their first chunks (the kinds are scanned concurrently)
-  L.boff = L.big + 256 + au(2 * sizeof(int32_t) * (size_t)(f->nf + 2 * f->ne + 2 * f->nv + 3));
+  // the overflow lists: their counters, then per kind its entries and their first
+  // chunks (the kinds are scanned concurrently)
+  L.boff = L.big + sizeof(unsigned long long) * OV_CTRS_ALL +
+           au(2 * sizeof(int32_t) * (size_t)OV_SHARDS *
+              (size_t)(ov_shard_cap(f->nf) + ov_shard_cap(2 * f->ne) + ov_shard_cap(2 * f->nv)));
   L.ctr = L.boff + au(sizeof(int64_t) * (size_t)(f->n_meshes + 1));
   L.total = L.ctr + au(8 * sizeof(unsigned long long));
   return L;
@@ -1277,7 +1281,7 @@ ScanArgs scan_args(const csc_features* f, unsigned long long* keys, int64_t cap)
   A.ov_items = nullptr;
   A.ov_chunk0 = nullptr;
   A.ov_ctr = nullptr;
-  A.ov_cap = 0;
+  A.ov_shard = 0;
   A.stats = f->d_stats;
   A.cap = cap;
   A.nf = f->nf;
@@ -1325,124 +1329,111 @@ unsigned resident_blocks(K kernel, int threads) {
   return (unsigned)(per_cu * cus);
 }
 
-template <int KIND, bool LOG>
-unsigned small_grid(const ScanArgs& A) {
-  const unsigned need = grid_1d(A.n_items, 256);
-  if (A.grid_mode == SCAN_GRID_LAUNCH) return need;
-  static const unsigned resident = resident_blocks(k_scan_small<KIND, LOG>, 256);
-  return need < resident ? need : resident;
+// the kinds' blocks of the one-lane pass, each kind's own range: a grid sized to
+// the items (SCAN_GRID_LAUNCH) or at most the blocks resident at once; short lists
+// (by their launch bound) get a wave per SCAN_MIN_GROUP items
+template <int KINDS, bool LOG>
+void launch_small(ScanKinds& A, hipStream_t s) {
+  static const unsigned resident = resident_blocks(k_scan_small<KINDS, LOG>, 64 * SCAN_WAVES);
+  A.first[0] = 0;
+  for (int k = 0; k < 3; k++) {
+    ScanArgs& K = A.k[k];
+    unsigned g = 0;
+    if ((KINDS >> k) & 1) {
+      const unsigned full = grid_1d(K.n_items, 64 * SCAN_WAVES), fine = grid_1d(K.n_items, SCAN_MIN_GROUP * SCAN_WAVES);
+      if (K.grid_mode == SCAN_GRID_QUEUE) {
+        g = full < resident ? full : resident;
+        // groups per pop of the group queue: about two pops per wavefront of the
+        // grid (from the launch bound of the item count), at least 1, at most 64
+        const int64_t c = (K.n_items + 63) / 64 / (2 * SCAN_WAVES * (int64_t)g);
+        K.queue_chunk = (int32_t)(c < 1 ? 1 : (c > 64 ? 64 : c));
+      } else {
+        g = fine < resident ? fine : resident;
+        if (K.grid_mode == SCAN_GRID_LAUNCH && full > g) g = full;
+      }
+    }
+    A.first[k + 1] = A.first[k] + g;
+  }
+  k_scan_small<KINDS, LOG><<<A.first[3], 64 * SCAN_WAVES, 0, s>>>(A);
 }
 
-// the chunked overflow pass: every wavefront the device holds at once (a few
-// thousand; an empty list costs one load and exit per wavefront)
-template <int KIND, bool LOG>
-unsigned big_grid() {
-  static const unsigned resident = resident_blocks(k_scan_big<KIND, false, LOG>, 64);
-  return resident;
+// the overflow lists on every wavefront the device holds at once (empty lists
+// cost a load and an exit per wavefront)
+template <int LISTS, bool LOG>
+void launch_over(const ScanKinds& A, hipStream_t s) {
+  static const unsigned resident = resident_blocks(k_scan_over<LISTS, LOG>, 64 * SCAN_WAVES);
+  k_scan_over<LISTS, LOG><<<resident, 64 * SCAN_WAVES, 0, s>>>(A);
 }
 
-// groups per pop of the group queue: about two pops per wavefront of the grid
-// (from the launch bound of the item count), at least 1, at most 64
-inline int32_t queue_chunk(const ScanArgs& A, unsigned blocks) {
-  const int64_t groups = (A.n_items + 63) / 64, waves = 4 * (int64_t)blocks;
-  const int64_t k = groups / (2 * waves);
-  return (int32_t)(k < 1 ? 1 : (k > 64 ? 64 : k));
-}
-
+// one kind by itself: its three launches timed as stages of their own, or their
+// atomics logged
 template <int KIND>
-void launch_kind(ScanArgs A, int stage, int stage_big, hipStream_t s, const AtomicLog* lg) {
+void launch_kind(ScanKinds A, int stage, int stage_big, hipStream_t s, const AtomicLog* lg) {
+  ScanKinds L = A;
+  if (lg) L.k[KIND] = with_log(A.k[KIND], lg);
   {
     StageTimer t(stage, s);
-    if (logged(lg, KIND)) {
-      const unsigned g = small_grid<KIND, true>(A);
-      A.queue_chunk = queue_chunk(A, g);
-      k_scan_small<KIND, true><<<g, 256, 0, s>>>(with_log(A, lg));
-    } else {
-      const unsigned g = small_grid<KIND, false>(A);
-      A.queue_chunk = queue_chunk(A, g);
-      k_scan_small<KIND, false><<<g, 256, 0, s>>>(A);
-    }
+    if (logged(lg, KIND)) launch_small<1 << KIND, true>(L, s);
+    else launch_small<1 << KIND, false>(A, s);
   }
   {
     StageTimer t(stage_big, s);
-    if (logged(lg, 3 + KIND)) k_scan_big<KIND, false, true><<<big_grid<KIND, true>(), 64, 0, s>>>(with_log(A, lg));
-    else k_scan_big<KIND, false, false><<<big_grid<KIND, false>(), 64, 0, s>>>(A);
+    if (logged(lg, 3 + KIND)) launch_over<1 << 2 * KIND, true>(L, s);
+    else launch_over<1 << 2 * KIND, false>(A, s);
   }
-  // wide polyhedra (boxes over WIDE_CELLS): rare, FP64, in chunks of rows
+  // wide polyhedra (boxes over WIDE_CELLS): FP64 distances
   StageTimer t(TS_SCAN_WIDE, s);
-  if (logged(lg, 6 + KIND)) k_scan_big<KIND, true, true><<<PERSIST_BLOCKS / 8, 64, 0, s>>>(with_log(A, lg));
-  else k_scan_big<KIND, true, false><<<PERSIST_BLOCKS / 8, 64, 0, s>>>(A);
+  if (logged(lg, 6 + KIND)) launch_over<2 << 2 * KIND, true>(L, s);
+  else launch_over<2 << 2 * KIND, false>(A, s);
 }
 
 // key initialisation and the scan launches of the three kinds; counters
-// (3 slots) may be null; big: the overflow lists (6 counters in 256 bytes, then
-// each kind's entries and first chunks). For a batch, faces run on
-// the caller's stream and edges, then vertices, on the side stream, forked
-// after the key initialisation and joined at the end (their atomic minima
-// commute): the batch's mix of polyhedron sizes leaves idle slots in each
-// kind's passes (batch of 64: 1.875 -> 1.792 ms per step). One large mesh
-// fills the GPU with each kind alone, and there the overlap only adds
-// contention (1024^3 sphere: 3.43 -> 3.47 ms), so it stays on one stream.
-// With stage timing on, the kinds also run one after another, so that each
-// timed stage is one kernel running alone.
+// (3 slots) may be null; big: the overflow lists (OV_CTRS_ALL counters, then each
+// kind's entries and first chunks). The kinds share one launch of the
+// one-lane pass and one of the overflow pass; with stage timing on, or for a log
+// of the atomics, each kind's launches run alone, one after another.
 // fill_store: every key of the allocated bricks set to empty first; else the
 // caller keeps the store empty between scans (csc_options.keep_store_empty).
 void run_scans(const csc_features* f, unsigned long long* keys, int64_t cap, unsigned long long* counters,
                int32_t* big, hipStream_t s, bool fill_store, const AtomicLog* lg = nullptr) {
   unsigned long long* ov_ctr = (unsigned long long*)big;
-  int32_t* ov = big + 64;  // past the 256 bytes of counters
+  int32_t* ov = big + 2 * OV_CTRS_ALL;
   {
     StageTimer t(TS_INIT, s);
-    // with the overflow lists' two counters and group head per kind
-    if (fill_store) k_init_keys<<<PERSIST_BLOCKS * 4, 256, 0, s>>>(keys, f->d_stats, cap, ov_ctr, 9);
-    else k_init_keys<<<1, 64, 0, s>>>(keys, f->d_stats, 0, ov_ctr, 9);
+    // with the overflow lists' counters and the group heads
+    if (fill_store) k_init_keys<<<PERSIST_BLOCKS * 4, 256, 0, s>>>(keys, f->d_stats, cap, ov_ctr, OV_CTRS_ALL);
+    else k_init_keys<<<1, 1024, 0, s>>>(keys, f->d_stats, 0, ov_ctr, OV_CTRS_ALL);
   }
-  // a fork that cannot be set up leaves everything on the caller's stream
-  bool fork = f->n_meshes > 1 && !stage_timing_on() && f->side && !lg;
-  if (fork)
-    fork = hipEventRecord(f->ev_fork, s) == hipSuccess && hipStreamWaitEvent(f->side, f->ev_fork, 0) == hipSuccess;
-  hipStream_t s2 = fork ? f->side : s;
-  ScanArgs A = scan_args(f, keys, cap);
-  A.grid_mode = f->opt.scan_grid;
-  A.head = ov_ctr + 6;
-  A.ov_ctr = ov_ctr;
-  A.ov_cap = f->nf;
-  A.ov_items = ov;
-  A.ov_chunk0 = ov + f->nf;
-  A.counter = counters;
-  A.n_items = f->nf;
-  A.items = f->face_order_n == f->nf ? f->face_order : nullptr;
-  A.small_rows = f->opt.small_rows[0];
-  A.per_cell = f->opt.scan_mode == 1;
-  launch_kind<KIND_FACE>(A, TS_SCAN_FACE, TS_SCAN_FACE_BIG, s, lg);
-  ov += 2 * f->nf;
-  A.head = ov_ctr + 7;
-  A.ov_ctr = ov_ctr + 2;
-  A.ov_cap = 2 * f->ne;
-  A.ov_items = ov;
-  A.ov_chunk0 = ov + 2 * f->ne;
-  A.small_rows = f->opt.small_rows[1];
-  A.per_cell = f->opt.scan_mode == 1;
-  A.items = f->epoly;
-  A.n_items = 2 * f->ne;
-  A.n_items_d = &f->d_stats[ST_NEPOLY];
-  A.counter = counters ? counters + 1 : nullptr;
-  launch_kind<KIND_EDGE>(A, TS_SCAN_EDGE, TS_SCAN_EDGE_BIG, s2, lg);
-  ov += 4 * f->ne;
-  A.head = ov_ctr + 8;
-  A.ov_ctr = ov_ctr + 4;
-  A.ov_cap = 2 * f->nv;
-  A.ov_items = ov;
-  A.ov_chunk0 = ov + 2 * f->nv;
-  A.small_rows = f->opt.small_rows[2];
-  A.per_cell = f->opt.scan_mode == 1;
-  A.items = f->vpoly;
-  A.n_items = 2 * f->nv;
-  A.n_items_d = &f->d_stats[ST_NVPOLY];
-  A.counter = counters ? counters + 2 : nullptr;
-  launch_kind<KIND_VERT>(A, TS_SCAN_VERT, TS_SCAN_VERT_BIG, s2, lg);
-  if (fork && (hipEventRecord(f->ev_join, s2) != hipSuccess || hipStreamWaitEvent(s, f->ev_join, 0) != hipSuccess))
-    (void)hipStreamSynchronize(s2);  // no join on the device: finish the side branch from the host
+  ScanKinds K;
+  for (int k = 0; k < 3; k++) {
+    ScanArgs& A = K.k[k];
+    A = scan_args(f, keys, cap);
+    const int64_t n = k == KIND_FACE ? f->nf : (k == KIND_EDGE ? 2 * f->ne : 2 * f->nv);
+    A.grid_mode = f->opt.scan_grid;
+    A.head = ov_ctr + 3 * OV_CTRS + k;
+    A.ov_ctr = ov_ctr + k * OV_CTRS;
+    A.ov_shard = ov_shard_cap(n);
+    A.ov_items = ov;
+    A.ov_chunk0 = (uint32_t*)(ov + OV_SHARDS * A.ov_shard);
+    ov += 2 * OV_SHARDS * A.ov_shard;
+    A.counter = counters ? counters + k : nullptr;
+    A.n_items = n;
+    A.small_rows = f->opt.small_rows[k];
+    A.per_cell = f->opt.scan_mode == 1;
+  }
+  K.k[KIND_FACE].items = f->face_order_n == f->nf ? f->face_order : nullptr;
+  K.k[KIND_EDGE].items = f->epoly;
+  K.k[KIND_EDGE].n_items_d = &f->d_stats[ST_NEPOLY];
+  K.k[KIND_VERT].items = f->vpoly;
+  K.k[KIND_VERT].n_items_d = &f->d_stats[ST_NVPOLY];
+  if (!lg && !stage_timing_on()) {
+    launch_small<7, false>(K, s);
+    launch_over<63, false>(K, s);
+    return;
+  }
+  launch_kind<KIND_FACE>(K, TS_SCAN_FACE, TS_SCAN_FACE_BIG, s, lg);
+  launch_kind<KIND_EDGE>(K, TS_SCAN_EDGE, TS_SCAN_EDGE_BIG, s, lg);
+  launch_kind<KIND_VERT>(K, TS_SCAN_VERT, TS_SCAN_VERT_BIG, s, lg);
 }
 
 // after scans with no sign pass: the store left empty again for a caller that
