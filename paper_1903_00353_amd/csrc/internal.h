@@ -32,6 +32,14 @@ static_assert(BRICK_CELLS % 64 == 0 && BRICK_ROUNDS <= 8, "a brick fills whole w
 // of 64 bytes per instruction on a batch of 64 meshes, whose logged atomics
 // then replay 31% faster).
 __host__ __device__ inline int brick_local(int i, int j, int k) {
+  if constexpr (BRICK_SHIFT == 3) {
+    // the three coordinates in fields of 10 bits, the bits of each spread to places 0,
+    // 3 and 6 of its field, then the fields laid over each other one place apart
+    const uint32_t y = (uint32_t)(i & 7) | ((uint32_t)(j & 7) << 10) | ((uint32_t)(k & 7) << 20);
+    constexpr uint32_t M = 1u | (1u << 10) | (1u << 20);
+    const uint32_t z = (y & M) | ((y << 2) & (M << 3)) | ((y << 4) & (M << 6));
+    return (int)((z | (z >> 9) | (z >> 18)) & 511u);
+  }
   int l = 0;
 #pragma unroll
   for (int b = 0; b < BRICK_SHIFT; b++)

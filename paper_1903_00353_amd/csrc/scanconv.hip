@@ -80,6 +80,35 @@ struct I3 {
   int x, y, z;
 };
 
+// The mesh descriptors do not change while a scan runs: read through the constant
+// address space, a descriptor that is the same for the whole wavefront costs
+// scalar loads, which hold no vector registers and do not wait behind the atomics
+// in flight (vector memory operations complete in order). Forward scan: 5.2M faces
+// at 1024^3 631 -> 582 us (one mesh, the fused one-lane pass 128 -> 115 registers),
+// a batch of 64 meshes 736 -> 696 us.
+using MeshConst = const __attribute__((address_space(4))) MeshDesc;
+
+// f(descriptor) for each lane's mesh, once per distinct mesh of the active lanes
+// (a wavefront of neighbouring items mostly holds one). The empty asm keeps the
+// descriptor's address in scalar registers: the compiler would otherwise replace it,
+// where mesh == m, by each lane's own. ONE: the handle holds a single mesh.
+template <bool ONE, class F>
+__device__ inline void with_mesh(const ScanArgs& P, int mesh, F f) {
+  if constexpr (ONE) {
+    f(*(MeshConst*)(uint64_t)(uintptr_t)P.md);
+    return;
+  }
+  unsigned long long left = __ballot(true);
+  while (left != 0) {
+    const int m = __builtin_amdgcn_readlane(mesh, __ffsll((long long)left) - 1);
+    uint64_t at = (uint64_t)(uintptr_t)(P.md + m);
+    asm volatile("" : "+s"(at));
+    const bool mine = mesh == m;
+    if (mine) f(*(MeshConst*)at);
+    left &= ~__ballot(mine);
+  }
+}
+
 struct Poly {
   float pl[5][4];   // inside: m . p + off >= -eps  (p relative to the anchor cell centre)
   float g[9];       // feature points relative to the anchor cell centre
@@ -143,13 +172,15 @@ __device__ inline bool axis_cells(double lo, double hi, double o, double ih, int
 }
 
 // bounding box [lo, hi] (world) -> anchor and dimensions in cells; false if empty
-__device__ inline bool box_cells(const MeshDesc& G, const double lo[3], const double hi[3], Poly& q) {
+template <class Mesh>
+__device__ inline bool box_cells(Mesh& G, const double lo[3], const double hi[3], Poly& q) {
   return axis_cells(lo[0], hi[0], G.origin[0], G.inv_h, G.n[0], q.anc.x, q.dim.x) &&
          axis_cells(lo[1], hi[1], G.origin[1], G.inv_h, G.n[1], q.anc.y, q.dim.y) &&
          axis_cells(lo[2], hi[2], G.origin[2], G.inv_h, G.n[2], q.anc.z, q.dim.z);
 }
 
-__device__ inline d3 anchor_centre(const MeshDesc& G, const Poly& q) {
+template <class Mesh>
+__device__ inline d3 anchor_centre(Mesh& G, const Poly& q) {
   return mkd(G.origin[0] + (q.anc.x + 0.5) * G.h, G.origin[1] + (q.anc.y + 0.5) * G.h,
              G.origin[2] + (q.anc.z + 0.5) * G.h);
 }
@@ -165,7 +196,8 @@ __device__ inline void set_plane(Poly& q, int i, f3 m, f3 through) {
 // caps |n . (x - a)| <= band*h (both the outward and inward prism at once). The
 // side planes move out by the largest slack of the absorbed edges and vertices
 // of the face (the regions of those nearly flat features lie within it).
-__device__ inline int build_face(const ScanArgs& P, const MeshDesc& G, int64_t f, Poly& q) {
+template <class Mesh>
+__device__ inline int build_face(const ScanArgs& P, Mesh& G, int64_t f, Poly& q) {
   const FaceRec& R = P.frec[f];
   const float4 ra = R.c[0], rb = R.c[1], rc = R.c[2], nn = R.n;
   d3 a = mkd(ra.x, ra.y, ra.z), b = mkd(rb.x, rb.y, rb.z), c = mkd(rc.x, rc.y, rc.z);
@@ -205,7 +237,8 @@ __device__ inline int build_face(const ScanArgs& P, const MeshDesc& G, int64_t f
 // (outward side) or their negatives (inward side), between the end caps, cut by
 // the base plane through the edge with the summed normal (Section 8.2); the far
 // side is the band distance itself (cells with |d| >= band*h are dropped).
-__device__ inline int build_edge(const ScanArgs& P, const MeshDesc& G, int32_t ent, Poly& q) {
+template <class Mesh>
+__device__ inline int build_edge(const ScanArgs& P, Mesh& G, int32_t ent, Poly& q) {
   int64_t e = ent >> 1;
   double sg = (ent & 1) ? -1.0 : 1.0;
   int4 E = P.edges[e];
@@ -262,7 +295,8 @@ __device__ inline int build_edge(const ScanArgs& P, const MeshDesc& G, int32_t e
 // Vertex cone (Section 4.2, Section 8.3) about the (possibly reflected)
 // pseudonormal with the most diverging positive-pointing normal on its side, or a
 // hemisphere (Section 4.1.3); box = cone box intersected with the sphere box.
-__device__ inline int build_vertex(const ScanArgs& P, const MeshDesc& G, int32_t ent, Poly& q) {
+template <class Mesh>
+__device__ inline int build_vertex(const ScanArgs& P, Mesh& G, int32_t ent, Poly& q) {
   int64_t v = ent >> 1;
   double sg = (ent & 1) ? -1.0 : 1.0;
   float4 vi = P.vinfo[v];
@@ -308,26 +342,6 @@ __device__ inline int build_vertex(const ScanArgs& P, const MeshDesc& G, int32_t
   return q.dim.x * q.dim.y * q.dim.z;
 }
 
-template <int KIND>
-__device__ inline int build_poly(const ScanArgs& P, int64_t item, Poly& q) {
-  int nc;
-  if constexpr (KIND == KIND_FACE) {
-    const int64_t f = P.items ? P.items[item] : item;  // the face order, if one is set
-    q.mesh = P.face_mesh[f];
-    nc = build_face(P, P.md[q.mesh], f, q);
-  } else if constexpr (KIND == KIND_EDGE) {
-    const int32_t ent = P.items[item];
-    q.mesh = P.face_mesh[P.edges[ent >> 1].z];
-    nc = build_edge(P, P.md[q.mesh], ent, q);
-  } else {
-    const int32_t ent = P.items[item];
-    q.mesh = P.vert_mesh[ent >> 1];
-    nc = build_vertex(P, P.md[q.mesh], ent, q);
-  }
-  q.wide = nc > 0 && max(q.dim.x, max(q.dim.y, q.dim.z)) > WIDE_CELLS;
-  return nc;
-}
-
 __device__ inline int lanes_below(unsigned long long m) {
   return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
@@ -339,17 +353,21 @@ __device__ inline float pick3(float x, float y, float z, int a) {
 }
 
 // Per-plane coefficients along a row: the slack-extended test m . p + off >= -eps at
-// cell (t, du, dv) of the row reads  sl * t + su * du + sv * dv + k >= 0.
+// cell (t, du, dv) of the row reads  sl * t + v >= 0, v = su * du + sv * dv + k, so
+// the plane bounds t below by -v / sl (sl > 0) or above (sl < 0). One of lo and hi
+// holds 1 / sl, the other NaN, which the maximum and minimum over the planes pass
+// over. A plane parallel to the row (|sl| tiny) takes 1e30 in lo: a row outside it
+// gets a bound past every cell, a row inside it one below all.
 struct Rows {
-  float sl[5], inv[5], su[5], sv[5], k[5];
+  float sl[5], lo[5], hi[5], su[5], sv[5], k[5];
   float A[3];       // vertex position (ball test)
   float R2;         // (band*h + eps)^2
   float hf, ihf, eps;  // cell size, its inverse and the slack of the polyhedron's grid
   int nt;           // cells along the row
 };
 
-template <int KIND, bool WIDE>
-__device__ inline void setup_rows(const Poly& q, const MeshDesc& G, Rows& r) {
+template <int KIND, bool WIDE, class Mesh>
+__device__ inline void setup_rows(const Poly& q, Mesh& G, Rows& r) {
   constexpr int NPL = KIND == KIND_VERT ? 1 : 5;
   // a wide polyhedron's planes are rounded at the size of its box: its slack
   // grows by 1e-6 h per cell of extent (several times that rounding)
@@ -357,7 +375,10 @@ __device__ inline void setup_rows(const Poly& q, const MeshDesc& G, Rows& r) {
 #pragma unroll
   for (int i = 0; i < NPL; i++) {
     r.sl[i] = pick3(q.pl[i][0], q.pl[i][1], q.pl[i][2], q.ra) * G.hf;
-    r.inv[i] = fabsf(r.sl[i]) > 1e-20f ? __builtin_amdgcn_rcpf(r.sl[i]) : 0.f;
+    const bool along = fabsf(r.sl[i]) > 1e-20f;
+    const float inv = along ? __builtin_amdgcn_rcpf(r.sl[i]) : 1e30f;
+    r.lo[i] = inv > 0.f ? inv : __builtin_nanf("");
+    r.hi[i] = inv < 0.f ? inv : __builtin_nanf("");
     r.su[i] = pick3(q.pl[i][0], q.pl[i][1], q.pl[i][2], q.ua) * G.hf;
     r.sv[i] = pick3(q.pl[i][0], q.pl[i][1], q.pl[i][2], q.va) * G.hf;
     r.k[i] = q.pl[i][3] + eps;
@@ -372,23 +393,47 @@ __device__ inline void setup_rows(const Poly& q, const MeshDesc& G, Rows& r) {
   r.nt = q.nt;
 }
 
+// the polyhedron of an item and its row coefficients; returns the cells of its box
+// (0: nothing to scan)
+template <int KIND, bool WIDE, bool ONE>
+__device__ inline int build_poly(const ScanArgs& P, int64_t item, Poly& q, Rows& r) {
+  int nc = 0;
+  int64_t f = 0;
+  int32_t ent = 0;
+  if constexpr (KIND == KIND_FACE) f = P.items ? P.items[item] : item;  // the face order, if one is set
+  else ent = P.items[item];
+  auto build = [&](auto& G) {
+    if constexpr (KIND == KIND_FACE) nc = build_face(P, G, f, q);
+    else if constexpr (KIND == KIND_EDGE) nc = build_edge(P, G, ent, q);
+    else nc = build_vertex(P, G, ent, q);
+    if (nc > 0) setup_rows<KIND, WIDE>(q, G, r);
+  };
+  if constexpr (ONE) {
+    q.mesh = 0;
+    build(*(MeshConst*)(uint64_t)(uintptr_t)P.md);
+  } else {
+    if constexpr (KIND == KIND_FACE) q.mesh = P.face_mesh[f];
+    else if constexpr (KIND == KIND_EDGE) q.mesh = P.face_mesh[P.edges[ent >> 1].z];
+    else q.mesh = P.vert_mesh[ent >> 1];
+    build(P.md[q.mesh]);
+  }
+  q.wide = nc > 0 && max(q.dim.x, max(q.dim.y, q.dim.z)) > WIDE_CELLS;
+  return nc;
+}
+
 // cells [t0, t1] of row (du, dv) that can lie in the polyhedron (conservative)
 template <int KIND>
 __device__ inline bool row_range(const Rows& r, int du, int dv, int& t0, int& t1) {
   const float hf = r.hf;
   constexpr int NPL = KIND == KIND_VERT ? 1 : 5;
   float lo = 0.f, hi = (float)(r.nt - 1);
-  bool dead = false;  // a plane parallel to the row with the row outside it
-  // selects, not branches: every lane takes the same instructions
+  // no branches: every lane takes the same instructions
 #pragma unroll
   for (int i = 0; i < NPL; i++) {
     const float v = r.su[i] * du + r.sv[i] * dv + r.k[i];
-    const float x = -v * r.inv[i];
-    lo = fmaxf(lo, r.inv[i] > 0.f ? x : -__builtin_inff());
-    hi = fminf(hi, r.inv[i] < 0.f ? x : __builtin_inff());
-    dead = dead || (r.inv[i] == 0.f && v < 0.f);
+    lo = fmaxf(lo, -v * r.lo[i]);
+    hi = fminf(hi, -v * r.hi[i]);
   }
-  if (dead) return false;
   if constexpr (KIND == KIND_VERT) {  // the ball |p - v| < band*h (+ slack)
     const float qu = du * hf - r.A[1], qv = dv * hf - r.A[2];
     const float disc = r.R2 - qu * qu - qv * qv;
@@ -403,24 +448,17 @@ __device__ inline bool row_range(const Rows& r, int du, int dv, int& t0, int& t1
   return t0 <= t1;
 }
 
-// the brick slot of the last brick looked up (consecutive candidates of a lane
-// mostly share a brick)
-struct BrickCache {
-  int64_t bl = -1;
-  int32_t slot = -1;
-};
-
 // Candidate cells of a wavefront's polyhedra pass through a small ring in LDS:
 // each lane searches the rows of its own polyhedron (cheap interval tests) and
 // appends the cells it finds; every 64 queued candidates are then finished with
 // all 64 lanes busy, each lane fetching the owning lane's polyhedron by lane
 // permutation. This keeps the exact distance and the atomic, the expensive part,
 // free of the imbalance between polyhedra of very different sizes.
-constexpr int QCAP = 128;  // < 64 left after each drain, plus at most 64 appended per round
+constexpr int QCAP = 256;  // < 64 left after each drain, plus up to 192 of a round's cells at once
 
 __device__ inline unsigned long long pack_cand(int lane, int t, int du, int dv) {
-  return ((unsigned long long)lane << 48) | ((unsigned long long)t << 32) | ((unsigned long long)du << 16) |
-         (unsigned long long)dv;
+  const uint32_t hi = ((uint32_t)lane << 16) | (uint32_t)t, lo = ((uint32_t)du << 16) | (uint32_t)dv;
+  return ((unsigned long long)hi << 32) | lo;
 }
 
 // a value of the polyhedron held by lane L
@@ -436,7 +474,7 @@ __device__ inline T from_lane(T x, int L) {
 // 4.1.3), so that it stays right next to the surface however far the corners
 // lie. False when the cell lies outside the band.
 template <int KIND>
-__device__ inline bool dist_wide(const ScanArgs& P, const MeshDesc& G, int id, int i, int j, int k, float& d,
+__device__ inline bool dist_wide(const ScanArgs& P, MeshConst& G, int id, int i, int j, int k, float& d,
                                  uint32_t& code) {
   const d3 c = mkd(G.origin[0] + (i + 0.5) * G.h, G.origin[1] + (j + 0.5) * G.h, G.origin[2] + (k + 0.5) * G.h);
   const d3 o = mkd(0.0, 0.0, 0.0);
@@ -500,98 +538,106 @@ __device__ inline void log_atomic(const ScanArgs& P, uint32_t at) {
   }
 }
 
-// exact distance of one queued candidate and its packed atomic minimum; called by
+// Exact distance of one queued candidate and its packed atomic minimum; called by
 // all lanes of the wavefront together (lane permutations), `valid` per lane.
 // WIDE (overflow pass only): the distance in FP64 (dist_wide). LOG: record the
 // atomic instruction (diagnostic instantiation).
-template <int KIND, bool WIDE, bool LOG>
+// What bounds it: vector instructions, and the wait for the brick slot, a load that
+// also waits for the atomics issued before it. The slot is therefore asked for
+// before the distance is computed (for every candidate, also those the distance
+// drops) and read after it.
+template <int KIND, bool WIDE, bool ONE, bool LOG>
 __device__ inline void finish_cand(const ScanArgs& P, const Poly& q, unsigned long long ent, bool valid,
-                                   BrickCache& bc, unsigned& issued) {
+                                   unsigned& issued) {
   const int L = valid ? (int)(ent >> 48) : 0;
-  const int t = (int)((ent >> 32) & 0xffff), du = (int)((ent >> 16) & 0xffff), dv = (int)(ent & 0xffff);
-  const int mesh = from_lane(q.mesh, L), id = from_lane(q.id, L);
+  const int t = (int)((ent >> 32) & 0xffff), du = (int)((uint32_t)ent >> 16), dv = (int)((uint32_t)ent & 0xffff);
+  const int mesh = ONE ? 0 : from_lane(q.mesh, L), id = from_lane(q.id, L);
   // row axes, with the face's absorbed features above them (one lane move).
   // Every pass decides the same cells: the packed key orders equal distances by
   // sign code before feature id, so a face whose boundary cell one pass decided
   // and another left open would win or lose a tie by schedule.
   const int axes = from_lane(q.ra | (q.ua << 2) | (q.absorbed << 4), L);
   const int ax = from_lane(q.anc.x, L), ay = from_lane(q.anc.y, L), az = from_lane(q.anc.z, L);
-  const f3 g0 = mk(from_lane(q.g[0], L), from_lane(q.g[1], L), from_lane(q.g[2], L));
-  f3 g1 = mk(0.f, 0.f, 0.f), g2 = mk(0.f, 0.f, 0.f), nn = mk(0.f, 0.f, 0.f);
-  float side = 1.f;
-  if constexpr (KIND == KIND_FACE) {
-    g1 = mk(from_lane(q.g[3], L), from_lane(q.g[4], L), from_lane(q.g[5], L));
-    g2 = mk(from_lane(q.g[6], L), from_lane(q.g[7], L), from_lane(q.g[8], L));
-    nn = mk(from_lane(q.cone[0], L), from_lane(q.cone[1], L), from_lane(q.cone[2], L));
-  } else if constexpr (KIND == KIND_EDGE) {
-    g1 = mk(from_lane(q.g[3], L), from_lane(q.g[4], L), from_lane(q.g[5], L));
-    nn = mk(from_lane(q.pl[4][0], L), from_lane(q.pl[4][1], L), from_lane(q.pl[4][2], L));
-    side = from_lane(q.side, L);
-  } else {
-    nn = mk(from_lane(q.cone[0], L), from_lane(q.cone[1], L), from_lane(q.cone[2], L));
-    side = from_lane(q.side, L);
+  [[maybe_unused]] f3 g0 = mk(0.f, 0.f, 0.f), g1 = g0, g2 = g0, nn = g0;
+  [[maybe_unused]] float side = 1.f;
+  if constexpr (!WIDE) {
+    g0 = mk(from_lane(q.g[0], L), from_lane(q.g[1], L), from_lane(q.g[2], L));
+    if constexpr (KIND == KIND_FACE) {
+      g1 = mk(from_lane(q.g[3], L), from_lane(q.g[4], L), from_lane(q.g[5], L));
+      g2 = mk(from_lane(q.g[6], L), from_lane(q.g[7], L), from_lane(q.g[8], L));
+      nn = mk(from_lane(q.cone[0], L), from_lane(q.cone[1], L), from_lane(q.cone[2], L));
+    } else if constexpr (KIND == KIND_EDGE) {
+      g1 = mk(from_lane(q.g[3], L), from_lane(q.g[4], L), from_lane(q.g[5], L));
+      nn = mk(from_lane(q.pl[4][0], L), from_lane(q.pl[4][1], L), from_lane(q.pl[4][2], L));
+      side = from_lane(q.side, L);
+    } else {
+      nn = mk(from_lane(q.cone[0], L), from_lane(q.cone[1], L), from_lane(q.cone[2], L));
+      side = from_lane(q.side, L);
+    }
   }
   if (!valid) return;
-  const MeshDesc& G = P.md[mesh];
   const int ra = axes & 3, ua = (axes >> 2) & 3;
   const int di = ra == 0 ? t : (ua == 0 ? du : dv);
   const int dj = ra == 1 ? t : (ua == 1 ? du : dv);
   const int dk = ra == 2 ? t : (ua == 2 ? du : dv);
   const int i = ax + di, j = ay + dj, k = az + dk;
-  float d;
-  uint32_t code;
-  if constexpr (WIDE) {
-    if (!dist_wide<KIND>(P, G, id, i, j, k, d, code)) return;
-  } else {
-  const float hf = G.hf;
-  const f3 p = mk(di * hf, dj * hf, dk * hf);
-  if constexpr (KIND == KIND_FACE) {
-    f3 qq;
-    float w[3];
-    const int region = closest_triangle(p, g0, g1, g2, qq, w);
-    d = norm3(p - qq);
-    // Interior closest point: the face normal is the pseudonormal. On the
-    // boundary, at an absorbed edge or vertex (region r: edge from corner r - 1,
-    // or corner r - 4; bit r - 1 either way), the face normal gives the same
-    // sign: such a cell sees the feature along a direction within 90 degrees of
-    // every incident face normal (the absorption bound, an angle under 45
-    // degrees, at most doubled), so its dot products with the face normal and
-    // with the feature's pseudonormal share their sign. Other boundary points
-    // are left to the sign pass.
-    const bool own = region == 0 || ((axes >> (3 + region)) & 1);
-    code = !own ? SIGN_OPEN : (dot(p - qq, nn) >= 0.f ? SIGN_POS : SIGN_NEG);
-  } else if constexpr (KIND == KIND_EDGE) {
-    float tt;
-    const f3 qq = closest_segment(p, g0, g1, tt);
-    d = norm3(p - qq);
-    // interior of the edge: pseudonormal n1 + n2 = side * (base plane normal) * |n1 + n2|
-    const bool ok = tt > 0.f && tt < 1.f && dot(nn, nn) > 0.f;
-    code = !ok ? SIGN_OPEN : (dot(p - qq, nn) * side >= 0.f ? SIGN_POS : SIGN_NEG);
-  } else {
-    const f3 rr = p - g0;
-    d = norm3(rr);
-    // the vertex itself: its angle-weighted pseudonormal (axis = side * N)
-    code = dot(rr, nn) * side >= 0.f ? SIGN_POS : SIGN_NEG;
-  }
-  if (!(d < G.whf)) return;
-  }
-  const int64_t bl = brick_pos(G, i >> BRICK_SHIFT, j >> BRICK_SHIFT, k >> BRICK_SHIFT);
-  if (bl != bc.bl) {
-    bc.bl = bl;
-    bc.slot = P.brick_index[bl];
-  }
-  const int32_t slot = bc.slot;
-  if (slot >= 0 && slot < P.cap) {
-    const unsigned long long key = ((unsigned long long)__float_as_uint(d) << 32) | (code << 30) | (uint32_t)id;
-    const int64_t at = (int64_t)slot * BRICK_CELLS + brick_local(i, j, k);
-    if constexpr (LOG) log_atomic(P, (uint32_t)at);
-    atomicMin(&P.keys[at], key);
-    issued++;
-  } else if (slot >= P.cap) {
-    atomicOr((uint32_t*)&P.stats[ST_ERR], ERR_OVERFLOW);
-  }
+  with_mesh<ONE>(P, mesh, [&](MeshConst& G) {
+    const int bx = i >> BRICK_SHIFT, by = j >> BRICK_SHIFT, bz = k >> BRICK_SHIFT;
+    const int tile = (bx >> 2) + G.nt[0] * ((by >> 2) + G.nt[1] * (bz >> 2));  // brick_pos, below 2^26
+    const uint32_t pos = (uint32_t)(G.brick_base + (tile << 6) + (bx & 3) + ((by & 3) << 2) + ((bz & 3) << 4));
+    const int32_t slot = P.brick_index[pos];
+    const int local = brick_local(i, j, k);
+    float d;
+    uint32_t code;
+    bool in;
+    if constexpr (WIDE) {
+      in = dist_wide<KIND>(P, G, id, i, j, k, d, code);
+    } else {
+      const float hf = G.hf;
+      const f3 p = mk(di * hf, dj * hf, dk * hf);
+      if constexpr (KIND == KIND_FACE) {
+        f3 qq;
+        float w[3];
+        const int region = closest_triangle(p, g0, g1, g2, qq, w);
+        d = norm3(p - qq);
+        // Interior closest point: the face normal is the pseudonormal. On the
+        // boundary, at an absorbed edge or vertex (region r: edge from corner r - 1,
+        // or corner r - 4; bit r - 1 either way), the face normal gives the same
+        // sign: such a cell sees the feature along a direction within 90 degrees of
+        // every incident face normal (the absorption bound, an angle under 45
+        // degrees, at most doubled), so its dot products with the face normal and
+        // with the feature's pseudonormal share their sign. Other boundary points
+        // are left to the sign pass.
+        const bool own = region == 0 || ((axes >> (3 + region)) & 1);
+        code = !own ? SIGN_OPEN : (dot(p - qq, nn) >= 0.f ? SIGN_POS : SIGN_NEG);
+      } else if constexpr (KIND == KIND_EDGE) {
+        float tt;
+        const f3 qq = closest_segment(p, g0, g1, tt);
+        d = norm3(p - qq);
+        // interior of the edge: pseudonormal n1 + n2 = side * (base plane normal) * |n1 + n2|
+        const bool ok = tt > 0.f && tt < 1.f && dot(nn, nn) > 0.f;
+        code = !ok ? SIGN_OPEN : (dot(p - qq, nn) * side >= 0.f ? SIGN_POS : SIGN_NEG);
+      } else {
+        const f3 rr = p - g0;
+        d = norm3(rr);
+        // the vertex itself: its angle-weighted pseudonormal (axis = side * N)
+        code = dot(rr, nn) * side >= 0.f ? SIGN_POS : SIGN_NEG;
+      }
+      in = d < G.whf;
+    }
+    if (in && slot >= 0) {
+      if (slot < P.cap) {
+        const unsigned long long key = ((unsigned long long)__float_as_uint(d) << 32) | (code << 30) | (uint32_t)id;
+        const int64_t at = (int64_t)slot * BRICK_CELLS + local;
+        if constexpr (LOG) log_atomic(P, (uint32_t)at);
+        atomicMin(&P.keys[at], key);
+        issued++;
+      } else {
+        atomicOr((uint32_t*)&P.stats[ST_ERR], ERR_OVERFLOW);
+      }
+    }
+  });
 }
-
 
 // Alg. 2 for one cell: every half-space with slack (and, for vertices, the
 // ball of radius band*h); the per-cell alternative to the row interval
@@ -608,12 +654,12 @@ __device__ inline bool cell_in(const Rows& o, int t, int du, int dv) {
   return in;
 }
 
-// The row coefficients of every lane's polyhedron, staged in LDS for the
-// one-polyhedron-per-lane pass so that the lane taking a row reads its owner's
-// with a few 16-byte loads: faces and edges inv, su, sv, k, sl of their five
-// planes, then nt, the owner's first row in the wavefront's numbering and nu;
-// vertices the same for their one plane, then the ball and cone data in (row,
-// u, v) order.
+// The row coefficients of every lane's polyhedron, staged in LDS so that the lane
+// taking a row reads its owner's with a few 16-byte loads: faces and edges lo, hi,
+// su, sv, k of their five planes, then nt and nu, the row number of the owner's row
+// 0 in the wavefront's numbering and 1 / nu; vertices the same for their one plane,
+// then the ball and cone data in (row, u, v) order. With every cell tested by
+// itself (per_cell) sl takes lo's place.
 template <int KIND>
 struct RowSlot {
   static constexpr int F4 = KIND == KIND_VERT ? 5 : 7;  // float4 per lane
@@ -621,24 +667,30 @@ struct RowSlot {
 
 struct RowsOf {
   Rows o;
-  int excl, nu;  // excl: the row number (of the wavefront's numbering) of the owner's row 0
+  int row0, nu;  // row0: the row number (of the wavefront's numbering) of the owner's row 0
+  float inv_nu;
   f3 cax;       // vertices: cone axis in (row, u, v) order
   float cct;    // vertices: aperture cosine, or below -1 for a hemisphere
 };
 
 template <int KIND>
-__device__ inline void put_slot(float4* sl, const Rows& r, const Poly& q, int excl) {
+__device__ inline void put_slot(float4* sl, const Rows& r, const Poly& q, int row0, bool per_cell) {
+  const float dims = __uint_as_float((uint32_t)r.nt | ((uint32_t)q.nu << 16));  // each below 2^16
+  const float inv_nu = __builtin_amdgcn_rcpf((float)q.nu);
   if constexpr (KIND != KIND_VERT) {
-    sl[0] = make_float4(r.inv[0], r.inv[1], r.inv[2], r.inv[3]);
-    sl[1] = make_float4(r.inv[4], r.su[0], r.su[1], r.su[2]);
-    sl[2] = make_float4(r.su[3], r.su[4], r.sv[0], r.sv[1]);
-    sl[3] = make_float4(r.sv[2], r.sv[3], r.sv[4], r.k[0]);
-    sl[4] = make_float4(r.k[1], r.k[2], r.k[3], r.k[4]);
-    sl[5] = make_float4(r.sl[0], r.sl[1], r.sl[2], r.sl[3]);
-    sl[6] = make_float4(r.sl[4], __int_as_float(r.nt), __int_as_float(excl), __int_as_float(q.nu));
+    float a[5];
+#pragma unroll
+    for (int i = 0; i < 5; i++) a[i] = per_cell ? r.sl[i] : r.lo[i];
+    sl[0] = make_float4(a[0], a[1], a[2], a[3]);
+    sl[1] = make_float4(a[4], r.hi[0], r.hi[1], r.hi[2]);
+    sl[2] = make_float4(r.hi[3], r.hi[4], r.su[0], r.su[1]);
+    sl[3] = make_float4(r.su[2], r.su[3], r.su[4], r.sv[0]);
+    sl[4] = make_float4(r.sv[1], r.sv[2], r.sv[3], r.sv[4]);
+    sl[5] = make_float4(r.k[0], r.k[1], r.k[2], r.k[3]);
+    sl[6] = make_float4(r.k[4], dims, __int_as_float(row0), inv_nu);
   } else {
-    sl[0] = make_float4(r.inv[0], r.su[0], r.sv[0], r.k[0]);
-    sl[1] = make_float4(r.sl[0], __int_as_float(r.nt), __int_as_float(excl), __int_as_float(q.nu));
+    sl[0] = make_float4(per_cell ? r.sl[0] : r.lo[0], r.hi[0], r.su[0], r.sv[0]);
+    sl[1] = make_float4(r.k[0], dims, __int_as_float(row0), inv_nu);
     sl[2] = make_float4(r.A[0], r.A[1], r.A[2], r.R2);
     sl[3] = make_float4(r.hf, r.ihf, r.eps, q.cone[3]);
     sl[4] = make_float4(pick3(q.cone[0], q.cone[1], q.cone[2], q.ra), pick3(q.cone[0], q.cone[1], q.cone[2], q.ua),
@@ -649,29 +701,42 @@ __device__ inline void put_slot(float4* sl, const Rows& r, const Poly& q, int ex
 template <int KIND>
 __device__ inline RowsOf get_slot(const float4* sl) {
   RowsOf w;
+  float4 last;
   if constexpr (KIND != KIND_VERT) {
-    const float4 a = sl[0], b = sl[1], c = sl[2], d = sl[3], e = sl[4], f = sl[5], g = sl[6];
-    w.o.inv[0] = a.x; w.o.inv[1] = a.y; w.o.inv[2] = a.z; w.o.inv[3] = a.w; w.o.inv[4] = b.x;
-    w.o.su[0] = b.y; w.o.su[1] = b.z; w.o.su[2] = b.w; w.o.su[3] = c.x; w.o.su[4] = c.y;
-    w.o.sv[0] = c.z; w.o.sv[1] = c.w; w.o.sv[2] = d.x; w.o.sv[3] = d.y; w.o.sv[4] = d.z;
-    w.o.k[0] = d.w; w.o.k[1] = e.x; w.o.k[2] = e.y; w.o.k[3] = e.z; w.o.k[4] = e.w;
-    w.o.sl[0] = f.x; w.o.sl[1] = f.y; w.o.sl[2] = f.z; w.o.sl[3] = f.w; w.o.sl[4] = g.x;
-    w.o.nt = __float_as_int(g.y);
-    w.excl = __float_as_int(g.z);
-    w.nu = __float_as_int(g.w);
+    const float4 a = sl[0], b = sl[1], c = sl[2], d = sl[3], e = sl[4], f = sl[5];
+    last = sl[6];
+    w.o.lo[0] = a.x; w.o.lo[1] = a.y; w.o.lo[2] = a.z; w.o.lo[3] = a.w; w.o.lo[4] = b.x;
+    w.o.hi[0] = b.y; w.o.hi[1] = b.z; w.o.hi[2] = b.w; w.o.hi[3] = c.x; w.o.hi[4] = c.y;
+    w.o.su[0] = c.z; w.o.su[1] = c.w; w.o.su[2] = d.x; w.o.su[3] = d.y; w.o.su[4] = d.z;
+    w.o.sv[0] = d.w; w.o.sv[1] = e.x; w.o.sv[2] = e.y; w.o.sv[3] = e.z; w.o.sv[4] = e.w;
+    w.o.k[0] = f.x; w.o.k[1] = f.y; w.o.k[2] = f.z; w.o.k[3] = f.w; w.o.k[4] = last.x;
     w.cct = -2.f;
   } else {
-    const float4 a = sl[0], b = sl[1], c = sl[2], d = sl[3], e = sl[4];
-    w.o.inv[0] = a.x; w.o.su[0] = a.y; w.o.sv[0] = a.z; w.o.k[0] = a.w;
-    w.o.sl[0] = b.x;
-    w.o.nt = __float_as_int(b.y);
-    w.excl = __float_as_int(b.z);
-    w.nu = __float_as_int(b.w);
+    const float4 a = sl[0], c = sl[2], d = sl[3], e = sl[4];
+    last = sl[1];
+    w.o.lo[0] = a.x; w.o.hi[0] = a.y; w.o.su[0] = a.z; w.o.sv[0] = a.w; w.o.k[0] = last.x;
     w.o.A[0] = c.x; w.o.A[1] = c.y; w.o.A[2] = c.z; w.o.R2 = c.w;
     w.o.hf = d.x; w.o.ihf = d.y; w.o.eps = d.z; w.cct = d.w;
     w.cax = mk(e.x, e.y, e.z);
   }
+#pragma unroll
+  for (int i = 0; i < (KIND == KIND_VERT ? 1 : 5); i++) w.o.sl[i] = w.o.lo[i];  // per_cell
+  w.o.nt = (int)(__float_as_uint(last.y) & 0xffffu);
+  w.nu = (int)(__float_as_uint(last.y) >> 16);
+  w.row0 = __float_as_int(last.z);
+  w.inv_nu = last.w;
   return w;
+}
+
+// floor(a / b) for 0 <= a < 2^31 and 1 <= b with a quotient below 2^16, inv = 1 / b
+// to about 1 ulp: the float quotient (error below 2^-6) is at most one off, and the
+// remainder puts it right
+__device__ inline int div_rows(int a, int b, float inv) {
+  int q = (int)((float)a * inv);
+  const int r = a - q * b;
+  q += r >= b ? 1 : 0;
+  q -= r < 0 ? 1 : 0;
+  return q;
 }
 
 // The rows of the wavefront's polyhedra (lane l holds `rows` rows of its own
@@ -683,17 +748,21 @@ __device__ inline RowsOf get_slot(const float4* sl) {
 // and queues its candidate cells in the wavefront's ring under the owner's lane
 // number; every 64 queued cells are finished by all lanes together. Must be
 // called by all lanes of the wavefront.
-template <int KIND, bool WIDE, bool LOG>
+template <int KIND, bool WIDE, bool ONE, bool LOG>
 __device__ inline void scan_rows_lanes(const ScanArgs& P, const Poly& q, const Rows& r, int rows, int row0,
                                        float4* slots, int* marks, unsigned long long* qb, unsigned& issued) {
   constexpr int F4 = RowSlot<KIND>::F4;
   const int lane = threadIdx.x & 63;
   const int incl = wave_prefix_sum(rows), excl = incl - rows;
   const int total = __builtin_amdgcn_readlane(incl, 63);
-  if (rows > 0) put_slot<KIND>(slots + lane * F4, r, q, excl - row0);
+  if (rows > 0) put_slot<KIND>(slots + lane * F4, r, q, excl - row0, P.per_cell);
   uint32_t head = 0, tail = 0;  // the same in every lane
-  BrickCache bc;
   int carry = 0;
+  auto drain = [&]() {  // 64 queued cells
+    wave_sync_lds();
+    finish_cand<KIND, WIDE, ONE, LOG>(P, q, qb[(head + lane) & (QCAP - 1)], true, issued);
+    head += 64;
+  };
   for (int base = 0; base < total; base += 64) {
     marks[lane] = -1;
     wave_sync_lds();
@@ -704,9 +773,8 @@ __device__ inline void scan_rows_lanes(const ScanArgs& P, const Poly& q, const R
     carry = __builtin_amdgcn_readlane(L, 63);
     const int g = base + lane;
     const RowsOf w = get_slot<KIND>(slots + L * F4);
-    const int rloc = g - w.excl;
-    const int nud = w.nu > 0 ? w.nu : 1;
-    const int dv = g < total ? rloc / nud : 0, du = g < total ? rloc - dv * nud : 0;
+    const int rloc = g < total ? g - w.row0 : 0;
+    const int dv = div_rows(rloc, w.nu, w.inv_nu), du = rloc - dv * w.nu;
     int t = 0, t1 = -1;
     if (P.per_cell) {  // every cell of the row, each tested by itself below
       t = 0;
@@ -715,26 +783,51 @@ __device__ inline void scan_rows_lanes(const ScanArgs& P, const Poly& q, const R
       t1 = -1;
     }
     if (g >= total) t1 = -1;
-    while (true) {
-      const bool has = t <= t1;
-      if (__ballot(has) == 0) break;
-      bool push = has && (!P.per_cell || cell_in<KIND>(w.o, t, du, dv));
-      if constexpr (KIND == KIND_VERT) {  // cone discriminant with slack (Eq. 10)
-        if (push && w.cct > -1.f) {
-          const f3 rr = mk(t * w.o.hf - w.o.A[0], du * w.o.hf - w.o.A[1], dv * w.o.hf - w.o.A[2]);
-          const float te = dot(rr, w.cax) + w.o.eps;
-          push = te >= 0.f && te * te >= w.cct * w.cct * dot(rr, rr);
+    unsigned long long cand = pack_cand(L, t, du, dv);
+    if (KIND != KIND_VERT && !P.per_cell) {
+      // every cell of the interval is queued: a lane's cells go to consecutive ring
+      // places from its prefix of the counts on, as many rounds' cells at a time as
+      // the ring takes
+      int n = t1 >= t ? t1 - t + 1 : 0;
+      const int ci = wave_prefix_sum(n);
+      const int all = __builtin_amdgcn_readlane(ci, 63);
+      int at = ci - n;  // this lane's next cell in the round's numbering
+      for (int done = 0; done < all;) {
+        const int room = QCAP - (int)(tail - head), end = all - done < room ? all : done + room;
+        int k = (at + n < end ? at + n : end) - at;  // this lane's cells of this part
+        uint32_t slot = tail + (uint32_t)(at - done);
+        while (__ballot(k > 0) != 0) {
+          if (k > 0) {
+            qb[slot & (QCAP - 1)] = cand;
+            slot++;
+            cand += 1ull << 32;
+            at++;
+            n--;
+            k--;
+          }
         }
+        tail += (uint32_t)(end - done);
+        done = end;
+        while (tail - head >= 64) drain();
       }
-      const unsigned long long pm = __ballot(push);
-      if (push) qb[(tail + lanes_below(pm)) & (QCAP - 1)] = pack_cand(L, t, du, dv);
-      tail += (uint32_t)__popcll(pm);
-      if (has) t++;
-      if (tail - head >= 64) {
-        wave_sync_lds();
-        const unsigned long long e = qb[(head + lane) & (QCAP - 1)];
-        finish_cand<KIND, WIDE, LOG>(P, q, e, true, bc, issued);
-        head += 64;
+    } else {
+      while (true) {
+        const bool has = t <= t1;
+        if (__ballot(has) == 0) break;
+        bool push = has && (!P.per_cell || cell_in<KIND>(w.o, t, du, dv));
+        if constexpr (KIND == KIND_VERT) {  // cone discriminant with slack (Eq. 10)
+          if (push && w.cct > -1.f) {
+            const f3 rr = mk(t * w.o.hf - w.o.A[0], du * w.o.hf - w.o.A[1], dv * w.o.hf - w.o.A[2]);
+            const float te = dot(rr, w.cax) + w.o.eps;
+            push = te >= 0.f && te * te >= w.cct * w.cct * dot(rr, rr);
+          }
+        }
+        const unsigned long long pm = __ballot(push);
+        if (push) qb[(tail + lanes_below(pm)) & (QCAP - 1)] = cand;
+        cand += 1ull << 32;
+        tail += (uint32_t)__popcll(pm);
+        if (has) t++;
+        if (tail - head >= 64) drain();
       }
     }
   }
@@ -742,7 +835,7 @@ __device__ inline void scan_rows_lanes(const ScanArgs& P, const Poly& q, const R
     wave_sync_lds();
     const bool valid = (uint32_t)lane < tail - head;
     const unsigned long long e = valid ? qb[(head + lane) & (QCAP - 1)] : 0ull;
-    finish_cand<KIND, WIDE, LOG>(P, q, e, valid, bc, issued);
+    finish_cand<KIND, WIDE, ONE, LOG>(P, q, e, valid, issued);
   }
   // the ring, slots and marks are reused by the next call: finish the reads first
   __builtin_amdgcn_wave_barrier();
@@ -829,19 +922,18 @@ constexpr int SCAN_ROWS = 32;
 // one polyhedron per lane, the rows of a wavefront's polyhedra shared by its
 // lanes; polyhedra with more than small_rows rows go to the front of the
 // overflow list, wide ones to its back
-template <int KIND, bool LOG>
+template <int KIND, bool ONE, bool LOG>
 __device__ inline void scan_group(const ScanArgs& P, int64_t item, bool has, int small_rows, float4* slots, int* marks,
                                   unsigned long long* qb, unsigned& issued) {
-  Poly q;  // not cleared: a lane without a polyhedron owns no row, so no lane reads it
+  Poly q;  // not cleared, like r: a lane without a polyhedron owns no row, so no lane reads it
+  Rows r;
   q.wide = 0;
-  const int nc = has ? build_poly<KIND>(P, item, q) : 0;
+  const int nc = has ? build_poly<KIND, false, ONE>(P, item, q, r) : 0;
   const int rows = nc > 0 ? q.nu * q.nv : 0;
   const bool big = nc > 0 && (rows > small_rows || q.wide);
   ov_append(P, big && !q.wide, 0, item, rows);
   ov_append(P, big && q.wide, 1, item, rows);
-  Rows r;  // set only for lanes with rows to deal; rows past the end are dropped whatever it holds
-  if (nc > 0 && !big) setup_rows<KIND, false>(q, P.md[q.mesh], r);
-  scan_rows_lanes<KIND, false, LOG>(P, q, r, nc > 0 && !big ? rows : 0, 0, slots, marks, qb, issued);
+  scan_rows_lanes<KIND, false, ONE, LOG>(P, q, r, nc > 0 && !big ? rows : 0, 0, slots, marks, qb, issued);
 }
 
 // the LDS of one wavefront of the scan passes
@@ -853,7 +945,7 @@ struct ScanLds {
 constexpr int SCAN_WAVES = 4;  // wavefronts per block
 
 // this block's share of one kind: block b of nb
-template <int KIND, bool LOG>
+template <int KIND, bool ONE, bool LOG>
 __device__ inline void scan_kind(const ScanArgs& P, unsigned b, unsigned nb, ScanLds& S) {
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int64_t count = item_count(P);
@@ -871,7 +963,7 @@ __device__ inline void scan_kind(const ScanArgs& P, unsigned b, unsigned nb, Sca
     // every wave leaves once its next chunk starts past the last group
     for (int64_t g0 = pop(); g0 < groups; g0 = pop())
       for (int64_t g = g0; g < g0 + k && g < groups; g++)
-        scan_group<KIND, LOG>(P, 64 * g + lane, 64 * g + lane < count, P.small_rows ? P.small_rows : SCAN_ROWS, S.slot,
+        scan_group<KIND, ONE, LOG>(P, 64 * g + lane, 64 * g + lane < count, P.small_rows ? P.small_rows : SCAN_ROWS, S.slot,
                               S.mark, S.q, issued);
   } else {
     int gw = SCAN_MIN_GROUP;
@@ -880,7 +972,7 @@ __device__ inline void scan_kind(const ScanArgs& P, unsigned b, unsigned nb, Sca
     // (a grid sized to 64 items per wave covers the list in one step whatever gw)
     for (int64_t g = (int64_t)b * SCAN_WAVES + w; g * gw < count; g += nw) {
       const int64_t item = g * gw + lane;
-      scan_group<KIND, LOG>(P, item, lane < gw && item < count, small_rows, S.slot, S.mark, S.q, issued);
+      scan_group<KIND, ONE, LOG>(P, item, lane < gw && item < count, small_rows, S.slot, S.mark, S.q, issued);
     }
   }
   add_issued(P, issued, 0);
@@ -890,24 +982,25 @@ __device__ inline void scan_kind(const ScanArgs& P, unsigned b, unsigned nb, Sca
 struct ScanKinds {
   ScanArgs k[3];
   unsigned first[4];
+  bool single;  // one mesh
 };
 
 // KINDS: bit k for kind k. All three (7) in the scans; one alone where a stage is
 // timed or its atomics logged. Together the kinds fill the device where one
 // alone leaves it idle (a 20,480-face sphere: 80 + 240 + 80 blocks), and their
 // last waves overlap.
-template <int KINDS, bool LOG>
+template <int KINDS, bool ONE, bool LOG>
 __global__ __launch_bounds__(64 * SCAN_WAVES, 4) void k_scan_small(ScanKinds P) {
   __shared__ ScanLds lds[SCAN_WAVES];
   ScanLds& S = lds[threadIdx.x >> 6];
   const unsigned b = blockIdx.x;
   if constexpr ((KINDS & 1) != 0)
-    if (b < P.first[1]) scan_kind<KIND_FACE, LOG>(P.k[0], b, P.first[1], S);
+    if (b < P.first[1]) scan_kind<KIND_FACE, ONE, LOG>(P.k[0], b, P.first[1], S);
   if constexpr ((KINDS & 2) != 0)
     if (b >= P.first[1] && b < P.first[2])
-      scan_kind<KIND_EDGE, LOG>(P.k[1], b - P.first[1], P.first[2] - P.first[1], S);
+      scan_kind<KIND_EDGE, ONE, LOG>(P.k[1], b - P.first[1], P.first[2] - P.first[1], S);
   if constexpr ((KINDS & 4) != 0)
-    if (b >= P.first[2]) scan_kind<KIND_VERT, LOG>(P.k[2], b - P.first[2], P.first[3] - P.first[2], S);
+    if (b >= P.first[2]) scan_kind<KIND_VERT, ONE, LOG>(P.k[2], b - P.first[2], P.first[3] - P.first[2], S);
 }
 
 // Chunks c0 .. c0 + k - 1 (k <= OV_STEP, fewer at its end) of one part of an overflow
@@ -917,7 +1010,7 @@ __global__ __launch_bounds__(64 * SCAN_WAVES, 4) void k_scan_small(ScanKinds P) 
 // the j-th of 64 evenly spaced entries; chunk numbers grow along the list). Every
 // entry holds at least one chunk, so the chunks lie in that entry and the 63
 // after it, and each lane finds its own as a row finds its polyhedron.
-template <int KIND, bool WIDE, bool LOG>
+template <int KIND, bool WIDE, bool ONE, bool LOG>
 __device__ inline void scan_chunks(const ScanArgs& P, int shard, int64_t c0, int k, ScanLds& S, unsigned& issued) {
   const int lane = threadIdx.x & 63;
   const unsigned long long ctr = *ov_counter(P, WIDE, shard);
@@ -944,16 +1037,15 @@ __device__ inline void scan_chunks(const ScanArgs& P, int shard, int64_t c0, int
   const uint32_t first_own = __shfl((uint32_t)first, own, 64);
   wave_sync_lds();  // the marks are used again below
   const bool has = lane < k && c0 + lane < total;
-  Poly q;  // read only under lanes that own rows
-  int cnt = 0, r0 = 0;
+  Poly q;  // read only under lanes that own rows, like r
   Rows r;
-  if (has && build_poly<KIND>(P, P.ov_items[ov_slot(P, WIDE, shard, lo + own)], q) > 0) {
+  int cnt = 0, r0 = 0;
+  if (has && build_poly<KIND, WIDE, ONE>(P, P.ov_items[ov_slot(P, WIDE, shard, lo + own)], q, r) > 0) {
     r0 = (int)((uint32_t)(c0 + lane) - first_own) * OV_CHUNK;
     cnt = q.nu * q.nv - r0;
     cnt = cnt < OV_CHUNK ? (cnt > 0 ? cnt : 0) : OV_CHUNK;
-    setup_rows<KIND, WIDE>(q, P.md[q.mesh], r);
   }
-  scan_rows_lanes<KIND, WIDE, LOG>(P, q, r, cnt, r0, S.slot, S.mark, S.q, issued);
+  scan_rows_lanes<KIND, WIDE, ONE, LOG>(P, q, r, cnt, r0, S.slot, S.mark, S.q, issued);
 }
 
 // The overflow lists (bit 2 k + wide of LISTS: kind k, wide or not) in steps of up
@@ -961,7 +1053,7 @@ __device__ inline void scan_chunks(const ScanArgs& P, int shard, int64_t c0, int
 // steps. The chunks per step grow with the lists, from one (few polyhedra, spread
 // over as many waves as there are) to OV_STEP (each lane sets a polyhedron up).
 // Wide lists, whose distances take FP64, come first.
-template <int LISTS, bool LOG>
+template <int LISTS, bool ONE, bool LOG>
 __global__ __launch_bounds__(64 * SCAN_WAVES, 4) void k_scan_over(ScanKinds P) {
   __shared__ ScanLds lds[SCAN_WAVES];
   ScanLds& S = lds[threadIdx.x >> 6];
@@ -978,7 +1070,8 @@ __global__ __launch_bounds__(64 * SCAN_WAVES, 4) void k_scan_over(ScanKinds P) {
     all += __builtin_amdgcn_readlane(wave_prefix_sum((int)(c < (1u << 24) ? c : 1u << 24)), 63);
   }
   if (all == 0) return;
-  const int64_t want = (all + nw - 1) / nw;
+  // (steps in whole rounds of the grid's waves)
+  const int64_t rounds = (all + nw * OV_STEP - 1) / (nw * OV_STEP), want = (all + nw * rounds - 1) / (nw * rounds);
   // a logged run takes one chunk per step: the order of the lists varies from run to
   // run, and the number of its rounds must not
   const int k = LOG ? 1 : (int)(want < OV_STEP ? want : OV_STEP);
@@ -1004,12 +1097,12 @@ __global__ __launch_bounds__(64 * SCAN_WAVES, 4) void k_scan_over(ScanKinds P) {
     }
     if (l < 0) break;
     const int64_t c0 = at * k;
-    if ((LISTS & 1) && l == 0) scan_chunks<KIND_FACE, false, LOG>(P.k[0], shard, c0, k, S, issued);
-    if ((LISTS & 2) && l == 1) scan_chunks<KIND_FACE, true, LOG>(P.k[0], shard, c0, k, S, issued);
-    if ((LISTS & 4) && l == 2) scan_chunks<KIND_EDGE, false, LOG>(P.k[1], shard, c0, k, S, issued);
-    if ((LISTS & 8) && l == 3) scan_chunks<KIND_EDGE, true, LOG>(P.k[1], shard, c0, k, S, issued);
-    if ((LISTS & 16) && l == 4) scan_chunks<KIND_VERT, false, LOG>(P.k[2], shard, c0, k, S, issued);
-    if ((LISTS & 32) && l == 5) scan_chunks<KIND_VERT, true, LOG>(P.k[2], shard, c0, k, S, issued);
+    if ((LISTS & 1) && l == 0) scan_chunks<KIND_FACE, false, ONE, LOG>(P.k[0], shard, c0, k, S, issued);
+    if ((LISTS & 2) && l == 1) scan_chunks<KIND_FACE, true, ONE, LOG>(P.k[0], shard, c0, k, S, issued);
+    if ((LISTS & 4) && l == 2) scan_chunks<KIND_EDGE, false, ONE, LOG>(P.k[1], shard, c0, k, S, issued);
+    if ((LISTS & 8) && l == 3) scan_chunks<KIND_EDGE, true, ONE, LOG>(P.k[1], shard, c0, k, S, issued);
+    if ((LISTS & 16) && l == 4) scan_chunks<KIND_VERT, false, ONE, LOG>(P.k[2], shard, c0, k, S, issued);
+    if ((LISTS & 32) && l == 5) scan_chunks<KIND_VERT, true, ONE, LOG>(P.k[2], shard, c0, k, S, issued);
     if (P.k[l >> 1].counter) {
       add_issued(P.k[l >> 1], issued, 3);
       issued = 0;
@@ -1334,7 +1427,10 @@ unsigned resident_blocks(K kernel, int threads) {
 // (by their launch bound) get a wave per SCAN_MIN_GROUP items
 template <int KINDS, bool LOG>
 void launch_small(ScanKinds& A, hipStream_t s) {
-  static const unsigned resident = resident_blocks(k_scan_small<KINDS, LOG>, 64 * SCAN_WAVES);
+  // one mesh: its own instance, whose descriptor sits in scalar registers
+  static const unsigned many = resident_blocks(k_scan_small<KINDS, false, LOG>, 64 * SCAN_WAVES),
+                        one = resident_blocks(k_scan_small<KINDS, true, LOG>, 64 * SCAN_WAVES);
+  const unsigned resident = A.single ? one : many;
   A.first[0] = 0;
   for (int k = 0; k < 3; k++) {
     ScanArgs& K = A.k[k];
@@ -1354,15 +1450,18 @@ void launch_small(ScanKinds& A, hipStream_t s) {
     }
     A.first[k + 1] = A.first[k] + g;
   }
-  k_scan_small<KINDS, LOG><<<A.first[3], 64 * SCAN_WAVES, 0, s>>>(A);
+  if (A.single) k_scan_small<KINDS, true, LOG><<<A.first[3], 64 * SCAN_WAVES, 0, s>>>(A);
+  else k_scan_small<KINDS, false, LOG><<<A.first[3], 64 * SCAN_WAVES, 0, s>>>(A);
 }
 
 // the overflow lists on every wavefront the device holds at once (empty lists
 // cost a load and an exit per wavefront)
 template <int LISTS, bool LOG>
 void launch_over(const ScanKinds& A, hipStream_t s) {
-  static const unsigned resident = resident_blocks(k_scan_over<LISTS, LOG>, 64 * SCAN_WAVES);
-  k_scan_over<LISTS, LOG><<<resident, 64 * SCAN_WAVES, 0, s>>>(A);
+  static const unsigned many = resident_blocks(k_scan_over<LISTS, false, LOG>, 64 * SCAN_WAVES),
+                        one = resident_blocks(k_scan_over<LISTS, true, LOG>, 64 * SCAN_WAVES);
+  if (A.single) k_scan_over<LISTS, true, LOG><<<one, 64 * SCAN_WAVES, 0, s>>>(A);
+  else k_scan_over<LISTS, false, LOG><<<many, 64 * SCAN_WAVES, 0, s>>>(A);
 }
 
 // one kind by itself: its three launches timed as stages of their own, or their
@@ -1405,6 +1504,7 @@ void run_scans(const csc_features* f, unsigned long long* keys, int64_t cap, uns
     else k_init_keys<<<1, 1024, 0, s>>>(keys, f->d_stats, 0, ov_ctr, OV_CTRS_ALL);
   }
   ScanKinds K;
+  K.single = f->n_meshes == 1;
   for (int k = 0; k < 3; k++) {
     ScanArgs& A = K.k[k];
     A = scan_args(f, keys, cap);
