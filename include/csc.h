@@ -241,13 +241,13 @@ int csc_scan_convert(const csc_features* f, void* workspace_d, size_t ws_bytes, 
  * equal to +0) become one vertex; vertices are numbered in order of first
  * appearance in the soup (corner order 3f + j), and tris_d[f][j] is the vertex
  * of corner j of triangle f, so triangle order and corner order (orientation)
- * are kept. Equal positions are grouped by sorting on the exact coordinates (not
- * on coarse Morton codes), so no group needs a sequential pass.
+ * are kept. Equal positions meet in a hash table keyed by the exact coordinates
+ * (not by coarse Morton codes), so no group needs a sequential pass.
  *
  * soup_d: float32 [nf][3][3] device. verts_d: float32 [3*nf][3] device (room for
  * every corner being distinct); the first *nv rows are written. tris_d: int32
  * [nf][3] device. nv: host pointer receiving the vertex count. Allocates
- * temporaries (44 bytes per corner plus the radix sort's storage) with
+ * temporaries (14 bytes per corner) with
  * hipMallocAsync on `stream` and synchronises it before returning. Triangles that collapse (two corners at
  * one position) are not removed here; csc_build_features rejects them.
  * Errors: INVALID_ARG (null, nf <= 0, 3*nf >= 2^31, non-finite coordinate),

@@ -102,3 +102,18 @@ def test_welded_soup_field_matches_oracle():
     print(rep, flush=True)
     assert rep["n_oracle"] > 10000
     assert_parity(rep)
+
+
+@pytest.mark.parametrize("nf,values", [(1, 1), (682, 3), (683, 40), (5000, 1), (4099, 400)])
+def test_weld_tile_edges_and_crowded_positions(nf, values):
+    """Soups around the 2048-corner tiles of the numbering passes, with corners that
+    share a position by the thousand (values ** 3 positions, both zeros among the
+    coordinates) or hardly at all: equal to the oracle bit for bit."""
+    rng = np.random.default_rng(nf + values)
+    pool = np.concatenate([np.float32([0.0, -0.0]), rng.normal(size=values).astype(np.float32)])
+    soup = pool[rng.integers(0 if values > 1 else 2, pool.size, size=(nf, 3, 3))]
+    print("[case] weld crowded", nf, values, flush=True)
+    vd, td = device_weld(soup)
+    vo, to = oracle.weld_soup(soup)
+    assert np.array_equal(td, to)
+    assert np.array_equal(vd.view(np.uint32), vo.view(np.uint32))
