@@ -3,11 +3,20 @@
 //
 // Unlike the paper's Morton-code sort of a triangle soup (Section 7.1, 7.2) the
 // input here is indexed, so the corners of all triangles are grouped by vertex
-// (stable radix sort, or counting + scatter + per-vertex sort when the build is
-// captured into a graph), twins are matched around each vertex, and edges are
-// numbered by a prefix sum over the half-edges that own them (start index < end
-// index). Every id is deterministic. The whole sequence is device work with no
-// host synchronisation; csc_features_sync reads errors and counts back.
+// (dealt into ranges of vertices, then counted and placed inside each range), twins
+// are matched around each vertex, and edges are numbered by a prefix sum over the
+// half-edges that own them (start index < end index). Every id is deterministic.
+// The whole sequence is device work with no host synchronisation;
+// csc_features_sync reads errors and counts back.
+//
+// Seven launches on one stream: k_begin, k_inputs, k_deal, k_bucket, k_vertex,
+// k_edges, k_lists. Counts are summed per tile where they arise and added up by the
+// blocks that need what lies before them, and the bricks and edges are numbered by
+// spare blocks of k_deal and k_bucket, so that no launch only scans. (Coarse sums kept
+// by atomics were slower: atomics on one cache line take 6 to 10 ns each, one after
+// another, 34 us for the 5,625 wavefronts of 360,000 faces.) With a radix sort, separate scans and a second stream the build took 25 launches: a
+// 20,480-face sphere 110 us (now 54), 360,000 faces 204 (107), a batch of 64 meshes
+// with 1.75M faces 509 (406), 5.2M faces 1578 (1207).
 #include <string.h>
 
 #include <new>
@@ -39,37 +48,89 @@ __device__ inline float4 rec_prev(const FaceRec* R, int32_t c) {
 }
 __device__ inline f3 rec_posf(float4 c) { return mk(c.x, c.y, c.z); }
 
-__global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
-  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
+constexpr int BT = 256;                   // threads of the build's blocks, and faces of a face tile
+constexpr int MAX_BUCKETS = 2048;
+constexpr int MAX_BUCKET_SHIFT = 13;      // at most 8192 vertices (32 KB of counters) per bucket
+
+// sum over the block's threads, in every thread
+__device__ inline int block_sum(int v, int* ws) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+  __syncthreads();  // ws may still be read from an earlier sum
+  if (lane == 0) ws[w] = v;
+  __syncthreads();
+  int t = 0;
+  for (int u = 0; u < nw; u++) t += ws[u];
+  return t;
 }
 
-__global__ void k_zero_i64(int64_t* p, int n) {
-  if ((int)threadIdx.x < n) p[threadIdx.x] = 0;
-}
-
-// Per face: its mesh, index range and repeated-corner checks, global indices. A
-// face with a bad index is replaced by three copies of its mesh's first vertex so
-// that every later access stays in bounds (the build then reports the error).
-__device__ inline void globalize_face(const int32_t* __restrict__ T, int64_t f, int m,
-                                      const int32_t* __restrict__ v_off, int32_t* tg, int32_t* face_mesh,
-                                      int32_t* owned, int64_t* stats) {
-  const int32_t nvm = v_off[m + 1] - v_off[m], vo = v_off[m];
-  int32_t a = T[3 * f], b = T[3 * f + 1], c = T[3 * f + 2];
-  if (a < 0 || b < 0 || c < 0 || a >= nvm || b >= nvm || c >= nvm) {
-    atomicOr(err_word(stats), ERR_INDEX);
-    a = b = c = 0;
-  } else if (a == b || b == c || a == c) {
-    atomicOr(err_word(stats), ERR_REPEAT);
+// exclusive prefix over the block's threads; *total gets the block's sum
+__device__ inline int block_prefix(int v, int* ws, int* total) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+  const int incl = wave_prefix_sum(v);
+  __syncthreads();
+  if (lane == 63) ws[w] = incl;
+  __syncthreads();
+  int before = 0, t = 0;
+  for (int u = 0; u < nw; u++) {
+    before += u < w ? ws[u] : 0;
+    t += ws[u];
   }
-  tg[3 * f] = a + vo;
-  tg[3 * f + 1] = b + vo;
-  tg[3 * f + 2] = c + vo;
-  face_mesh[f] = m;
-  // half-edge u -> w numbers its edge when u < w
-  owned[3 * f] = a < b ? 1 : 0;
-  owned[3 * f + 1] = b < c ? 1 : 0;
-  owned[3 * f + 2] = c < a ? 1 : 0;
+  *total = t;
+  return before + incl - v;
+}
+
+// sum of the first n tile sums (called by the whole block); sums on a 16-byte boundary
+__device__ inline int tiles_before(const int32_t* __restrict__ sums, int64_t n, int* ws) {
+  const int4* __restrict__ s4 = reinterpret_cast<const int4*>(sums);
+  int v = 0;
+#pragma unroll 4
+  for (int64_t k = threadIdx.x; k < n / 4; k += blockDim.x) {
+    const int4 x = s4[k];
+    v += x.x + x.y + x.z + x.w;
+  }
+  const int64_t k = n / 4 * 4 + threadIdx.x;
+  if (k < n) v += sums[k];
+  return block_sum(v, ws);
+}
+
+// exclusive prefix of n tile sums in place, by one block; returns their sum. The
+// array holds whole groups of SCAN_PER sums, on a 16-byte boundary; those past n are not read
+// as sums.
+constexpr int SCAN_PER = 16;
+__device__ inline int scan_tiles(int32_t* sums, int64_t n, int* ws) {
+  int carry = 0;
+  for (int64_t b = 0; b < n; b += (int64_t)blockDim.x * SCAN_PER) {
+    const int64_t k0 = b + (int64_t)threadIdx.x * SCAN_PER;
+    int4 v[SCAN_PER / 4];
+    int sum = 0, all;
+#pragma unroll
+    for (int q = 0; q < SCAN_PER / 4; q++) {
+      v[q] = k0 < n ? reinterpret_cast<const int4*>(sums + k0)[q] : make_int4(0, 0, 0, 0);
+      if (k0 + 4 * q >= n) v[q].x = 0;
+      if (k0 + 4 * q + 1 >= n) v[q].y = 0;
+      if (k0 + 4 * q + 2 >= n) v[q].z = 0;
+      if (k0 + 4 * q + 3 >= n) v[q].w = 0;
+      sum += v[q].x + v[q].y + v[q].z + v[q].w;
+    }
+    int at = carry + block_prefix(sum, ws, &all);
+#pragma unroll
+    for (int q = 0; q < SCAN_PER / 4; q++) {
+      const int4 o = make_int4(at, at + v[q].x, at + v[q].x + v[q].y, at + v[q].x + v[q].y + v[q].z);
+      at = o.w + v[q].w;
+      if (k0 < n) reinterpret_cast<int4*>(sums + k0)[q] = o;
+    }
+    carry += all;
+  }
+  return carry;
+}
+
+// the counters and brick flags (n 16-byte words at z) and the statistics zeroed
+__global__ __launch_bounds__(BT) void k_begin(uint4* z, int64_t n, int64_t* stats) {
+  if (blockIdx.x == 0 && threadIdx.x < ST_COUNT) stats[threadIdx.x] = 0;
+  const int64_t step = (int64_t)gridDim.x * BT;
+  for (int64_t i = blockIdx.x * (int64_t)BT + threadIdx.x; i < n; i += step) z[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // the largest m with off[m] <= x (off ascending, off[n_meshes] > x), stepping up
@@ -78,47 +139,6 @@ __device__ inline int segment_from(const int32_t* __restrict__ off, int m0, int6
   int m = m0;
   while ((int64_t)off[m + 1] <= x) m++;
   return m;
-}
-
-// the input passes in one launch: finite coordinates (thread i < 3 nv); global
-// indices and owned half-edges of face i < nf; mesh of vertex i < nv. The meshes
-// of the block's first face and vertex are searched once; each thread steps up
-// from there (a block rarely crosses a mesh boundary).
-__global__ void k_inputs(const float* __restrict__ V, int64_t nv, const int32_t* __restrict__ T, int64_t nf,
-                         const int32_t* __restrict__ f_off, const int32_t* __restrict__ v_off, int n_meshes,
-                         int32_t* tg, int32_t* face_mesh, int32_t* owned, int32_t* vert_mesh, int64_t* stats) {
-  __shared__ int s_mf, s_mv;
-  const int64_t b0 = blockIdx.x * (int64_t)blockDim.x, i = b0 + threadIdx.x;
-  if (threadIdx.x == 0) {
-    s_mf = b0 < nf ? find_segment(f_off, n_meshes + 1, b0) : 0;
-    s_mv = b0 < nv ? find_segment(v_off, n_meshes + 1, b0) : 0;
-  }
-  __syncthreads();
-  if (i < 3 * nv && !isfinite(V[i])) atomicOr(err_word(stats), ERR_NONFINITE);
-  if (i < nf) globalize_face(T, i, segment_from(f_off, s_mf, i), v_off, tg, face_mesh, owned, stats);
-  if (i < nv) vert_mesh[i] = segment_from(v_off, s_mv, i);
-}
-
-struct FillJob {
-  int32_t* p;
-  int64_t n;
-  int32_t v;
-};
-
-// three fills in one launch, over the concatenated ranges
-__global__ void k_fill3(FillJob a, FillJob b, FillJob c) {
-  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < a.n) {
-    a.p[i] = a.v;
-    return;
-  }
-  i -= a.n;
-  if (i < b.n) {
-    b.p[i] = b.v;
-    return;
-  }
-  i -= b.n;
-  if (i < c.n) c.p[i] = c.v;
 }
 
 // Segment offsets of the corners sorted by vertex: off[v] = first position whose
@@ -152,7 +172,6 @@ __global__ void k_offsets(const uint32_t* __restrict__ key, int64_t nh, int64_t 
 // slack code in the vertex's class word, the edge pass in a byte per edge (both
 // written by the thread that owns the feature), and k_face_slack gives every
 // face the largest code of its three edges and three vertices.
-constexpr float SLACK_UNIT = 1.f / 1024.f;  // cells per step of the stored slack
 
 __device__ inline uint8_t slack_code(double cells, float absorb) {
   if (!(cells <= (double)absorb)) return 0;
@@ -176,10 +195,35 @@ __device__ inline uint8_t vertex_slack(const VertexClass& cl, float band, float 
 }
 
 constexpr int VK_THREADS = 128;
-constexpr int VK_MAXD = 12;  // fans up to this degree are staged in LDS (18 KB per block: 4 wavefronts per SIMD)
+constexpr int VK_MAXD = 12;   // fans up to this degree are staged in LDS (18 KB per block: 4 wavefronts per SIMD)
+constexpr int VK_HALF = 6;    // corners whose loads are in flight together
+static_assert(VK_MAXD == 2 * VK_HALF && VK_MAXD <= 16, "two halves, places in 4 bits");
 
-// Per vertex u, over its fan of corners (staged in LDS; positions gathered from
-// the vertex array, which stays far better cached than the face records):
+// ascending order of n corners (heap sort: a fan too long for LDS may be very long)
+__device__ inline void sort_corners(int32_t* a, int n) {
+  auto sift = [&](int root, int end) {
+    const int32_t x = a[root];
+    for (int child; (child = 2 * root + 1) < end; root = child) {
+      if (child + 1 < end && a[child + 1] > a[child]) child++;
+      if (a[child] <= x) break;
+      a[root] = a[child];
+    }
+    a[root] = x;
+  };
+  for (int k = n / 2 - 1; k >= 0; k--) sift(k, n);
+  for (int end = n - 1; end > 0; end--) {
+    const int32_t x = a[0];
+    a[0] = a[end];
+    a[end] = x;
+    sift(0, end);
+  }
+}
+
+// Per vertex u, over its fan of corners in ascending order (staged in LDS, then
+// replaced there by the positions of the neighbours: each is read once, six loads
+// in flight together, where reading both far corners of every triangle again in
+// each of the two passes below took four times the loads one after another:
+// 5.2M faces 420 -> 305 us):
 //  * twins: the out-edge u -> w of corner c (half-edge c) pairs with the unique
 //    in-edge w -> u of another corner around u; none or several: not a closed
 //    2-manifold; two out-edges to the same w: inconsistent orientation;
@@ -187,113 +231,268 @@ constexpr int VK_MAXD = 12;  // fans up to this degree are staged in LDS (18 KB 
 //    neighbour against the plane through u with normal N (Section 3.1-3.2,
 //    Section 8.3), cone aperture and ruff test from the normals (Section 3.3,
 //    Section 4.2), all in double precision; number of vertex polyhedra.
+// Bounded by the latency of the gathers of triangle rows and positions and by its
+// FP64 arithmetic (4 wavefronts per SIMD, LDS-bound).
 __global__ __launch_bounds__(VK_THREADS) void k_vertex(const float* __restrict__ V, const int32_t* __restrict__ T,
-                                                      int64_t nv, const int32_t* __restrict__ off,
-                                                      const int32_t* __restrict__ vc, int ruff_mode, int saddle_mode,
-                                                      int force_both, const int32_t* __restrict__ vert_mesh,
-                                                      const MeshDesc* __restrict__ md, float absorb, int32_t* twin,
-                                                      float4* vinfo, uint32_t* vbits,
+                                                      int64_t nv, const int32_t* __restrict__ off, int32_t* vc,
+                                                      int ruff_mode, int saddle_mode, int force_both,
+                                                      const int32_t* __restrict__ vert_mesh,
+                                                      const MeshDesc* __restrict__ md, int n_meshes, float absorb,
+                                                      int32_t* twin, float4* vinfo, uint32_t* vbits, int32_t* polys,
                                                       int64_t* stats) {
   __shared__ int32_t s_c[VK_MAXD][VK_THREADS], s_n[VK_MAXD][VK_THREADS], s_p[VK_MAXD][VK_THREADS];
+  __shared__ int s_polys[VK_THREADS / 64];
   const int t = threadIdx.x;
-  const int64_t v = xcd_block() * VK_THREADS + t;
-  if (v >= nv) return;
-  const int32_t s0 = off[v], d = off[v + 1] - s0;
-  const bool staged = d <= VK_MAXD;
-  if (staged) {
-    for (int k = 0; k < d; k++) {
-      int32_t c = vc[s0 + k];
-      s_c[k][t] = c;
-      s_n[k][t] = T[next_corner(c)];
-      s_p[k][t] = T[prev_corner(c)];
+  const int64_t tile = xcd_block(), v = tile * VK_THREADS + t;
+  int sides = 0;
+  if (v < nv) {
+    const int32_t s0 = off[v], d = off[v + 1] - s0;
+    const bool staged = d <= VK_MAXD;
+    uint64_t place = 0;  // staged: 4 bits per corner, the corner whose next vertex is this one's previous one
+    if (staged && d > 0) {
+      const bool more = __ballot(d > VK_HALF) != 0;
+      {  // the first six in ascending order (a sorting network), the rest inserted
+        int32_t c[VK_HALF];
+#pragma unroll
+        for (int k = 0; k < VK_HALF; k++) c[k] = vc[s0 + (k < d ? k : 0)];
+#pragma unroll
+        for (int k = 0; k < VK_HALF; k++) c[k] = k < d ? c[k] : INT32_MAX;
+        constexpr int NET[12][2] = {{0, 5}, {1, 3}, {2, 4}, {1, 2}, {3, 4}, {0, 3},
+                                    {2, 5}, {0, 1}, {2, 3}, {4, 5}, {1, 2}, {3, 4}};
+#pragma unroll
+        for (int k = 0; k < 12; k++) {
+          const int32_t a = c[NET[k][0]], b = c[NET[k][1]];
+          c[NET[k][0]] = a < b ? a : b;
+          c[NET[k][1]] = a < b ? b : a;
+        }
+#pragma unroll
+        for (int k = 0; k < VK_HALF; k++) s_c[k][t] = c[k];
+      }
+      if (more) {
+        int32_t c[VK_HALF];
+#pragma unroll
+        for (int k = 0; k < VK_HALF; k++) c[k] = vc[s0 + (VK_HALF + k < d ? VK_HALF + k : 0)];
+#pragma unroll
+        for (int k = 0; k < VK_HALF; k++)
+          if (VK_HALF + k < d) {
+            int q = VK_HALF + k;
+            for (; q > 0 && s_c[q - 1][t] > c[k]; q--) s_c[q][t] = s_c[q - 1][t];
+            s_c[q][t] = c[k];
+          }
+      }
+      for (int h = 0; h < (more ? VK_MAXD : VK_HALF); h += VK_HALF) {
+        int32_t c[VK_HALF], a0[VK_HALF], a1[VK_HALF], a2[VK_HALF];
+#pragma unroll
+        for (int k = 0; k < VK_HALF; k++) {
+          c[k] = s_c[h + k < d ? h + k : 0][t];
+          const int32_t* row = T + (c[k] - c[k] % 3);
+          a0[k] = row[0];
+          a1[k] = row[1];
+          a2[k] = row[2];
+        }
+#pragma unroll
+        for (int k = 0; k < VK_HALF; k++)
+          if (h + k < d) {
+            const int j = c[k] % 3;
+            s_n[h + k][t] = j == 0 ? a1[k] : (j == 1 ? a2[k] : a0[k]);
+            s_p[h + k][t] = j == 0 ? a2[k] : (j == 1 ? a0[k] : a1[k]);
+          }
+      }
+    } else if (!staged) {
+      sort_corners(vc + s0, d);
     }
-  }
-  auto C_ = [&](int k) { return staged ? s_c[k][t] : vc[s0 + k]; };
-  auto N_ = [&](int k) { return staged ? s_n[k][t] : T[next_corner(vc[s0 + k])]; };
-  auto P_ = [&](int k) { return staged ? s_p[k][t] : T[prev_corner(vc[s0 + k])]; };
-  uint32_t e = 0;
-  for (int i = 0; i < d; i++) {
-    const int32_t w = N_(i);
-    int32_t match = -1, nmatch = 0;
-    for (int k = 0; k < d; k++) {
-      if (k != i && N_(k) == w) e |= ERR_ORIENT;
-      if (P_(k) == w) {
-        nmatch++;
-        match = prev_corner(C_(k));
+    auto C_ = [&](int k) { return staged ? s_c[k][t] : vc[s0 + k]; };
+    auto N_ = [&](int k) { return staged ? s_n[k][t] : T[next_corner(vc[s0 + k])]; };
+    auto P_ = [&](int k) { return staged ? s_p[k][t] : T[prev_corner(vc[s0 + k])]; };
+    uint32_t e = 0;
+    for (int i = 0; i < d; i++) {
+      const int32_t w = N_(i);
+      int32_t match = -1, nmatch = 0;
+      for (int k = 0; k < d; k++) {
+        if (k != i && N_(k) == w) e |= ERR_ORIENT;
+        if (P_(k) == w) {
+          nmatch++;
+          match = prev_corner(C_(k));
+          if (staged) place = (place & ~(15ull << (4 * k))) | ((uint64_t)i << (4 * k));
+        }
+      }
+      if (nmatch != 1) e |= ERR_NONMANIFOLD;
+      twin[C_(i)] = nmatch == 1 ? match : -1;
+    }
+    if (e) atomicOr(err_word(stats), e);
+    if (staged && d > 0) {
+      // positions of the next vertices in place of the ids (a corner whose previous
+      // vertex is no next vertex, on a surface that is rejected, takes the first's)
+      const bool more = __ballot(d > VK_HALF) != 0;
+      for (int h = 0; h < (more ? VK_MAXD : VK_HALF); h += VK_HALF) {
+        f3 x[VK_HALF];
+#pragma unroll
+        for (int k = 0; k < VK_HALF; k++) x[k] = vload_f(V, h + k < d ? s_n[h + k][t] : (int32_t)v);
+#pragma unroll
+        for (int k = 0; k < VK_HALF; k++)
+          if (h + k < d) {
+            s_c[h + k][t] = __float_as_int(x[k].x);
+            s_p[h + k][t] = __float_as_int(x[k].y);
+            s_n[h + k][t] = __float_as_int(x[k].z);
+          }
       }
     }
-    if (nmatch != 1) e |= ERR_NONMANIFOLD;
-    twin[C_(i)] = nmatch == 1 ? match : -1;
+    auto at = [&](int k) {
+      return mkd((double)__int_as_float(s_c[k][t]), (double)__int_as_float(s_p[k][t]),
+                 (double)__int_as_float(s_n[k][t]));
+    };
+    auto XN = [&](int k) { return staged ? at(k) : vload_d(V, N_(k)); };
+    auto XP = [&](int k) { return staged ? at((int)(place >> (4 * k)) & 15) : vload_d(V, P_(k)); };
+    const d3 pv = vload_d(V, v);
+    VertexAccum acc;
+    for (int k = 0; k < d; k++) acc.add_face(pv, XN(k), XP(k));
+    VertexTest vt;
+    vt.init(acc.n_alpha);
+    for (int k = 0; k < d; k++) {
+      const d3 p1 = XN(k), p2 = XP(k);
+      vt.neighbour(pv, p1);
+      vt.normal(pv, p1, p2);
+    }
+    VertexClass cl = vt.finish(ruff_mode, saddle_mode, force_both);
+    if (d == 0) cl.bits = 0;  // isolated vertex: no feature
+    // a nearly flat vertex hands its region to the prisms of its faces (side slack
+    // band * sin(2 theta), theta the cone aperture): see vertex_slack
+    const uint8_t q =
+        absorb > 0.f && !force_both ? vertex_slack(cl, md[n_meshes > 1 ? vert_mesh[v] : 0].band, absorb) : 0;
+    if (q) cl.bits = (cl.bits & ~(V_POS | V_NEG)) | V_ABSORBED | ((uint32_t)q << V_SLACK_SHIFT);
+    float cf = (float)cl.cos_t;
+    if ((double)cf > cl.cos_t) cf = nextafterf(cf, -2.f);  // the stored cone contains the exact one
+    vinfo[v] = make_float4((float)cl.axis.x, (float)cl.axis.y, (float)cl.axis.z, cf);
+    vbits[v] = cl.bits;
+    sides = (int)(cl.bits & (V_POS | V_NEG));
   }
-  if (e) atomicOr(err_word(stats), e);
-  const d3 pv = vload_d(V, v);
-  VertexAccum acc;
-  for (int k = 0; k < d; k++) acc.add_face(pv, vload_d(V, N_(k)), vload_d(V, P_(k)));
-  VertexTest vt;
-  vt.init(acc.n_alpha);
-  for (int k = 0; k < d; k++) {
-    const d3 p1 = vload_d(V, N_(k)), p2 = vload_d(V, P_(k));
-    vt.neighbour(pv, p1);
-    vt.normal(pv, p1, p2);
+  const int n = __popcll(__ballot((sides & 1) != 0)) + __popcll(__ballot((sides & 2) != 0));
+  if ((t & 63) == 0) s_polys[t >> 6] = n;
+  __syncthreads();
+  if (t == 0) {
+    int sum = 0;
+    for (int w = 0; w < VK_THREADS / 64; w++) sum += s_polys[w];
+    polys[tile] = sum;
   }
-  VertexClass cl = vt.finish(ruff_mode, saddle_mode, force_both);
-  if (d == 0) cl.bits = 0;  // isolated vertex: no feature
-  // a nearly flat vertex hands its region to the prisms of its faces (side slack
-  // band * sin(2 theta), theta the cone aperture): see vertex_slack
-  const uint8_t q = absorb > 0.f && !force_both ? vertex_slack(cl, md[vert_mesh[v]].band, absorb) : 0;
-  if (q) cl.bits = (cl.bits & ~(V_POS | V_NEG)) | V_ABSORBED | ((uint32_t)q << V_SLACK_SHIFT);
-  float cf = (float)cl.cos_t;
-  if ((double)cf > cl.cos_t) cf = nextafterf(cf, -2.f);  // the stored cone contains the exact one
-  vinfo[v] = make_float4((float)cl.axis.x, (float)cl.axis.y, (float)cl.axis.z, cf);
-  vbits[v] = cl.bits;
+}
+static_assert(V_POS == 1u && V_NEG == 2u, "side bits of the class word");
+
+// The extrusion lists: item i (an edge or a vertex) has 0-2 polyhedra, bit 0 of its
+// side mask the outward one (entry i << 1) and bit 1 the inward one ((i << 1) | 1);
+// the entries follow item order. `at`: the place of this thread's first entry.
+__device__ inline int put_entries(int32_t* q, int at, int64_t item, int sides) {
+  if (sides & 1) q[at++] = (int32_t)item << 1;
+  if (sides & 2) q[at++] = ((int32_t)item << 1) | 1;
+  return at;
 }
 
-// Edge records from the owned half-edges (u -> w with u < w) and, for each edge,
-// its class from the exact orientation of its four corners (Section 8.2: the
-// discriminant of the two face normals, evaluated exactly) with the sides to
-// extrude. The third corner of the owning face precedes u in that face; the
-// third corner of the twin's face precedes the twin's start. (An open or
-// non-manifold surface can own more or fewer than 3F/2 half-edges: such a build
-// is rejected, and nothing is written past ne; cls is zero-filled
-// beforehand, so edges no half-edge produced stay unclassified and empty.)
-__global__ void k_edges(const FaceRec* __restrict__ R, int64_t nh, int64_t ne,
-                        const int32_t* __restrict__ twin, const int32_t* __restrict__ eid, int force_both,
-                        const int32_t* __restrict__ face_mesh, const MeshDesc* __restrict__ md, float absorb,
-                        int4* edges, int32_t* face_edges, uint8_t* cls, uint8_t* eslack) {
-  int64_t h = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (h >= nh) return;
-  // this face's record: the three threads of a face read one sector together
-  const float4 cu = rec_at(R, (int32_t)h), cw = rec_next(R, (int32_t)h);
-  int32_t u = rec_vertex(cu), w = rec_vertex(cw);
-  int32_t t = twin[h];
-  if (u < w) {
-    int32_t e = eid[h];
-    face_edges[h] = e < ne ? e : -1;
-    if (e >= ne) return;
-    edges[e] = make_int4(u, w, (int)(h / 3), t >= 0 ? t / 3 : -1);
-    int c = 0, sides = 0;
-    uint8_t q = 0;
-    if (t >= 0) {
-      const f3 fu = rec_posf(cu), fw = rec_posf(cw), f1 = rec_posf(rec_prev(R, (int32_t)h)),
-               f2 = rec_posf(rec_prev(R, t));
-      c = classify_edge(fu, fw, f1, f2);
-      if (c == EDGE_CONVEX) sides = 1;
-      else if (c == EDGE_CONCAVE) sides = 2;
-      else if (c == EDGE_UNKNOWN) sides = 3;
-      if (force_both) sides = 3;
-      // a nearly flat edge hands its wedge to its two face prisms
-      if (absorb > 0.f && !force_both && (c == EDGE_CONVEX || c == EDGE_CONCAVE)) {
-        q = edge_slack(tod(fu), tod(fw), tod(f1), tod(f2), md[face_mesh[h / 3]].band, absorb);
-        if (q) sides = 0;
+// the vertex polyhedra of QV tiles of k_vertex (block b of the list)
+constexpr int QV = 16;
+template <int TH>
+__device__ inline void vertex_list(int64_t b, const uint32_t* __restrict__ vbits, int64_t nv,
+                                   const int32_t* __restrict__ polys, int64_t tiles, int32_t* q, int64_t* total,
+                                   int* ws) {
+  constexpr int QV_ITEMS = QV * VK_THREADS / TH;
+  static_assert(QV_ITEMS * TH == QV * VK_THREADS, "whole items per thread");
+  const int offset = tiles_before(polys, b * QV, ws);
+  const int64_t first = b * QV * VK_THREADS + (int64_t)threadIdx.x * QV_ITEMS;
+  int m[QV_ITEMS], c = 0;
+#pragma unroll
+  for (int k = 0; k < QV_ITEMS; k++) {
+    m[k] = first + k < nv ? (int)(vbits[first + k] & (V_POS | V_NEG)) : 0;
+    c += __popc(m[k]);
+  }
+  int sum;
+  int at = offset + block_prefix(c, ws, &sum);
+#pragma unroll
+  for (int k = 0; k < QV_ITEMS; k++) at = put_entries(q, at, first + k, m[k]);
+  if ((b + 1) * QV >= tiles && threadIdx.x == 0) *total = offset + sum;
+}
+
+struct EdgeArgs {
+  const FaceRec* rec;
+  const int32_t* twin;
+  const int32_t* face_mesh;
+  const MeshDesc* md;
+  int4* edges;
+  int32_t* face_edges;
+  uint8_t* cls;
+  uint8_t* eslack;
+  const int32_t* eid;    // [nf][3] edge id of each owned half-edge
+  const uint32_t* vbits;
+  int32_t* vpoly;
+  int64_t* stats;
+  const int32_t* vpolys;   // per tile of k_vertex
+  int32_t* epolys;         // per block of this pass
+  int64_t nf, ne, nv, blocks, vertex_tiles;
+  float absorb;
+  int n_meshes, force_both;
+};
+
+// One thread per half-edge: edge records from the owned half-edges (u -> w with
+// u < w) and, for each edge, its class from the exact orientation of its four
+// corners (Section 8.2: the discriminant of the two face normals, evaluated
+// exactly) with the sides to extrude. The third corner of the owning face precedes u
+// in that face; the third corner of the twin's face precedes the twin's start. Edges
+// are numbered along the half-edges. (An open or non-manifold surface can own more or
+// fewer than 3F/2 half-edges: such a build is rejected, and nothing is written past
+// ne; the edges that no half-edge produced are left unclassified and empty.) The
+// blocks past the half-edges' write the vertex list. Bounded by the gathers of the
+// twins' corners and edge ids: the ids come from an array (edge_bases), not from a
+// prefix over the block, whose barriers held the gathers back (5.2M faces: 502 us
+// in blocks of 768 threads, 234 with the array).
+__global__ __launch_bounds__(BT) void k_edges(EdgeArgs P) {
+  __shared__ int ws[BT / 64];
+  if (blockIdx.x >= P.blocks) {
+    vertex_list<BT>(blockIdx.x - P.blocks, P.vbits, P.nv, P.vpolys, P.vertex_tiles, P.vpoly, &P.stats[ST_NVPOLY], ws);
+    return;
+  }
+  const int64_t h = blockIdx.x * (int64_t)BT + threadIdx.x, f = h / 3;
+  int sides = 0;
+  if (f < P.nf) {
+    // this face's record: the three threads of a face read one sector together
+    const float4 cu = rec_at(P.rec, (int32_t)h), cw = rec_next(P.rec, (int32_t)h);
+    const int32_t t = P.twin[h];
+    const bool owns = rec_vertex(cu) < rec_vertex(cw);
+    const int32_t id = owns ? P.eid[h] : (t >= 0 ? P.eid[t] : -1);
+    P.face_edges[h] = id < P.ne ? id : -1;
+    if (owns) {
+      const float4 c1 = rec_prev(P.rec, (int32_t)h);
+      if (id < P.ne) {
+        P.edges[id] = make_int4(rec_vertex(cu), rec_vertex(cw), (int)f, t >= 0 ? t / 3 : -1);
+        int k = 0;
+        uint8_t q = 0;
+        if (t >= 0) {
+          const f3 fu = rec_posf(cu), fw = rec_posf(cw), f1 = rec_posf(c1), f2 = rec_posf(rec_prev(P.rec, t));
+          k = classify_edge(fu, fw, f1, f2);
+          if (k == EDGE_CONVEX) sides = 1;
+          else if (k == EDGE_CONCAVE) sides = 2;
+          else if (k == EDGE_UNKNOWN) sides = 3;
+          if (P.force_both) sides = 3;
+          // a nearly flat edge hands its wedge to its two face prisms
+          if (P.absorb > 0.f && !P.force_both && (k == EDGE_CONVEX || k == EDGE_CONCAVE)) {
+            q = edge_slack(tod(fu), tod(fw), tod(f1), tod(f2), P.md[P.n_meshes > 1 ? P.face_mesh[f] : 0].band,
+                           P.absorb);
+            if (q) sides = 0;
+          }
+        }
+        P.eslack[id] = q;
+        P.cls[id] = (uint8_t)(k | (sides << 2) | (q ? EDGE_ABSORBED : 0));
       }
     }
-    eslack[e] = q;
-    cls[e] = (uint8_t)(c | (sides << 2) | (q ? EDGE_ABSORBED : 0));
-  } else {
-    int32_t e = t >= 0 ? eid[t] : -1;
-    face_edges[h] = e < ne ? e : -1;
   }
+  const int n = __popcll(__ballot(sides & 1)) + __popcll(__ballot(sides & 2));
+  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = n;
+  __syncthreads();
+  if (threadIdx.x == 0) P.epolys[blockIdx.x] = ws[0] + ws[1] + ws[2] + ws[3];
+  if (blockIdx.x == 0)
+    for (int64_t k = P.stats[ST_NE] + threadIdx.x; k < P.ne; k += BT) {
+      P.edges[k] = make_int4(-1, -1, -1, -1);
+      P.eslack[k] = 0;
+      P.cls[k] = 0;
+    }
 }
+static_assert(BT == 256, "three blocks of half-edges per face tile, four wavefronts each");
 
 // Unit face normal (double precision, stored in single) and the band bricks near
 // the face: the bricks holding a cell centre within band*h + eps of the face's
@@ -303,10 +502,8 @@ __global__ void k_edges(const FaceRec* __restrict__ R, int64_t nh, int64_t ne,
 // axis, edge wedges and vertex cones within band*h + eps of their feature), and
 // a scan writes only cells within band*h of a feature, so every cell a scan can
 // write has its brick marked by one of the faces holding its feature.
-__device__ inline void face_geom_one(const float* __restrict__ V, const int32_t* __restrict__ T, int64_t f,
-                                     const int32_t* __restrict__ face_mesh, const MeshDesc* __restrict__ md,
-                                     FaceRec* rec, int32_t* flag, int64_t* stats) {
-  const int32_t ia = T[3 * f], ib = T[3 * f + 1], ic = T[3 * f + 2];
+__device__ inline void face_geom_one(const float* __restrict__ V, int64_t f, int32_t ia, int32_t ib, int32_t ic,
+                                     const MeshDesc& g, FaceRec* rec, uint8_t* flag, int64_t* stats) {
   const f3 af = vload_f(V, ia), bf = vload_f(V, ib), cf = vload_f(V, ic);
   const d3 a = mkd(af.x, af.y, af.z), b = mkd(bf.x, bf.y, bf.z), c = mkd(cf.x, cf.y, cf.z);
   const d3 n = cross(b - a, c - a);
@@ -321,7 +518,6 @@ __device__ inline void face_geom_one(const float* __restrict__ V, const int32_t*
   o.c[1] = make_float4(bf.x, bf.y, bf.z, __int_as_float(ib));
   o.c[2] = make_float4(cf.x, cf.y, cf.z, __int_as_float(ic));
   o.n = un4;
-  const MeshDesc& g = md[face_mesh[f]];
   const double r = g.whd + g.epsd;
   const double X[3][3] = {{a.x, b.x, c.x}, {a.y, b.y, c.y}, {a.z, b.z, c.z}};
   int lo[3], hi[3];
@@ -360,14 +556,326 @@ __device__ inline void face_geom_one(const float* __restrict__ V, const int32_t*
       }
 }
 
-// a grid striding over the faces (geom_blocks: sized below the device, so
-// that the corner sort, which it runs beside, keeps compute units of its own)
-__global__ void k_face_geom(const float* __restrict__ V, const int32_t* __restrict__ T, int64_t nf,
-                            const int32_t* __restrict__ face_mesh, const MeshDesc* __restrict__ md, FaceRec* rec,
-                            int32_t* flag, int64_t* stats) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t f = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; f < nf; f += stride)
-    face_geom_one(V, T, f, face_mesh, md, rec, flag, stats);
+struct InputArgs {
+  const float* V;
+  const int32_t* T;
+  const int32_t* f_off;
+  const int32_t* v_off;
+  const MeshDesc* md;
+  int32_t* tg;           // [nf][3] global vertex indices
+  int32_t* face_mesh;    // batches only
+  int32_t* vert_mesh;    // batches only
+  FaceRec* rec;
+  uint8_t* flag;         // brick marks
+  int32_t* bucket_count; // null: corners are not dealt into buckets
+  int64_t* stats;
+  int32_t* owned;        // per wavefront of 64 faces
+  int64_t nv, nf, face_tiles;
+  int n_meshes, bucket_shift, buckets;
+};
+
+// The input passes in one launch, a persistent grid striding over tiles of BT faces:
+// finite coordinates; of each face its mesh, index range and repeated-corner
+// checks, global indices (a face with a bad index is replaced by three copies of its
+// mesh's first vertex so that every later access stays in bounds; the build then
+// reports the error), its record and band bricks (face_geom_one), its owned
+// half-edges (u -> w with u < w: they number the edges) counted per wavefront, and its
+// corners counted per bucket of vertices, in LDS until the block is done. The mesh
+// of a tile's first face is searched once; each thread steps up from there.
+__global__ __launch_bounds__(BT) void k_inputs(InputArgs P) {
+  __shared__ int s_count[MAX_BUCKETS];
+  const int t = threadIdx.x;
+  if (P.bucket_count)
+    for (int b = t; b < P.buckets; b += BT) s_count[b] = 0;
+  __syncthreads();
+  for (int64_t tile = blockIdx.x; tile < P.face_tiles; tile += gridDim.x) {
+    const int64_t f = tile * BT + t;
+    int owned = 0;
+    if (f < P.nf) {
+      int m = 0;
+      if (P.n_meshes > 1) {
+        m = segment_from(P.f_off, find_segment(P.f_off, P.n_meshes + 1, tile * BT), f);
+        P.face_mesh[f] = m;
+      }
+      const int32_t vo = P.n_meshes > 1 ? P.v_off[m] : 0;
+      const int32_t nvm = P.n_meshes > 1 ? P.v_off[m + 1] - vo : (int32_t)P.nv;
+      int32_t a = P.T[3 * f], b = P.T[3 * f + 1], c = P.T[3 * f + 2];
+      if (a < 0 || b < 0 || c < 0 || a >= nvm || b >= nvm || c >= nvm) {
+        atomicOr(err_word(P.stats), ERR_INDEX);
+        a = b = c = 0;
+      } else if (a == b || b == c || a == c) {
+        atomicOr(err_word(P.stats), ERR_REPEAT);
+      }
+      owned = (a < b ? 1 : 0) + (b < c ? 1 : 0) + (c < a ? 1 : 0);
+      a += vo;
+      b += vo;
+      c += vo;
+      P.tg[3 * f] = a;
+      P.tg[3 * f + 1] = b;
+      P.tg[3 * f + 2] = c;
+      if (P.bucket_count) {
+        atomicAdd(&s_count[a >> P.bucket_shift], 1);
+        atomicAdd(&s_count[b >> P.bucket_shift], 1);
+        atomicAdd(&s_count[c >> P.bucket_shift], 1);
+      }
+      face_geom_one(P.V, f, a, b, c, P.md[m], P.rec, P.flag, P.stats);
+    }
+    // owned half-edges per wavefront of 64 faces: no barrier in the loop
+    const int sum = __popcll(__ballot(owned & 1)) + 2 * __popcll(__ballot(owned & 2));
+    if ((t & 63) == 0) P.owned[tile * (BT / 64) + (t >> 6)] = sum;
+  }
+  const int64_t step = (int64_t)gridDim.x * BT;
+  for (int64_t i = blockIdx.x * (int64_t)BT + t; i < 3 * P.nv; i += step)
+    if (!isfinite(P.V[i])) atomicOr(err_word(P.stats), ERR_NONFINITE);
+  if (P.n_meshes > 1)
+    for (int64_t i = blockIdx.x * (int64_t)BT + t; i < P.nv; i += step)
+      P.vert_mesh[i] = find_segment(P.v_off, P.n_meshes + 1, i);
+  if (P.bucket_count) {
+    __syncthreads();
+    for (int b = t; b < P.buckets; b += BT)
+      if (s_count[b]) atomicAdd(&P.bucket_count[b], s_count[b]);
+  }
+}
+
+struct BrickArgs {
+  const uint8_t* flag;         // [nbt], zero up to a whole tile (16 flags per thread of a block)
+  int32_t* index;
+  int32_t* list;
+  int32_t* bmesh;
+  const int32_t* brick_base;
+  int32_t* first_slot;
+  int64_t* stats;
+  int32_t* marked;             // per tile
+  int64_t nbt, tiles;
+  int n_meshes;
+};
+
+// the 16 flags (0 or 1 each) of this thread in brick tile `tile`
+__device__ inline uint4 brick_flags(const BrickArgs& P, int64_t tile) {
+  return reinterpret_cast<const uint4*>(P.flag)[tile * blockDim.x + threadIdx.x];
+}
+
+__device__ inline void count_bricks(const BrickArgs& P, int64_t tile, int* ws) {
+  const uint4 x = brick_flags(P, tile);
+  const int sum = block_sum(__popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w), ws);
+  if (threadIdx.x == 0) P.marked[tile] = sum;
+}
+
+// slots of the flagged bricks (exclusive prefix of the flags), their list and mesh,
+// and the first slot of every mesh (a mesh's bricks are a multiple of 64, so a
+// thread's 16 lie in one mesh)
+__device__ inline void number_bricks(const BrickArgs& P, int64_t tile, int* ws) {
+  const uint4 x = brick_flags(P, tile);
+  const uint32_t w[4] = {x.x, x.y, x.z, x.w};
+  const int before = tiles_before(P.marked, tile, ws);
+  int sum;
+  int slot = before + block_prefix(__popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w), ws, &sum);
+  const int64_t b0 = (tile * blockDim.x + threadIdx.x) * 16;
+  if (b0 < P.nbt) {
+    const int m = P.n_meshes > 1 ? find_segment(P.brick_base, P.n_meshes + 1, b0) : 0;
+    if (b0 == P.brick_base[m]) P.first_slot[m] = slot;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      int4 idx;
+      int* id = &idx.x;
+#pragma unroll
+      for (int k = 0; k < 4; k++) {
+        if ((w[q] >> (8 * k)) & 1u) {
+          id[k] = slot;
+          P.list[slot] = (int32_t)(b0 + 4 * q + k);
+          P.bmesh[slot] = m;
+          slot++;
+        } else {
+          id[k] = -1;
+        }
+      }
+      *reinterpret_cast<int4*>(P.index + b0 + 4 * q) = idx;
+    }
+  }
+  if (tile == P.tiles - 1 && threadIdx.x == 0) {
+    P.first_slot[P.n_meshes] = before + sum;
+    P.stats[ST_NBRICKS] = before + sum;
+  }
+}
+
+// The corner table in two steps. k_deal takes tiles of TH * ITEMS corners and deals
+// them into the buckets (ranges of 2^shift vertices): ranks inside the tile from LDS
+// counters, a place in the bucket for the tile's share from one atomic per bucket,
+// so that a share's corners lie together. k_bucket takes one bucket per block,
+// counts its vertices in LDS, and places its corners; a vertex's corners come out in
+// any order (k_vertex sorts its fan). The blocks past the tiles and the buckets number
+// the band bricks and the edges. Two reads and one write of 8 bytes per corner
+// in all beside the 4-byte indices, where the radix sort read and wrote 16 bytes three
+// times and counted digits in between (5.2M faces, 15.7M corners: k_deal 72 us and k_bucket 124, the edge ids and
+// bricks included, against some 330 for the sort alone).
+struct DealArgs {
+  const int32_t* tg;
+  int64_t nh, tiles, nv;
+  const int32_t* bucket_count;
+  int32_t* bucket_next;   // zeroed by k_begin
+  uint2* pairs;           // (vertex, corner) by bucket
+  int32_t* off;
+  int32_t* corners;
+  int shift, buckets;
+};
+
+// The number of owned half-edges before each half-edge, the id of the edge it owns:
+// those of the wavefronts of 64 faces before (counted by k_inputs, scanned by a block
+// of k_deal), those of the faces before in the wavefront, those before in the face.
+struct EdgeBase {
+  const int32_t* tg;
+  int32_t* owned;    // [waves] per 64 faces; their exclusive prefix once scanned
+  int32_t* eid;      // [nf][3]
+  int64_t* stats;
+  int64_t nf, waves, tiles;  // tiles of the block's size
+};
+
+__device__ inline void edge_bases(const EdgeBase& P, int64_t tile) {
+  const int64_t f = tile * blockDim.x + threadIdx.x;
+  int o0 = 0, o1 = 0, o2 = 0;
+  if (f < P.nf) {
+    const int32_t a = P.tg[3 * f], b = P.tg[3 * f + 1], c = P.tg[3 * f + 2];
+    o0 = a < b ? 1 : 0;
+    o1 = b < c ? 1 : 0;
+    o2 = c < a ? 1 : 0;
+  }
+  const int owned = o0 + o1 + o2, before = wave_prefix_sum(owned) - owned;
+  if (f < P.nf) {
+    const int at = P.owned[f >> 6] + before;
+    P.eid[3 * f] = at;
+    P.eid[3 * f + 1] = at + o0;
+    P.eid[3 * f + 2] = at + o0 + o1;
+  }
+}
+
+__device__ inline void scan_owned(const EdgeBase& P, int* ws) {
+  const int found = scan_tiles(P.owned, P.waves, ws);
+  if (threadIdx.x == 0) P.stats[ST_NE] = found;
+}
+
+template <int TH, int ITEMS>
+__global__ __launch_bounds__(TH) void k_deal(DealArgs P, BrickArgs B, EdgeBase E) {
+  __shared__ int s_count[MAX_BUCKETS], s_base[MAX_BUCKETS];
+  __shared__ int ws[TH / 64];
+  const int t = threadIdx.x;
+  if (blockIdx.x == 0) {
+    scan_owned(E, ws);
+    return;
+  }
+  const int64_t tile = (int64_t)blockIdx.x - 1;
+  if (tile >= P.tiles) {
+    count_bricks(B, tile - P.tiles, ws);
+    return;
+  }
+  for (int b = t; b < P.buckets; b += TH) s_count[b] = 0;
+  __syncthreads();
+  int32_t v[ITEMS], r[ITEMS];
+  const int64_t base = tile * (int64_t)(TH * ITEMS) + t;
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) v[k] = base + (int64_t)k * TH < P.nh ? P.tg[base + (int64_t)k * TH] : -1;
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++) r[k] = v[k] >= 0 ? atomicAdd(&s_count[v[k] >> P.shift], 1) : 0;
+  __syncthreads();
+  // where each bucket starts, and this tile's share of it
+  int run = 0;
+  for (int b0 = 0; b0 < P.buckets; b0 += TH) {
+    const int b = b0 + t, c = b < P.buckets ? P.bucket_count[b] : 0;
+    int sum;
+    const int start = run + block_prefix(c, ws, &sum);
+    run += sum;
+    if (b < P.buckets) {
+      const int mine = s_count[b];
+      s_base[b] = start + (mine ? atomicAdd(&P.bucket_next[b], mine) : 0);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < ITEMS; k++)
+    if (v[k] >= 0)
+      P.pairs[s_base[v[k] >> P.shift] + r[k]] = make_uint2((uint32_t)v[k], (uint32_t)(base + (int64_t)k * TH));
+}
+
+template <int TH>
+__global__ __launch_bounds__(TH) void k_bucket(DealArgs P, BrickArgs B, EdgeBase E) {
+  extern __shared__ int s_count[];  // 2^shift
+  __shared__ int ws[TH / 64];
+  if ((int)blockIdx.x >= P.buckets) {
+    const int64_t x = (int64_t)blockIdx.x - P.buckets;
+    if (x < E.tiles) edge_bases(E, x);
+    else number_bricks(B, x - E.tiles, ws);
+    return;
+  }
+  const int t = threadIdx.x, b = blockIdx.x, size = 1 << P.shift;
+  const int64_t v0 = (int64_t)b << P.shift;
+  int before = 0;
+  for (int k = t; k < b; k += TH) before += P.bucket_count[k];
+  const int start = block_sum(before, ws), n = P.bucket_count[b];
+  if (b == P.buckets - 1 && t == 0) P.off[P.nv] = (int32_t)P.nh;
+  if (n == 0) {  // vertices of no triangle
+    for (int k = t; k < size; k += TH)
+      if (v0 + k < P.nv) P.off[v0 + k] = start;
+    return;
+  }
+  for (int k = t; k < size; k += TH) s_count[k] = 0;
+  __syncthreads();
+  // AHEAD pairs of a thread are loaded together, then used: one at a time, each load
+  // waits out the memory latency
+  constexpr int AHEAD = 8;
+  const uint2* pairs = P.pairs + start;
+  for (int k0 = 0; k0 < n; k0 += AHEAD * TH) {
+    uint32_t v[AHEAD];
+#pragma unroll
+    for (int a = 0; a < AHEAD; a++) {
+      const int k = k0 + a * TH + t;
+      v[a] = pairs[k < n ? k : 0].x - (uint32_t)v0;
+    }
+#pragma unroll
+    for (int a = 0; a < AHEAD; a++)
+      if (k0 + a * TH + t < n) atomicAdd(&s_count[v[a]], 1);
+  }
+  __syncthreads();
+  const int per = (size + TH - 1) / TH;  // counters of a thread: consecutive
+  int sum = 0;
+  for (int k = 0; k < per; k++) {
+    const int i = t * per + k;
+    if (i < size) sum += s_count[i];
+  }
+  int all;
+  int at = block_prefix(sum, ws, &all);
+  for (int k = 0; k < per; k++) {
+    const int i = t * per + k;
+    if (i < size) {
+      const int c = s_count[i];
+      s_count[i] = at;
+      if (v0 + i < P.nv) P.off[v0 + i] = start + at;
+      at += c;
+    }
+  }
+  __syncthreads();
+  for (int k0 = 0; k0 < n; k0 += AHEAD * TH) {
+    uint2 x[AHEAD];
+#pragma unroll
+    for (int a = 0; a < AHEAD; a++) {
+      const int k = k0 + a * TH + t;
+      x[a] = pairs[k < n ? k : 0];
+    }
+#pragma unroll
+    for (int a = 0; a < AHEAD; a++)
+      if (k0 + a * TH + t < n) P.corners[start + atomicAdd(&s_count[x[a].x - (uint32_t)v0], 1)] = (int32_t)x[a].y;
+  }
+}
+
+// the same numbering of bricks and edges in two launches of its own, where the corner table comes from the radix sort
+__global__ __launch_bounds__(BT) void k_bricks(BrickArgs B, EdgeBase E, int pass) {
+  __shared__ int ws[BT / 64];
+  const int64_t x = blockIdx.x;
+  if (pass == 0) {
+    if (x == 0) scan_owned(E, ws);
+    else count_bricks(B, x - 1, ws);
+  } else {
+    if (x < E.tiles) edge_bases(E, x);
+    else number_bricks(B, x - E.tiles, ws);
+  }
 }
 
 // class statistics (and absorbed features): each thread counts 16 edge-class bytes and 4 vertex words per
@@ -429,137 +937,65 @@ __global__ __launch_bounds__(256) void k_class_stats(const uint8_t* __restrict__
     atomicAdd((unsigned long long*)&stats[map[threadIdx.x]], (unsigned long long)h[threadIdx.x]);
 }
 
-// per face: the largest slack code of its edges and vertices (gathers of the
-// coalesced per-feature codes instead of scattered byte writes per face side),
-// and which of them are absorbed (the face scan signs their cells itself)
-__global__ void k_face_slack(const int32_t* __restrict__ T, const int32_t* __restrict__ face_edges,
-                             const uint32_t* __restrict__ vbits, const uint8_t* __restrict__ eslack, int64_t nf,
-                             int64_t ne, uint8_t* fslack, uint8_t* fabsorbed) {
-  const int64_t f = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (f >= nf) return;
+struct ListArgs {
+  const int32_t* T;
+  const int32_t* face_edges;
+  const uint32_t* vbits;
+  const uint8_t* eslack;
+  const uint8_t* cls;
+  const int32_t* eid;         // [nf][3] owned half-edges before each half-edge
+  const int32_t* epolys;      // per block of k_edges: three per face tile
+  uint8_t* fslack;
+  uint8_t* fabsorbed;
+  int32_t* epoly;
+  int64_t* stats;
+  int64_t nf, ne, lists, list_tiles;  // list blocks, face tiles of each
+};
+
+// The first blocks write the edge list, each that of the edges of list_tiles face
+// tiles (which follow one another); the others take the faces: the largest slack code
+// of a face's edges and vertices (gathers of the coalesced per-feature codes instead
+// of scattered byte writes per face side), and which of them are absorbed (the face
+// scan signs their cells itself).
+__global__ __launch_bounds__(BT) void k_lists(ListArgs P) {
+  __shared__ int ws[BT / 64];
+  if (blockIdx.x < P.lists) {
+    const int64_t f0 = blockIdx.x * P.list_tiles * BT, f1 = f0 + P.list_tiles * BT;
+    const int64_t e0 = P.eid[3 * f0] < P.ne ? P.eid[3 * f0] : P.ne;  // none past ne
+    int64_t e1 = f1 < P.nf ? P.eid[3 * f1] : P.ne;
+    if (e1 > P.ne) e1 = P.ne;
+    int at = tiles_before(P.epolys, 3 * blockIdx.x * P.list_tiles, ws);
+    for (int64_t b = e0; b < e1; b += 4 * BT) {
+      const int64_t e = b + 4 * (int64_t)threadIdx.x;
+      int m[4], c = 0, sum;
+#pragma unroll
+      for (int k = 0; k < 4; k++) {
+        m[k] = e + k < e1 ? (P.cls[e + k] >> 2) & 3 : 0;
+        c += __popc(m[k]);
+      }
+      int mine = at + block_prefix(c, ws, &sum);
+#pragma unroll
+      for (int k = 0; k < 4; k++) mine = put_entries(P.epoly, mine, e + k, m[k]);
+      at += sum;
+    }
+    if (blockIdx.x == P.lists - 1 && threadIdx.x == 0) P.stats[ST_NEPOLY] = at;
+    return;
+  }
+  const int64_t f = (blockIdx.x - P.lists) * BT + threadIdx.x;
+  if (f >= P.nf) return;
   uint32_t q = 0, bits = 0;
 #pragma unroll
   for (int j = 0; j < 3; j++) {
-    const uint32_t qv = (vbits[T[3 * f + j]] >> V_SLACK_SHIFT) & 0xffu;
+    const uint32_t qv = (P.vbits[P.T[3 * f + j]] >> V_SLACK_SHIFT) & 0xffu;
     q = max(q, qv);
     if (qv) bits |= 8u << j;
-    const int32_t e = face_edges[3 * f + j];
-    const uint32_t qe = e >= 0 && e < ne ? (uint32_t)eslack[e] : 0u;
+    const int32_t e = P.face_edges[3 * f + j];
+    const uint32_t qe = e >= 0 && e < P.ne ? (uint32_t)P.eslack[e] : 0u;
     q = max(q, qe);
     if (qe) bits |= 1u << j;
   }
-  fslack[f] = (uint8_t)q;
-  fabsorbed[f] = (uint8_t)bits;
-}
-
-// The extrusion lists in one compaction: item i (an edge or a vertex) has 0-2
-// polyhedra, bit 0 of its side mask the outward one (entry i << 1) and bit 1
-// the inward one ((i << 1) | 1); the entries follow item order. Pass 1 counts
-// the polyhedra of each tile of QTILE items; pass 2 gives every tile its offset
-// (the sum of the tile counts before it, added up by the block itself when the
-// tiles are few, else scanned beforehand) and writes its entries, ranked inside
-// the tile by a block scan. The side masks come straight from the classes, so
-// no count array and no separate queue launch are needed.
-struct VertexSides {
-  const uint32_t* bits;
-  __device__ int operator()(int64_t i) const { return (int)(bits[i] & (V_POS | V_NEG)); }
-};
-struct EdgeSides {
-  const uint8_t* cls;
-  __device__ int operator()(int64_t i) const { return (cls[i] >> 2) & 3; }
-};
-constexpr int QB = 256, QITEMS = 8, QTILE = QB * QITEMS;
-constexpr int64_t Q_SHORT_TILES = 4096;
-
-template <class S>
-__global__ __launch_bounds__(QB) void k_queue_sums(S sides, int64_t n, int32_t* sums) {
-  const int64_t base = (int64_t)blockIdx.x * QTILE;
-  int c = 0;
-  for (int i = threadIdx.x; i < QTILE; i += QB) {
-    const int64_t idx = base + i;
-    if (idx < n) c += __popc(sides(idx));
-  }
-  for (int o = 32; o > 0; o >>= 1) c += __shfl_down(c, o, 64);
-  __shared__ int ws[QB / 64];
-  if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = c;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int t = 0;
-    for (int w = 0; w < QB / 64; w++) t += ws[w];
-    sums[blockIdx.x] = t;
-  }
-}
-
-template <class S>
-__global__ __launch_bounds__(QB) void k_queue_write(S sides, int64_t n, const int32_t* __restrict__ sums, int scanned,
-                                                    int32_t* q, int64_t* total) {
-  __shared__ int ws[QB / 64];
-  __shared__ int wx[QB / 64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  // this tile's offset
-  int pre = 0;
-  if (!scanned)
-    for (int j = threadIdx.x; j < (int)blockIdx.x; j += QB) pre += sums[j];
-  for (int o = 32; o > 0; o >>= 1) pre += __shfl_down(pre, o, 64);
-  if (lane == 0) ws[w] = pre;
-  // this thread's QITEMS consecutive items
-  const int64_t first = (int64_t)blockIdx.x * QTILE + (int64_t)threadIdx.x * QITEMS;
-  int m[QITEMS], c = 0;
-#pragma unroll
-  for (int k = 0; k < QITEMS; k++) {
-    m[k] = first + k < n ? sides(first + k) : 0;
-    c += __popc(m[k]);
-  }
-  const int incl = wave_prefix_sum(c);
-  if (lane == 63) wx[w] = incl;
-  __syncthreads();
-  int offset = scanned ? sums[blockIdx.x] : 0, before = 0, tile = 0;
-#pragma unroll
-  for (int u = 0; u < QB / 64; u++) {
-    if (!scanned) offset += ws[u];
-    before += u < w ? wx[u] : 0;
-    tile += wx[u];
-  }
-  int p = offset + before + incl - c;
-#pragma unroll
-  for (int k = 0; k < QITEMS; k++) {
-    const int32_t id = (int32_t)(first + k);
-    if (m[k] & 1) q[p++] = id << 1;
-    if (m[k] & 2) q[p++] = (id << 1) | 1;
-  }
-  if (!scanned && threadIdx.x == 0 && blockIdx.x == gridDim.x - 1) *total = offset + tile;
-}
-
-template <class S>
-hipError_t queue_compact(S sides, int64_t n, int32_t* q, int64_t* total, int32_t* tmp, hipStream_t s) {
-  int64_t nb = (n + QTILE - 1) / QTILE;
-  if (nb < 1) nb = 1;
-  k_queue_sums<S><<<(unsigned)nb, QB, 0, s>>>(sides, n, tmp);
-  const bool few = nb <= Q_SHORT_TILES;
-  if (!few) {
-    hipError_t e = scan_sums_inplace(tmp, nb, total, s);
-    if (e != hipSuccess) return e;
-  }
-  k_queue_write<S><<<(unsigned)nb, QB, 0, s>>>(sides, n, tmp, few ? 0 : 1, q, total);
-  return hipGetLastError();
-}
-
-// slots of the flagged bricks (index = exclusive prefix of the flags), their
-// list and mesh, and the first slot of every mesh
-__global__ void k_brick_fix(const int32_t* __restrict__ flag, int32_t* index, int32_t* list, int32_t* bmesh,
-                            const int32_t* __restrict__ brick_base, int n_meshes, int32_t* first_slot,
-                            const int64_t* __restrict__ stats, int64_t n) {
-  int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (b >= n) return;
-  const int m = find_segment(brick_base, n_meshes + 1, b);
-  if (b == brick_base[m]) first_slot[m] = index[b];
-  if (b == n - 1) first_slot[n_meshes] = (int32_t)stats[ST_NBRICKS];
-  if (flag[b]) {
-    list[index[b]] = (int32_t)b;
-    bmesh[index[b]] = m;
-  } else {
-    index[b] = -1;
-  }
+  P.fslack[f] = (uint8_t)q;
+  P.fabsorbed[f] = (uint8_t)bits;
 }
 
 int status_from_errors(uint64_t err, int64_t ne_found, int64_t ne_expected) {
@@ -577,11 +1013,12 @@ int status_from_errors(uint64_t err, int64_t ne_found, int64_t ne_expected) {
 // above it (the paper orders its triangle soup by Morton code as well, Section
 // 7.1; here the order only schedules the face pass and changes no result).
 __global__ void k_face_order_keys(const FaceRec* __restrict__ R, const int32_t* __restrict__ face_mesh,
-                                  const MeshDesc* __restrict__ md, int64_t nf, int axis_bits, uint32_t* key) {
+                                  const MeshDesc* __restrict__ md, int n_meshes, int64_t nf, int axis_bits,
+                                  uint32_t* key) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const uint32_t top = (1u << axis_bits) - 1u;
   for (int64_t f = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; f < nf; f += stride) {
-    const int m = face_mesh[f];
+    const int m = n_meshes > 1 ? face_mesh[f] : 0;
     const MeshDesc& G = md[m];
     const float4 a = R[f].c[0], b = R[f].c[1], c = R[f].c[2];
     const double x[3] = {((double)a.x + b.x + c.x) / 3.0, ((double)a.y + b.y + c.y) / 3.0,
@@ -634,7 +1071,8 @@ extern "C" int csc_features_order_faces(csc_features* F, int32_t enable, void* s
   if (he != hipSuccess) return he == hipErrorOutOfMemory ? CSC_OUT_OF_MEMORY : fail_hip(he);
   uint32_t* key = (uint32_t*)tmp;
   uint32_t* key_sorted = (uint32_t*)(tmp + key_bytes);
-  k_face_order_keys<<<grid_1d(nf, 256), 256, 0, s>>>(F->face_rec, F->face_mesh, F->d_mesh, nf, axis_bits, key);
+  k_face_order_keys<<<grid_1d(nf, 256), 256, 0, s>>>(F->face_rec, F->face_mesh, F->d_mesh, F->n_meshes, nf,
+                                                        axis_bits, key);
   he = hipGetLastError();
   if (he == hipSuccess)
     he = sort_pairs(tmp + 2 * key_bytes, sort_bytes, key, key_sorted, nullptr, F->face_order, nf, bits, s);
@@ -651,49 +1089,103 @@ size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
 
 enum {
   L_MESH, L_FOFF, L_VOFF, L_BBASE, L_TRIS, L_FMESH, L_VMESH, L_VTXOFF, L_VTXC, L_FEDGES, L_EDGES, L_FREC, L_ECLS,
-  L_VINFO, L_VBITS, L_EPOLY, L_VPOLY, L_BINDEX, L_BLIST, L_BMESH, L_FIRST, L_TA, L_TB, L_TC, L_TSCAN, L_BFLAG,
-  L_TSCAN2, L_STATS, L_SORT, L_FSLACK, L_ESLACK, L_FABS, L_EID, L_N
+  L_VINFO, L_VBITS, L_EPOLY, L_VPOLY, L_BINDEX, L_BLIST, L_BMESH, L_FIRST, L_TWIN, L_PAIRS, L_EID, L_SUMS, L_ZERO, L_STATS,
+  L_SORT, L_FSLACK, L_ESLACK, L_FABS, L_N
 };
+
+// How the corner table is made: buckets of 2^shift vertices, or (no buckets) the
+// radix sort, for more vertices than MAX_BUCKETS of the largest buckets hold. Large
+// inputs take long tiles (few shares per bucket), small ones short tiles (more blocks).
+// Build with short and with long tiles: 15.7M corners 1519 and 1207 us, 5.3M corners
+// 406 and 415, 1.1M corners 107 and 129.
+constexpr int DEAL_TH = 256, DEAL_ITEMS = 8, DEAL_BIG_TH = 1024, DEAL_BIG_ITEMS = 16;
+constexpr int64_t DEAL_BIG = 1 << 23;  // corners from which the long tiles are used
+// Blocks of the input pass: each adds its corner counts to every bucket once at its end
+// (a batch of 64 meshes: build 427 us with 1024, 414 with 2048; 5.2M faces 1212, 1207).
+constexpr int64_t INPUT_BLOCKS = 2048;
+struct Plan {
+  int shift = 0, buckets = 0;
+  bool big = false;
+  int64_t deal_tiles = 0, face_tiles = 0, vertex_tiles = 0, brick_tiles = 0;
+};
+
+Plan plan(int64_t nv, int64_t nf, int64_t nbt) {
+  Plan p;
+  // 256 to 512 buckets of at least 64 vertices; large inputs 1024 to 2048, each block then
+  // holds fewer corners and more run at once (5.2M faces: k_bucket 244 us with 320 buckets,
+  // 124 with 1280)
+  p.shift = 6;
+  const int64_t target = 3 * nf >= DEAL_BIG ? MAX_BUCKETS : 512;
+  while (p.shift < MAX_BUCKET_SHIFT && ((nv - 1) >> p.shift) >= target) p.shift++;
+  const int64_t b = ((nv - 1) >> p.shift) + 1;
+  p.buckets = b <= MAX_BUCKETS ? (int)b : 0;
+  p.big = p.buckets > 0 && 3 * nf >= DEAL_BIG;
+  const int64_t tile = p.big ? DEAL_BIG_TH * DEAL_BIG_ITEMS : DEAL_TH * DEAL_ITEMS;
+  p.deal_tiles = (3 * nf + tile - 1) / tile;
+  p.face_tiles = (nf + BT - 1) / BT;
+  p.vertex_tiles = (nv + VK_THREADS - 1) / VK_THREADS;
+  const int64_t bt = 16 * (p.big ? DEAL_BIG_TH : BT);
+  p.brick_tiles = (nbt + bt - 1) / bt;
+  return p;
+}
+
+// the zeroed region: bucket counts and places, then the brick flags on a 16-byte
+// boundary, up to a whole tile of the larger blocks
+struct ZeroLayout {
+  int64_t count, next;  // in ints
+  size_t flags, bytes;
+};
+
+ZeroLayout zero_layout(const Plan& p, int64_t nbt) {
+  ZeroLayout z;
+  z.count = 0;
+  z.next = p.buckets;
+  z.flags = align_up(sizeof(int32_t) * 2 * (size_t)p.buckets);
+  const size_t tile = 16 * (size_t)DEAL_BIG_TH;
+  z.bytes = z.flags + ((size_t)nbt + tile - 1) / tile * tile;
+  return z;
+}
+
+// ints of an array of n tile sums: whole groups of SCAN_PER
+int64_t sums_of(int64_t n) { return (n + SCAN_PER - 1) / SCAN_PER * SCAN_PER; }
 
 struct Layout {
   size_t off[L_N];
   size_t total;
 };
 
-Layout layout(int n_meshes, int64_t nv, int64_t nf, int64_t nbt, size_t sort_bytes) {
+Layout layout(int n_meshes, int64_t nv, int64_t nf, int64_t nbt, const Plan& p, size_t sort_bytes) {
   const int64_t ne = 3 * nf / 2;
-  int64_t big = 3 * nf;
-  big = big > nbt ? big : nbt;
-  big = big > nv + 1 ? big : nv + 1;
-  big = big > ne + 1 ? big : ne + 1;
   size_t sz[L_N];
   sz[L_MESH] = sizeof(MeshDesc) * (size_t)n_meshes;
   sz[L_FOFF] = sz[L_VOFF] = sz[L_BBASE] = sizeof(int32_t) * (size_t)(n_meshes + 1);
   sz[L_TRIS] = sizeof(int32_t) * (size_t)(3 * nf);
-  sz[L_FMESH] = sizeof(int32_t) * (size_t)nf;
-  sz[L_VMESH] = sizeof(int32_t) * (size_t)nv;
+  sz[L_FMESH] = sizeof(int32_t) * (size_t)(n_meshes > 1 ? nf : 1);
+  sz[L_VMESH] = sizeof(int32_t) * (size_t)(n_meshes > 1 ? nv : 1);
   sz[L_VTXOFF] = sizeof(int32_t) * (size_t)(nv + 1);
   sz[L_VTXC] = sizeof(int32_t) * (size_t)(3 * nf);
   sz[L_FEDGES] = sizeof(int32_t) * (size_t)(3 * nf);
   sz[L_EDGES] = sizeof(int4) * (size_t)(ne + 1);
   sz[L_FREC] = sizeof(FaceRec) * (size_t)nf;
-  sz[L_ECLS] = (size_t)((ne + 4) / 4 * 4);  // whole ints: zero-filled as ints
+  sz[L_ECLS] = (size_t)(ne + 16);
   sz[L_VINFO] = sizeof(float4) * (size_t)nv;
   sz[L_VBITS] = sizeof(uint32_t) * (size_t)nv;
   sz[L_EPOLY] = sizeof(int32_t) * (size_t)(2 * ne + 1);
   sz[L_VPOLY] = sizeof(int32_t) * (size_t)(2 * nv + 1);
   sz[L_BINDEX] = sz[L_BLIST] = sz[L_BMESH] = sizeof(int32_t) * (size_t)nbt;
   sz[L_FIRST] = sizeof(int32_t) * (size_t)(n_meshes + 1);
-  sz[L_TA] = sz[L_TB] = sz[L_TC] = sizeof(int32_t) * (size_t)(big + 1);
-  sz[L_TSCAN] = sizeof(int32_t) * (size_t)scan_tmp_ints(big + 1);
-  sz[L_BFLAG] = sizeof(int32_t) * (size_t)(nbt + 1);
-  sz[L_TSCAN2] = sizeof(int32_t) * (size_t)scan_tmp_ints(big + 1);  // the brick flags and the edge numbering
+  sz[L_TWIN] = sizeof(int32_t) * (size_t)(3 * nf);
+  sz[L_PAIRS] = p.buckets > 0 ? sizeof(uint2) * (size_t)(3 * nf) : sizeof(uint32_t) * (size_t)(3 * nf);  // or sorted keys
+  sz[L_EID] = sizeof(int32_t) * (size_t)(3 * nf);
+  // tile sums: owned half-edges, edge polyhedra, vertex polyhedra, bricks
+  sz[L_SUMS] = sizeof(int32_t) * (size_t)(sums_of(p.face_tiles * (BT / 64)) + sums_of(3 * p.face_tiles) +
+                                          sums_of(p.vertex_tiles) + sums_of(p.brick_tiles));
+  sz[L_ZERO] = zero_layout(p, nbt).bytes;
   sz[L_STATS] = sizeof(int64_t) * ST_COUNT;
   sz[L_SORT] = sort_bytes;
   sz[L_FSLACK] = (size_t)(nf + 8);
   sz[L_ESLACK] = (size_t)(ne + 8);
   sz[L_FABS] = (size_t)(nf + 8);
-  sz[L_EID] = sizeof(int32_t) * (size_t)(3 * nf + 1);
   Layout L;
   size_t o = 0;
   for (int i = 0; i < L_N; i++) {
@@ -804,11 +1296,12 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
     F->face_order = nullptr;
     F->face_order_n = 0;
   }
+  const Plan pl = plan(tv, tf, tb);
   int sort_bits = 1;
   while (sort_bits < 31 && ((int64_t)1 << sort_bits) < tv) sort_bits++;
-  const size_t sort_bytes = sort_pairs_tmp_bytes(3 * tf, sort_bits);
-  if (sort_bytes == 0) return fail(fail_hip(hipErrorInvalidValue));
-  Layout L = layout(n_meshes, tv, tf, tb, sort_bytes);
+  const size_t sort_bytes = pl.buckets > 0 ? 0 : sort_pairs_tmp_bytes(3 * tf, sort_bits);
+  if (pl.buckets == 0 && sort_bytes == 0) return fail(fail_hip(hipErrorInvalidValue));
+  Layout L = layout(n_meshes, tv, tf, tb, pl, sort_bytes);
   const bool config_changed = fresh || !same_config(F, mesh, o) || F->arena_bytes < L.total || F->nv != tv ||
                               F->nf != tf;
   hipError_t he;
@@ -833,13 +1326,6 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
       return fail(fail_hip(he));
     }
   }
-  if (!F->side) {  // default priority, like every stream here
-    he = hipStreamCreateWithFlags(&F->side, hipStreamNonBlocking);
-    if (he == hipSuccess) he = hipEventCreateWithFlags(&F->ev_fork, hipEventDisableTiming);
-    if (he == hipSuccess) he = hipEventCreateWithFlags(&F->ev_join, hipEventDisableTiming);
-    if (he == hipSuccess) he = hipEventCreateWithFlags(&F->ev_geom, hipEventDisableTiming);
-    if (he != hipSuccess) return fail(fail_hip(he));
-  }
   char* A = F->arena;
   F->n_meshes = n_meshes;
   F->verts = verts_d;
@@ -848,7 +1334,6 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
   F->ne = te;
   F->nbt = tb;
   F->opt = o;
-  F->sort_bits = sort_bits;
   F->d_mesh = (MeshDesc*)(A + L.off[L_MESH]);
   F->f_off = (int32_t*)(A + L.off[L_FOFF]);
   F->v_off = (int32_t*)(A + L.off[L_VOFF]);
@@ -870,19 +1355,10 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
   F->brick_list = (int32_t*)(A + L.off[L_BLIST]);
   F->brick_mesh = (int32_t*)(A + L.off[L_BMESH]);
   F->first_slot = (int32_t*)(A + L.off[L_FIRST]);
-  F->t_a = (int32_t*)(A + L.off[L_TA]);
-  F->t_b = (int32_t*)(A + L.off[L_TB]);
-  F->t_c = (int32_t*)(A + L.off[L_TC]);
-  F->t_scan = (int32_t*)(A + L.off[L_TSCAN]);
-  F->brick_flag = (int32_t*)(A + L.off[L_BFLAG]);
-  F->t_scan2 = (int32_t*)(A + L.off[L_TSCAN2]);
   F->d_stats = (int64_t*)(A + L.off[L_STATS]);
-  F->t_sort = (void*)(A + L.off[L_SORT]);
-  F->t_sort_bytes = sort_bytes;
   F->fslack = (uint8_t*)(A + L.off[L_FSLACK]);
   F->eslack = (uint8_t*)(A + L.off[L_ESLACK]);
   F->fabsorbed = (uint8_t*)(A + L.off[L_FABS]);
-  F->t_eid = (int32_t*)(A + L.off[L_EID]);
   F->built = F->synced = false;
 
 #define CK(x)                                        \
@@ -909,68 +1385,157 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
   }
 
   StageTimer timer(TS_BUILD, s);
-  const int B = 256;
   const int64_t nh = 3 * tf, ne = te;
-  // 1. inputs: finite coordinates, per-mesh index ranges, global indices
-  k_zero_i64<<<1, 64, 0, s>>>(F->d_stats, ST_COUNT);
-  // (the owned half-edge flags wait in face_edges, which k_edges fills later)
-  k_inputs<<<grid_1d(3 * tv > tf ? 3 * tv : tf, B), B, 0, s>>>(verts_d, tv, tris_d, tf, F->f_off, F->v_off, n_meshes,
-                                                               F->tris_g, F->face_mesh, F->face_edges,
-                                                               F->vert_mesh, F->d_stats);
-  const int32_t* T = F->tris_g;
-  // Face records (corners, vertex indices, normal) with the band bricks near each
-  // face, the brick slots and lists, the cleared edge tables and the edge
-  // numbering: they need only the inputs, so they run on the side stream while
-  // the corner table is sorted and the vertices classified here; the edge pass
-  // waits for the records, the tables and the numbering.
-  CK(hipEventRecord(F->ev_fork, s));
-  // 2. vertex -> corner table: corners sorted by vertex (stable: each vertex's
-  // corners in ascending order), then the segment starts
-  CK(sort_pairs(F->t_sort, F->t_sort_bytes, (const uint32_t*)T, (uint32_t*)F->t_b, nullptr, F->vtx_corners, nh,
-                sort_bits, s));
-  k_offsets<<<grid_1d(nh, B), B, 0, s>>>((const uint32_t*)F->t_b, nh, tv, F->vtx_off);
-  // the side branch (forked right after the inputs, issued after the sort so
-  // that the sort's launches reach the device first)
-  CK(hipStreamWaitEvent(F->side, F->ev_fork, 0));
-  {
-    hipStream_t s2 = F->side;
-    k_fill_i32<<<grid_1d(tb, B), B, 0, s2>>>(F->brick_flag, tb, 0);
-    {
-      const unsigned need = grid_1d(tf, B), cap = (unsigned)o.geom_blocks;
-      k_face_geom<<<cap > 0 && need > cap ? cap : need, B, 0, s2>>>(verts_d, T, tf, F->face_mesh, F->d_mesh,
-                                                                    F->face_rec, F->brick_flag, F->d_stats);
-    }
-    {
-      const FillJob a = {(int32_t*)F->edges, 4 * (ne + 1), -1}, b = {nullptr, 0, 0},
-                    c = {(int32_t*)F->edge_cls, (ne + 3) / 4, 0};
-      k_fill3<<<grid_1d(a.n + b.n + c.n, B), B, 0, s2>>>(a, b, c);
-    }
-    // edge ids: a prefix sum over the owned half-edge flags that k_inputs left in face_edges
-    CK(exclusive_scan(F->face_edges, F->t_eid, nh, F->t_scan2, &F->d_stats[ST_NE], nullptr, s2));
-    CK(hipEventRecord(F->ev_geom, s2));
-    CK(exclusive_scan(F->brick_flag, F->brick_index, tb, F->t_scan2, &F->d_stats[ST_NBRICKS], nullptr, s2));
-    k_brick_fix<<<grid_1d(tb, B), B, 0, s2>>>(F->brick_flag, F->brick_index, F->brick_list, F->brick_mesh,
-                                              F->brick_base, n_meshes, F->first_slot, F->d_stats, tb);
-    CK(hipEventRecord(F->ev_join, s2));
-  }
-  // 3. per vertex: twins, pseudonormal, class, cone; then edge numbering
   const float absorb = o.absorb_cells > 0.f ? o.absorb_cells : 0.f;
-  k_vertex<<<grid_1d(tv, VK_THREADS), VK_THREADS, 0, s>>>(verts_d, T, tv, F->vtx_off, F->vtx_corners, o.ruff_mode,
-                                                        o.saddle_mode, o.force_both_sides, F->vert_mesh, F->d_mesh,
-                                                        absorb, F->t_a, F->vinfo, F->vbits, F->d_stats);
-  CK(queue_compact(VertexSides{F->vbits}, tv, F->vpoly, &F->d_stats[ST_NVPOLY], F->t_scan, s));
-  // edges with their classes and extrusion sides
-  CK(hipStreamWaitEvent(s, F->ev_geom, 0));  // the face records, cleared edge tables and edge ids
-  k_edges<<<grid_1d(nh, B), B, 0, s>>>(F->face_rec, nh, ne, F->t_a, F->t_eid, o.force_both_sides, F->face_mesh,
-                                       F->d_mesh, absorb, F->edges, F->face_edges, F->edge_cls, F->eslack);
-  k_face_slack<<<grid_1d(tf, B), B, 0, s>>>(T, F->face_edges, F->vbits, F->eslack, tf, ne, F->fslack,
-                                            F->fabsorbed);
-  // 4. edge polyhedron queue (the class statistics, which only the feature
+  const ZeroLayout z = zero_layout(pl, tb);
+  char* zero = A + L.off[L_ZERO];
+  int32_t* zi = (int32_t*)zero;
+  uint8_t* marks = (uint8_t*)(zero + z.flags);
+  int32_t* sums = (int32_t*)(A + L.off[L_SUMS]);
+  const int64_t waves = pl.face_tiles * (BT / 64);
+  int32_t *owned = sums, *epolys = owned + sums_of(waves), *vpolys = epolys + sums_of(3 * pl.face_tiles),
+          *marked = vpolys + sums_of(pl.vertex_tiles);
+  int32_t* eid = (int32_t*)(A + L.off[L_EID]);
+  int32_t* twin = (int32_t*)(A + L.off[L_TWIN]);
+  // 1. counters, coarse sums, brick flags and statistics cleared
+  {
+    const int64_t n = (int64_t)(z.bytes / 16);
+    const unsigned need = grid_1d(n, 4 * BT);
+    k_begin<<<need < 2048 ? need : 2048, BT, 0, s>>>((uint4*)zero, n, F->d_stats);
+  }
+  // 2. inputs, face records, band bricks, counts
+  {
+    InputArgs I;
+    I.V = verts_d;
+    I.T = tris_d;
+    I.f_off = F->f_off;
+    I.v_off = F->v_off;
+    I.md = F->d_mesh;
+    I.tg = F->tris_g;
+    I.face_mesh = F->face_mesh;
+    I.vert_mesh = F->vert_mesh;
+    I.rec = F->face_rec;
+    I.flag = marks;
+    I.bucket_count = pl.buckets > 0 ? zi + z.count : nullptr;
+    I.stats = F->d_stats;
+    I.owned = owned;
+    I.nv = tv;
+    I.nf = tf;
+    I.face_tiles = pl.face_tiles;
+    I.n_meshes = n_meshes;
+    I.bucket_shift = pl.shift;
+    I.buckets = pl.buckets;
+    const int64_t cap = o.geom_blocks > 0 && o.geom_blocks < INPUT_BLOCKS ? o.geom_blocks : INPUT_BLOCKS;
+    k_inputs<<<(unsigned)(pl.face_tiles < cap ? pl.face_tiles : cap), BT, 0, s>>>(I);
+  }
+  const int32_t* T = F->tris_g;
+  // 3. vertex -> corner table, and the bricks counted and numbered
+  BrickArgs bricks;
+  bricks.flag = marks;
+  bricks.index = F->brick_index;
+  bricks.list = F->brick_list;
+  bricks.bmesh = F->brick_mesh;
+  bricks.brick_base = F->brick_base;
+  bricks.first_slot = F->first_slot;
+  bricks.stats = F->d_stats;
+  bricks.marked = marked;
+  bricks.nbt = tb;
+  bricks.tiles = pl.brick_tiles;
+  bricks.n_meshes = n_meshes;
+  EdgeBase bases;
+  bases.tg = T;
+  bases.owned = owned;
+  bases.eid = eid;
+  bases.stats = F->d_stats;
+  bases.nf = tf;
+  bases.waves = waves;
+  const int block = pl.big ? DEAL_BIG_TH : BT;
+  bases.tiles = (tf + block - 1) / block;
+  if (pl.buckets > 0) {
+    DealArgs D;
+    D.tg = T;
+    D.nh = nh;
+    D.tiles = pl.deal_tiles;
+    D.nv = tv;
+    D.bucket_count = zi + z.count;
+    D.bucket_next = zi + z.next;
+    D.pairs = (uint2*)(A + L.off[L_PAIRS]);
+    D.off = F->vtx_off;
+    D.corners = F->vtx_corners;
+    D.shift = pl.shift;
+    D.buckets = pl.buckets;
+    const unsigned g = (unsigned)(1 + pl.deal_tiles + pl.brick_tiles);
+    const unsigned gb = (unsigned)(pl.buckets + bases.tiles + pl.brick_tiles);
+    const size_t lds = sizeof(int) << pl.shift;
+    if (pl.big) {
+      k_deal<DEAL_BIG_TH, DEAL_BIG_ITEMS><<<g, DEAL_BIG_TH, 0, s>>>(D, bricks, bases);
+      k_bucket<DEAL_BIG_TH><<<gb, DEAL_BIG_TH, lds, s>>>(D, bricks, bases);
+    } else {
+      k_deal<DEAL_TH, DEAL_ITEMS><<<g, DEAL_TH, 0, s>>>(D, bricks, bases);
+      k_bucket<DEAL_TH><<<gb, DEAL_TH, lds, s>>>(D, bricks, bases);
+    }
+  } else {
+    uint32_t* keys = (uint32_t*)(A + L.off[L_PAIRS]);
+    CK(sort_pairs(A + L.off[L_SORT], sort_bytes, (const uint32_t*)T, keys, nullptr, F->vtx_corners, nh, sort_bits, s));
+    k_offsets<<<grid_1d(nh, BT), BT, 0, s>>>(keys, nh, tv, F->vtx_off);
+    k_bricks<<<(unsigned)(1 + pl.brick_tiles), BT, 0, s>>>(bricks, bases, 0);
+    k_bricks<<<(unsigned)(bases.tiles + pl.brick_tiles), BT, 0, s>>>(bricks, bases, 1);
+  }
+  // 4. per vertex: twins, pseudonormal, class, cone
+  k_vertex<<<(unsigned)pl.vertex_tiles, VK_THREADS, 0, s>>>(verts_d, T, tv, F->vtx_off, F->vtx_corners, o.ruff_mode,
+                                                            o.saddle_mode, o.force_both_sides, F->vert_mesh, F->d_mesh,
+                                                            n_meshes, absorb, twin, F->vinfo, F->vbits, vpolys,
+                                                            F->d_stats);
+  // 5. edges with their classes and extrusion sides; the vertex list
+  {
+    EdgeArgs E;
+    E.rec = F->face_rec;
+    E.twin = twin;
+    E.face_mesh = F->face_mesh;
+    E.md = F->d_mesh;
+    E.edges = F->edges;
+    E.face_edges = F->face_edges;
+    E.cls = F->edge_cls;
+    E.eslack = F->eslack;
+    E.eid = eid;
+    E.vbits = F->vbits;
+    E.vpoly = F->vpoly;
+    E.stats = F->d_stats;
+    E.vpolys = vpolys;
+    E.epolys = epolys;
+    E.nf = tf;
+    E.ne = ne;
+    E.nv = tv;
+    E.blocks = (nh + BT - 1) / BT;
+    E.vertex_tiles = pl.vertex_tiles;
+    E.absorb = absorb;
+    E.n_meshes = n_meshes;
+    E.force_both = o.force_both_sides;
+    k_edges<<<(unsigned)(E.blocks + (pl.vertex_tiles + QV - 1) / QV), BT, 0, s>>>(E);
+  }
+  // 6. face slacks, the edge list (the class statistics, which only the feature
   // counts report, are taken by csc_features_sync when it reads them back)
-  CK(queue_compact(EdgeSides{F->edge_cls}, ne, F->epoly, &F->d_stats[ST_NEPOLY], F->t_scan, s));
+  {
+    ListArgs Q;
+    Q.T = T;
+    Q.face_edges = F->face_edges;
+    Q.vbits = F->vbits;
+    Q.eslack = F->eslack;
+    Q.cls = F->edge_cls;
+    Q.eid = eid;
+    Q.fslack = F->fslack;
+    Q.fabsorbed = F->fabsorbed;
+    Q.epoly = F->epoly;
+    Q.stats = F->d_stats;
+    Q.epolys = epolys;
+    // a list block adds up the sums before it: few blocks where there are many tiles
+    Q.list_tiles = pl.face_tiles / 512 < 1 ? 1 : (pl.face_tiles / 512 > 32 ? 32 : pl.face_tiles / 512);
+    Q.lists = (pl.face_tiles + Q.list_tiles - 1) / Q.list_tiles;
+    Q.nf = tf;
+    Q.ne = ne;
+    k_lists<<<(unsigned)(Q.lists + pl.face_tiles), BT, 0, s>>>(Q);
+  }
   F->classes_counted = false;
-  // 5. join the side stream
-  CK(hipStreamWaitEvent(s, F->ev_join, 0));
   CK(hipGetLastError());
 #undef CK
   F->built = true;

@@ -206,7 +206,6 @@ struct csc_features {
   int64_t nv = 0, nf = 0, ne = 0;   // totals over the batch
   int64_t nbt = 0;                  // bricks of all grids
   csc_options opt{};
-  int sort_bits = 1;
 
   char* arena = nullptr;
   size_t arena_bytes = 0;
@@ -216,10 +215,10 @@ struct csc_features {
   int32_t* v_off = nullptr;         // [n_meshes+1] first vertex
   int32_t* brick_base = nullptr;    // [n_meshes+1] first brick
   int32_t* tris_g = nullptr;        // [nf][3] global vertex indices (sanitised)
-  int32_t* face_mesh = nullptr;     // [nf]
-  int32_t* vert_mesh = nullptr;     // [nv]
+  int32_t* face_mesh = nullptr;     // [nf], batches of more than one mesh only
+  int32_t* vert_mesh = nullptr;     // [nv], likewise
   int32_t* vtx_off = nullptr;       // [nv+1]
-  int32_t* vtx_corners = nullptr;   // [3nf] per vertex its corners 3f+j, ascending
+  int32_t* vtx_corners = nullptr;   // [3nf] per vertex its corners 3f+j
   int32_t* face_edges = nullptr;    // [3nf]
   int4* edges = nullptr;            // [ne] (a, b, f_left, f_right), global indices
   FaceRec* face_rec = nullptr;      // [nf] corners, vertex ids and unit normal of each face
@@ -232,22 +231,8 @@ struct csc_features {
   int32_t* brick_list = nullptr;    // [nbt] slot -> brick
   int32_t* brick_mesh = nullptr;    // [nbt] slot -> mesh
   int32_t* first_slot = nullptr;    // [n_meshes+1] first slot of each mesh's bricks
-  int32_t* t_a = nullptr;           // temporaries
-  int32_t* t_b = nullptr;
-  int32_t* t_c = nullptr;
-  int32_t* t_scan = nullptr;
-  void* t_sort = nullptr;           // radix sort scratch
-  size_t t_sort_bytes = 0;
   int64_t* d_stats = nullptr;       // [ST_COUNT] counters; ST_ERR holds the error bits
   int64_t* h_stats = nullptr;       // pinned host mirror [ST_COUNT]
-  // the build's brick marking runs on `side`, forked from and joined back into
-  // the caller's stream with the two events (capturable: a parallel branch)
-  hipStream_t side = nullptr;
-  hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-  hipEvent_t ev_geom = nullptr;     // the face records are written (the vertex and edge passes read them)
-  int32_t* brick_flag = nullptr;    // [nbt + 1] brick marks of the build
-  int32_t* t_scan2 = nullptr;       // scan temporaries of the side branch
-  int32_t* t_eid = nullptr;         // [3nf + 1] edge id of each owned half-edge (prefix sum, side branch)
   uint8_t* fslack = nullptr;        // [nf] side slack of the face prism: the largest code of its absorbed
                                     // edges and vertices (1/1024 cells)
   uint8_t* eslack = nullptr;        // [ne] slack code of each absorbed edge (0: not absorbed)
