@@ -86,3 +86,32 @@ def test_more_vertices_than_the_buckets_hold():
     # the shell of half-width 3 h around the torus holds 2 * 3 h * 4 pi^2 R r in volume
     shell = 6.0 * 4.0 * np.pi ** 2 * R * r * N * N
     assert abs(band.n_band - shell) <= 0.01 * shell and err <= 1e-6 + 1e-5 / N
+
+
+def test_band_offsets_at_the_store_sizes_of_both_scans():
+    """The band's place in the outputs from the one-block scan of the bricks' counts, at
+    the edges of its runs of 4096 and its largest store, against the general scan: the
+    same offsets and cells, bit for bit."""
+    parts = [meshgen.icosphere(3), meshgen.torus(24, 18), meshgen.icosphere(1)]
+    grids = [Grid.unit(40, 3), Grid.unit(208, 3), Grid.unit(24, 3)]
+    verts = torch.from_numpy(np.concatenate([v for v, _ in parts])).cuda()
+    tris = torch.from_numpy(np.concatenate([f for _, f in parts])).cuda()
+    f = P.csc_build_features_batched(verts, tris, [v.shape[0] for v, _ in parts], [t.shape[0] for _, t in parts], grids)
+    nb = int(f.info()["n_bricks"])
+    assert nb < 4095
+
+    def scan(n):
+        print("[case] store of", n, "bricks", flush=True)
+        nbytes, mx = P.csc_scan_convert_workspace_for(f, n)
+        out = tuple(torch.full((mx,), -7, dtype=t, device="cuda") for t in (torch.float32, torch.int32, torch.int32))
+        off = torch.full((len(parts) + 1,), -1, dtype=torch.int64, device="cuda")
+        P.csc_scan_convert_batched(f, torch.empty(nbytes, dtype=torch.uint8, device="cuda"), out, off)
+        off = off.cpu().tolist()
+        return off, [o[:off[-1]].cpu() for o in out]
+
+    off, out = scan(16385)  # the general scan
+    assert off[0] == 0 and all(a < b for a, b in zip(off, off[1:]))
+    for n in (nb, 4095, 4096, 4097, 8193, 16384):
+        got_off, got = scan(n)
+        assert got_off == off
+        assert all(torch.equal(a, b) for a, b in zip(got, out))
