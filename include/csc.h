@@ -399,8 +399,10 @@ int csc_timing_reset(void);
 int csc_timing_read(double* ms, int64_t* calls, int32_t n);
 const char* csc_timing_stage_name(int32_t stage);
 
-/* Release a handle and its device memory (waits for nothing; the caller must
- * make sure no queued work still uses it). NULL is accepted. */
+/* Release a handle and its device memory, after the work queued on its device has
+ * ended. Up to 256 MiB per device of released memory are kept for the process's next
+ * handles and welds, and given back when they stay unused or an allocation runs out
+ * of memory. NULL is accepted. */
 void csc_features_free(csc_features* f);
 
 /* Static, human-readable text of a status code. */

@@ -3,6 +3,8 @@
 #include <string.h>
 
 #include <mutex>
+#include <new>
+#include <vector>
 
 #include "geometry.h"
 #include "internal.h"
@@ -11,6 +13,57 @@ namespace {
 thread_local char g_last_hip[256] = "";
 std::mutex g_dev_mu;
 int g_dev_ok[64];  // 0 unknown, 1 gfx950, 2 other
+
+struct Block {
+  char* p;
+  size_t bytes;
+  uint64_t stamp;
+};
+struct DevicePool {
+  std::vector<Block> blocks;
+  std::vector<int64_t*> pinned;
+  size_t bytes = 0;
+  uint64_t gives = 0;
+};
+// never destroyed: the runtime may be gone before this object would be
+struct Pools {
+  std::mutex mu;
+  DevicePool dev[64];
+};
+Pools* pools() {
+  static Pools* p = new (std::nothrow) Pools();
+  return p;
+}
+
+// frees on device dev, from whatever device is current
+template <typename F>
+void on_device(int dev, F f) {
+  int cur = dev;
+  (void)hipGetDevice(&cur);
+  if (cur != dev) (void)hipSetDevice(dev);
+  f();
+  if (cur != dev) (void)hipSetDevice(cur);
+}
+
+// allocations and frees of its scope leave another thread's stream capture alone
+struct CaptureRelaxed {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  bool on = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  ~CaptureRelaxed() {
+    if (on) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+};
+
+// every kept block of a device given back
+void pool_empty(int dev) {
+  std::vector<Block> all;
+  {
+    std::lock_guard<std::mutex> lk(pools()->mu);
+    all.swap(pools()->dev[dev].blocks);
+    pools()->dev[dev].bytes = 0;
+  }
+  for (const Block& b : all) (void)hipFree(b.p);
+}
 }  // namespace
 
 namespace csc {
@@ -35,6 +88,118 @@ int check_device() {
     g_dev_ok[dev] = strncmp(p.gcnArchName, "gfx950", 6) == 0 ? 1 : 2;
   }
   return g_dev_ok[dev] == 1 ? CSC_OK : CSC_UNSUPPORTED_DEVICE;
+}
+
+hipError_t pool_take(size_t bytes, char** p, size_t* got, int* dev) {
+  hipError_t e = hipGetDevice(dev);
+  if (e != hipSuccess) return e;
+  const bool pooled = pools() && *dev >= 0 && *dev < 64;
+  if (pooled) {
+    std::lock_guard<std::mutex> lk(pools()->mu);
+    DevicePool& D = pools()->dev[*dev];
+    // the smallest that holds it, unless more than half of it would lie idle
+    const size_t most = bytes > ((size_t)1 << 20) ? 2 * bytes : (size_t)2 << 20;
+    int best = -1;
+    for (int i = 0; i < (int)D.blocks.size(); i++)
+      if (D.blocks[i].bytes >= bytes && D.blocks[i].bytes <= most &&
+          (best < 0 || D.blocks[i].bytes < D.blocks[best].bytes))
+        best = i;
+    if (best >= 0) {
+      *p = D.blocks[best].p;
+      *got = D.blocks[best].bytes;
+      D.bytes -= D.blocks[best].bytes;
+      D.blocks[best] = D.blocks.back();
+      D.blocks.pop_back();
+      return hipSuccess;
+    }
+  }
+  CaptureRelaxed relaxed;
+  // up to an eighth more, so that the block serves a somewhat larger mesh as well
+  size_t step = 4096;
+  while (step * 16 <= bytes) step *= 2;
+  const size_t round = pooled ? (bytes + step - 1) / step * step : bytes;
+  e = hipMalloc((void**)p, round);
+  *got = round;
+  if (e == hipErrorOutOfMemory && pooled) {
+    (void)hipGetLastError();
+    pool_empty(*dev);
+    e = hipMalloc((void**)p, bytes);
+    *got = bytes;
+  }
+  if (e != hipSuccess) *p = nullptr;
+  return e;
+}
+
+void pool_give(int dev, char* p, size_t bytes) {
+  std::vector<Block> old;
+  if (pools() && dev >= 0 && dev < 64 && bytes <= POOL_BYTES) {
+    try {
+      std::lock_guard<std::mutex> lk(pools()->mu);
+      DevicePool& D = pools()->dev[dev];
+      D.gives++;
+      old.reserve(D.blocks.size());
+      D.blocks.reserve(POOL_BLOCKS + 1);
+      D.blocks.push_back(Block{p, bytes, D.gives});
+      D.bytes += bytes;
+      p = nullptr;
+      // out: the unused, and the oldest while there are too many
+      for (size_t i = 0; i < D.blocks.size();) {
+        size_t oldest = 0;
+        for (size_t j = 1; j < D.blocks.size(); j++)
+          if (D.blocks[j].stamp < D.blocks[oldest].stamp) oldest = j;
+        if (D.bytes <= POOL_BYTES && D.blocks.size() <= POOL_BLOCKS && D.gives - D.blocks[oldest].stamp <= POOL_AGE)
+          break;
+        old.push_back(D.blocks[oldest]);
+        D.bytes -= D.blocks[oldest].bytes;
+        D.blocks[oldest] = D.blocks.back();
+        D.blocks.pop_back();
+      }
+    } catch (const std::bad_alloc&) {  // p is not kept then
+    }
+  }
+  if (!p && old.empty()) return;
+  CaptureRelaxed relaxed;
+  if (p) (void)hipFree(p);
+  for (const Block& b : old) (void)hipFree(b.p);
+}
+
+hipError_t pinned_take(int64_t** p, int* dev) {
+  hipError_t e = hipGetDevice(dev);
+  if (e != hipSuccess) return e;
+  if (pools() && *dev >= 0 && *dev < 64) {
+    std::lock_guard<std::mutex> lk(pools()->mu);
+    std::vector<int64_t*>& v = pools()->dev[*dev].pinned;
+    if (!v.empty()) {
+      *p = v.back();
+      v.pop_back();
+      return hipSuccess;
+    }
+  }
+  CaptureRelaxed relaxed;
+  e = hipHostMalloc((void**)p, sizeof(int64_t) * PINNED_WORDS, hipHostMallocDefault);
+  if (e != hipSuccess) *p = nullptr;
+  return e;
+}
+
+void pinned_give(int dev, int64_t* p) {
+  if (pools() && dev >= 0 && dev < 64) {
+    try {
+      std::lock_guard<std::mutex> lk(pools()->mu);
+      std::vector<int64_t*>& v = pools()->dev[dev].pinned;
+      if (v.size() < (size_t)POOL_BLOCKS) {
+        v.push_back(p);
+        return;
+      }
+    } catch (const std::bad_alloc&) {
+    }
+  }
+  (void)hipHostFree(p);
+}
+
+bool device_idle(int dev) {
+  hipError_t e = hipSuccess;
+  on_device(dev, [&] { e = hipDeviceSynchronize(); });
+  return e == hipSuccess;
 }
 
 }  // namespace csc
@@ -67,9 +232,18 @@ extern "C" int csc_features_info(const csc_features* f, csc_feature_info* info) 
 
 extern "C" void csc_features_free(csc_features* f) {
   if (!f) return;
-  if (f->arena) (void)hipFree(f->arena);
+  // What the handle queued may still run, on any stream: its memory is kept for the
+  // next handle only once the device has finished it (as hipFree would wait for it).
+  const bool idle = (f->arena || f->h_stats) && device_idle(f->device);
+  if (f->arena) {
+    if (idle) pool_give(f->device, f->arena, f->arena_bytes);
+    else (void)hipFree(f->arena);
+  }
   if (f->face_order) (void)hipFree(f->face_order);
-  if (f->h_stats) (void)hipHostFree(f->h_stats);
+  if (f->h_stats) {
+    if (idle) pinned_give(f->device, f->h_stats);
+    else (void)hipHostFree(f->h_stats);
+  }
   delete f;
 }
 

@@ -126,9 +126,34 @@ __device__ inline int scan_tiles(int32_t* sums, int64_t n, int* ws) {
   return carry;
 }
 
-// the counters and brick flags (n 16-byte words at z) and the statistics zeroed
-__global__ __launch_bounds__(BT) void k_begin(uint4* z, int64_t n, int64_t* stats) {
-  if (blockIdx.x == 0 && threadIdx.x < ST_COUNT) stats[threadIdx.x] = 0;
+// Descriptors and offset tables of a few meshes as kernel arguments: they reach the
+// device with the build's first launch (a host-to-device copy costs 12 us).
+constexpr int TABLE_MESHES = 4;
+struct MeshTables {
+  MeshDesc m[TABLE_MESHES];
+  MeshDesc* md;
+  int32_t *f_off, *v_off, *brick_base;
+  int32_t n, nf, nv, nbt;  // meshes to write (0: the tables stand), totals
+};
+
+// the counters and brick flags (n 16-byte words at z) and the statistics zeroed, the
+// tables written
+__global__ __launch_bounds__(BT) void k_begin(uint4* z, int64_t n, int64_t* stats, MeshTables M) {
+  if (blockIdx.x == 0) {
+    if (threadIdx.x < ST_COUNT) stats[threadIdx.x] = 0;
+    if ((int)threadIdx.x < M.n) {
+      const int m = threadIdx.x;
+      M.md[m] = M.m[m];
+      M.f_off[m] = M.m[m].f_off;
+      M.v_off[m] = M.m[m].v_off;
+      M.brick_base[m] = M.m[m].brick_base;
+    }
+    if (threadIdx.x == 0 && M.n > 0) {
+      M.f_off[M.n] = M.nf;
+      M.v_off[M.n] = M.nv;
+      M.brick_base[M.n] = M.nbt;
+    }
+  }
   const int64_t step = (int64_t)gridDim.x * BT;
   for (int64_t i = blockIdx.x * (int64_t)BT + threadIdx.x; i < n; i += step) z[i] = make_uint4(0u, 0u, 0u, 0u);
 }
@@ -1312,19 +1337,15 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
       F->arena = nullptr;
       F->arena_bytes = 0;
     }
-    he = hipMalloc((void**)&F->arena, L.total);
+    he = pool_take(L.total, &F->arena, &F->arena_bytes, &F->device);
     if (he != hipSuccess) {
-      F->arena = nullptr;
+      F->arena_bytes = 0;
       return fail(he == hipErrorOutOfMemory ? CSC_OUT_OF_MEMORY : fail_hip(he));
     }
-    F->arena_bytes = L.total;
   }
   if (!F->h_stats) {
-    he = hipHostMalloc((void**)&F->h_stats, sizeof(int64_t) * ST_COUNT, hipHostMallocDefault);
-    if (he != hipSuccess) {
-      F->h_stats = nullptr;
-      return fail(fail_hip(he));
-    }
+    he = pinned_take(&F->h_stats, &F->device);
+    if (he != hipSuccess) return fail(fail_hip(he));
   }
   char* A = F->arena;
   F->n_meshes = n_meshes;
@@ -1367,9 +1388,26 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
     if (e_ != hipSuccess) return fail(fail_hip(e_)); \
   } while (0)
 
+  MeshTables M;
+  M.n = 0;
   if (config_changed) {
     // descriptors and offset tables change only with the configuration (never
     // inside a captured replay of the same batch)
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    CK(hipStreamIsCapturing(s, &cap));
+    if (cap != hipStreamCaptureStatusNone) CK(hipErrorStreamCaptureUnsupported);
+  }
+  if (config_changed && n_meshes <= TABLE_MESHES) {
+    for (int m = 0; m < n_meshes; m++) M.m[m] = mesh[m];
+    M.md = F->d_mesh;
+    M.f_off = F->f_off;
+    M.v_off = F->v_off;
+    M.brick_base = F->brick_base;
+    M.n = n_meshes;
+    M.nf = (int32_t)tf;
+    M.nv = (int32_t)tv;
+    M.nbt = (int32_t)tb;
+  } else if (config_changed) {
     std::vector<int32_t> tabs(3 * (size_t)(n_meshes + 1));
     for (int m = 0; m <= n_meshes; m++) {
       tabs[m] = m < n_meshes ? mesh[m].f_off : (int32_t)tf;
@@ -1381,8 +1419,8 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
     CK(hipMemcpy(F->v_off, tabs.data() + (n_meshes + 1), sizeof(int32_t) * (n_meshes + 1), hipMemcpyHostToDevice));
     CK(hipMemcpy(F->brick_base, tabs.data() + 2 * (n_meshes + 1), sizeof(int32_t) * (n_meshes + 1),
                  hipMemcpyHostToDevice));
-    F->mesh = mesh;
   }
+  if (config_changed) F->mesh = mesh;
 
   StageTimer timer(TS_BUILD, s);
   const int64_t nh = 3 * tf, ne = te;
@@ -1401,7 +1439,7 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
   {
     const int64_t n = (int64_t)(z.bytes / 16);
     const unsigned need = grid_1d(n, 4 * BT);
-    k_begin<<<need < 2048 ? need : 2048, BT, 0, s>>>((uint4*)zero, n, F->d_stats);
+    k_begin<<<need < 2048 ? need : 2048, BT, 0, s>>>((uint4*)zero, n, F->d_stats, M);
   }
   // 2. inputs, face records, band bricks, counts
   {

@@ -233,14 +233,23 @@ extern "C" int csc_weld_soup(const float* soup_d, int64_t nf, float* verts_d, in
   hipStream_t s = (hipStream_t)stream;
   const WeldLayout L = weld_layout(3 * nf);
   char* W = nullptr;
-  hipError_t e = hipMallocAsync((void**)&W, L.total, s);
+  int64_t* pinned = nullptr;
+  size_t bytes = 0;
+  int dev = 0;
+  hipError_t e = pool_take(L.total, &W, &bytes, &dev);
   if (e != hipSuccess) return e == hipErrorOutOfMemory ? CSC_OUT_OF_MEMORY : fail_hip(e);
-  WeldCount h = {0, 0, 0};
-  e = weld_queue(soup_d, nf, verts_d, tris_d, W, L, &h, s);
-  const hipError_t ef = hipFreeAsync(W, s);
-  if (e == hipSuccess) e = ef;
+  e = pinned_take(&pinned, &dev);
+  static_assert(sizeof(WeldCount) <= sizeof(int64_t) * PINNED_WORDS, "the report fits the pinned words");
+  if (e == hipSuccess) e = weld_queue(soup_d, nf, verts_d, tris_d, W, L, (WeldCount*)pinned, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) return fail_hip(e);
+  if (e != hipSuccess) {  // queued work may still use them: freed, which waits for it
+    (void)hipFree(W);
+    if (pinned) (void)hipHostFree(pinned);
+    return fail_hip(e);
+  }
+  const WeldCount h = *(const WeldCount*)pinned;
+  pool_give(dev, W, bytes);
+  pinned_give(dev, pinned);
   if (h.bad) return CSC_INVALID_ARG;
   *nv = h.nv;
   return CSC_OK;
