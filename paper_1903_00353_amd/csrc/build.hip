@@ -527,25 +527,35 @@ static_assert(BT == 256, "three blocks of half-edges per face tile, four wavefro
 // axis, edge wedges and vertex cones within band*h + eps of their feature), and
 // a scan writes only cells within band*h of a feature, so every cell a scan can
 // write has its brick marked by one of the faces holding its feature.
-__device__ inline void face_geom_one(const float* __restrict__ V, int64_t f, int32_t ia, int32_t ib, int32_t ic,
-                                     const MeshDesc& g, FaceRec* rec, uint8_t* flag, int64_t* stats) {
+struct FaceBox {
+  d3 un, a;     // unit normal (zero: degenerate, the whole box is kept), first corner
+  double ext;
+  int lo[3], n[3];  // bricks (n[0] = 0: none)
+};
+
+// the record and box of face f = (ia, ib, ic)
+__device__ inline FaceBox face_geom_one(const float* __restrict__ V, int64_t f, int32_t ia, int32_t ib, int32_t ic,
+                                        const MeshDesc& g, FaceRec* rec, int64_t* stats) {
   const f3 af = vload_f(V, ia), bf = vload_f(V, ib), cf = vload_f(V, ic);
   const d3 a = mkd(af.x, af.y, af.z), b = mkd(bf.x, bf.y, bf.z), c = mkd(cf.x, cf.y, cf.z);
   const d3 n = cross(b - a, c - a);
   const double l = len(n);
-  float4 un4 = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (!(l > 0)) atomicOr(err_word(stats), ERR_DEGENERATE);
-  else un4 = make_float4((float)(n.x / l), (float)(n.y / l), (float)(n.z / l), 0.f);
+  const bool cull = l > 0;
+  FaceBox B;
+  B.a = a;
+  B.un = cull ? mkd(n.x / l, n.y / l, n.z / l) : mkd(0.0, 0.0, 0.0);
+  if (!cull) atomicOr(err_word(stats), ERR_DEGENERATE);
   // the face's record: later passes read one aligned sector per face instead of
   // three vertex gathers
   FaceRec& o = rec[f];
   o.c[0] = make_float4(af.x, af.y, af.z, __int_as_float(ia));
   o.c[1] = make_float4(bf.x, bf.y, bf.z, __int_as_float(ib));
   o.c[2] = make_float4(cf.x, cf.y, cf.z, __int_as_float(ic));
-  o.n = un4;
+  o.n = make_float4((float)B.un.x, (float)B.un.y, (float)B.un.z, 0.f);
   const double r = g.whd + g.epsd;
   const double X[3][3] = {{a.x, b.x, c.x}, {a.y, b.y, c.y}, {a.z, b.z, c.z}};
-  int lo[3], hi[3];
+  bool none = false;
+#pragma unroll
   for (int ax = 0; ax < 3; ax++) {
     const double x0 = X[ax][0], x1 = X[ax][1], x2 = X[ax][2];
     const double mn = fmin(x0, fmin(x1, x2)) - r, mx = fmax(x0, fmax(x1, x2)) + r;
@@ -555,10 +565,14 @@ __device__ inline void face_geom_one(const float* __restrict__ V, int64_t f, int
     double hi_c = floor((mx - g.origin[ax]) * g.inv_h - 0.5 + 1e-3);
     lo_c = fmax(lo_c, 0.0);
     hi_c = fmin(hi_c, (double)(g.n[ax] - 1));
-    if (!(lo_c <= hi_c)) return;
-    lo[ax] = (int)lo_c / BRICK;
-    hi[ax] = (int)hi_c / BRICK;
+    if (!(lo_c <= hi_c)) {
+      none = true;
+      lo_c = hi_c = 0.0;
+    }
+    B.lo[ax] = (int)lo_c / BRICK;
+    B.n[ax] = (int)hi_c / BRICK - B.lo[ax] + 1;
   }
+  if (none) B.n[0] = 0;
   // A brick is kept only if some cell centre in it can lie within r of the face's
   // plane: a cell within band*h of an edge or vertex is that close to a face
   // holding it, and no key is written farther out. The centres of brick (x, y, z)
@@ -566,19 +580,18 @@ __device__ inline void face_geom_one(const float* __restrict__ V, int64_t f, int
   // whose distance to the plane is at least |n.(c - a)| - (BRICK - 1) h |n|_1 / 2.
   // The test gets 1e-3 h of slack over r against rounding; a degenerate face
   // keeps its whole box.
-  const bool cull = l > 0;
-  const d3 un = cull ? mkd(n.x / l, n.y / l, n.z / l) : mkd(0.0, 0.0, 0.0);
-  const double ext = 0.5 * (BRICK - 1) * g.h * (fabs(un.x) + fabs(un.y) + fabs(un.z)), lim = r + 1e-3 * g.h;
-  for (int z = lo[2]; z <= hi[2]; z++)
-    for (int y = lo[1]; y <= hi[1]; y++)
-      for (int x = lo[0]; x <= hi[0]; x++) {
-        if (cull) {
-          const d3 c = mkd(g.origin[0] + (BRICK * x + BRICK / 2) * g.h, g.origin[1] + (BRICK * y + BRICK / 2) * g.h,
-                           g.origin[2] + (BRICK * z + BRICK / 2) * g.h);
-          if (fabs(dot(un, c - a)) - ext > lim) continue;
-        }
-        flag[brick_pos(g, x, y, z)] = 1;  // plain stores: no read to wait for
-      }
+  B.ext = 0.5 * (BRICK - 1) * g.h * (fabs(B.un.x) + fabs(B.un.y) + fabs(B.un.z));
+  return B;
+}
+
+// Marks brick (x, y, z) of a face's box if the face's plane is near enough: a plain
+// store, no read to wait for (leaving out what the block has marked already, by a
+// table in LDS, cost more than the stores: 64 meshes' build 408 -> 426 us).
+__device__ inline void mark_brick(const MeshDesc& g, d3 un, d3 a, double ext, int x, int y, int z, uint8_t* flag) {
+  const d3 c = mkd(g.origin[0] + (BRICK * x + BRICK / 2) * g.h, g.origin[1] + (BRICK * y + BRICK / 2) * g.h,
+                   g.origin[2] + (BRICK * z + BRICK / 2) * g.h);
+  if (fabs(dot(un, c - a)) - ext > g.whd + g.epsd + 1e-3 * g.h) return;
+  flag[brick_pos(g, x, y, z)] = 1;
 }
 
 struct InputArgs {
@@ -599,55 +612,109 @@ struct InputArgs {
   int n_meshes, bucket_shift, buckets;
 };
 
-// The input passes in one launch, a persistent grid striding over tiles of BT faces:
+// The input passes in one launch, a persistent grid striding over tiles of FACES faces:
 // finite coordinates; of each face its mesh, index range and repeated-corner
 // checks, global indices (a face with a bad index is replaced by three copies of its
 // mesh's first vertex so that every later access stays in bounds; the build then
-// reports the error), its record and band bricks (face_geom_one), its owned
+// reports the error), its record and band bricks, its owned
 // half-edges (u -> w with u < w: they number the edges) counted per wavefront, and its
 // corners counted per bucket of vertices, in LDS until the block is done. The mesh
 // of a tile's first face is searched once; each thread steps up from there.
+// FACES = BT: a thread marks its face's bricks. FACES = 64, for few faces: the
+// first wavefront takes the faces, and the whole block their rows of bricks, one
+// after another: a mesh of few faces fills more of the chip, and a face of hundreds
+// of bricks among small ones holds up nobody (12 faces over 64^3 cells 45 -> 8 us; a wide
+// band of 25,984 faces 97 -> 40; 70,000 faces 29 -> 19). A thread's own loop has less to
+// read and no barrier, and is the faster from some 200,000 faces on (360,000: build 108
+// us and shared 121; 64 meshes, 1.75M: 405 and 508).
+template <int FACES>
 __global__ __launch_bounds__(BT) void k_inputs(InputArgs P) {
+  constexpr bool SHARE = FACES < BT;
   __shared__ int s_count[MAX_BUCKETS];
+  __shared__ double s_plane[SHARE ? FACES : 1][8];  // un, a, ext (and a word of padding)
+  __shared__ int s_box[SHARE ? FACES : 1][6];       // lo, n[0], n[1], mesh
+  __shared__ int64_t s_row[SHARE ? FACES + 1 : 1];
   const int t = threadIdx.x;
   if (P.bucket_count)
     for (int b = t; b < P.buckets; b += BT) s_count[b] = 0;
   __syncthreads();
-  for (int64_t tile = blockIdx.x; tile < P.face_tiles; tile += gridDim.x) {
-    const int64_t f = tile * BT + t;
-    int owned = 0;
-    if (f < P.nf) {
-      int m = 0;
-      if (P.n_meshes > 1) {
-        m = segment_from(P.f_off, find_segment(P.f_off, P.n_meshes + 1, tile * BT), f);
-        P.face_mesh[f] = m;
+  const int64_t tiles = P.face_tiles * (BT / FACES);
+  for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    const int64_t f = tile * FACES + t;
+    if (!SHARE || t < FACES) {
+      int owned = 0, m = 0;
+      FaceBox B{};
+      if (f < P.nf) {
+        if (P.n_meshes > 1) {
+          m = segment_from(P.f_off, find_segment(P.f_off, P.n_meshes + 1, tile * FACES), f);
+          P.face_mesh[f] = m;
+        }
+        const int32_t vo = P.n_meshes > 1 ? P.v_off[m] : 0;
+        const int32_t nvm = P.n_meshes > 1 ? P.v_off[m + 1] - vo : (int32_t)P.nv;
+        int32_t a = P.T[3 * f], b = P.T[3 * f + 1], c = P.T[3 * f + 2];
+        if (a < 0 || b < 0 || c < 0 || a >= nvm || b >= nvm || c >= nvm) {
+          atomicOr(err_word(P.stats), ERR_INDEX);
+          a = b = c = 0;
+        } else if (a == b || b == c || a == c) {
+          atomicOr(err_word(P.stats), ERR_REPEAT);
+        }
+        owned = (a < b ? 1 : 0) + (b < c ? 1 : 0) + (c < a ? 1 : 0);
+        a += vo;
+        b += vo;
+        c += vo;
+        P.tg[3 * f] = a;
+        P.tg[3 * f + 1] = b;
+        P.tg[3 * f + 2] = c;
+        if (P.bucket_count) {
+          atomicAdd(&s_count[a >> P.bucket_shift], 1);
+          atomicAdd(&s_count[b >> P.bucket_shift], 1);
+          atomicAdd(&s_count[c >> P.bucket_shift], 1);
+        }
+        B = face_geom_one(P.V, f, a, b, c, P.md[m], P.rec, P.stats);
+        if (!SHARE && B.n[0] > 0)
+          for (int z = B.lo[2]; z < B.lo[2] + B.n[2]; z++)
+            for (int y = B.lo[1]; y < B.lo[1] + B.n[1]; y++)
+              for (int x = B.lo[0]; x < B.lo[0] + B.n[0]; x++)
+                mark_brick(P.md[m], B.un, B.a, B.ext, x, y, z, P.flag);
       }
-      const int32_t vo = P.n_meshes > 1 ? P.v_off[m] : 0;
-      const int32_t nvm = P.n_meshes > 1 ? P.v_off[m + 1] - vo : (int32_t)P.nv;
-      int32_t a = P.T[3 * f], b = P.T[3 * f + 1], c = P.T[3 * f + 2];
-      if (a < 0 || b < 0 || c < 0 || a >= nvm || b >= nvm || c >= nvm) {
-        atomicOr(err_word(P.stats), ERR_INDEX);
-        a = b = c = 0;
-      } else if (a == b || b == c || a == c) {
-        atomicOr(err_word(P.stats), ERR_REPEAT);
+      if (SHARE) {
+        const double v[7] = {B.un.x, B.un.y, B.un.z, B.a.x, B.a.y, B.a.z, B.ext};
+        for (int k = 0; k < 7; k++) s_plane[t][k] = v[k];
+        const int w[6] = {B.lo[0], B.lo[1], B.lo[2], B.n[0], B.n[1], m};
+        for (int k = 0; k < 6; k++) s_box[t][k] = w[k];
+        int64_t incl = B.n[0] > 0 ? (int64_t)B.n[1] * B.n[2] : 0;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int64_t x = __shfl_up(incl, o, 64);
+          if (t >= o) incl += x;
+        }
+        s_row[t + 1] = incl;
+        if (t == 0) s_row[0] = 0;
       }
-      owned = (a < b ? 1 : 0) + (b < c ? 1 : 0) + (c < a ? 1 : 0);
-      a += vo;
-      b += vo;
-      c += vo;
-      P.tg[3 * f] = a;
-      P.tg[3 * f + 1] = b;
-      P.tg[3 * f + 2] = c;
-      if (P.bucket_count) {
-        atomicAdd(&s_count[a >> P.bucket_shift], 1);
-        atomicAdd(&s_count[b >> P.bucket_shift], 1);
-        atomicAdd(&s_count[c >> P.bucket_shift], 1);
-      }
-      face_geom_one(P.V, f, a, b, c, P.md[m], P.rec, P.flag, P.stats);
+      // owned half-edges per wavefront of 64 faces: no barrier in the loop
+      const int sum = __popcll(__ballot(owned & 1)) + 2 * __popcll(__ballot(owned & 2));
+      if ((t & 63) == 0) P.owned[tile * (FACES / 64) + (t >> 6)] = sum;
     }
-    // owned half-edges per wavefront of 64 faces: no barrier in the loop
-    const int sum = __popcll(__ballot(owned & 1)) + 2 * __popcll(__ballot(owned & 2));
-    if ((t & 63) == 0) P.owned[tile * (BT / 64) + (t >> 6)] = sum;
+    if (SHARE) {
+      __syncthreads();
+      const int64_t rows = s_row[FACES];
+      auto mark_rows = [&](auto mesh) {  // this thread's rows of bricks
+        int k = 0;
+        for (int64_t p = t; p < rows; p += BT) {
+          while (s_row[k + 1] <= p) k++;
+          const int row = (int)(p - s_row[k]), z = row / s_box[k][4], y = row - z * s_box[k][4];
+          const d3 un = mkd(s_plane[k][0], s_plane[k][1], s_plane[k][2]);
+          const d3 a = mkd(s_plane[k][3], s_plane[k][4], s_plane[k][5]);
+          const double ext = s_plane[k][6];
+          const MeshDesc& g = mesh(k);
+          const int x0 = s_box[k][0], x1 = x0 + s_box[k][3];
+          for (int x = x0; x < x1; x++) mark_brick(g, un, a, ext, x, s_box[k][1] + y, s_box[k][2] + z, P.flag);
+        }
+      };
+      if (P.n_meshes == 1) mark_rows([&](int) -> const MeshDesc& { return P.md[0]; });
+      else mark_rows([&](int k) -> const MeshDesc& { return P.md[s_box[k][5]]; });
+      __syncthreads();
+    }
   }
   const int64_t step = (int64_t)gridDim.x * BT;
   for (int64_t i = blockIdx.x * (int64_t)BT + t; i < 3 * P.nv; i += step)
@@ -1128,6 +1195,7 @@ constexpr int64_t DEAL_BIG = 1 << 23;  // corners from which the long tiles are 
 // Blocks of the input pass: each adds its corner counts to every bucket once at its end
 // (a batch of 64 meshes: build 427 us with 1024, 414 with 2048; 5.2M faces 1212, 1207).
 constexpr int64_t INPUT_BLOCKS = 2048;
+constexpr int64_t INPUT_SHARED = 1 << 17;  // faces up to which a block shares its faces' bricks (k_inputs)
 struct Plan {
   int shift = 0, buckets = 0;
   bool big = false;
@@ -1464,7 +1532,12 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
     I.bucket_shift = pl.shift;
     I.buckets = pl.buckets;
     const int64_t cap = o.geom_blocks > 0 && o.geom_blocks < INPUT_BLOCKS ? o.geom_blocks : INPUT_BLOCKS;
-    k_inputs<<<(unsigned)(pl.face_tiles < cap ? pl.face_tiles : cap), BT, 0, s>>>(I);
+    if (tf <= INPUT_SHARED) {
+      const int64_t tiles = pl.face_tiles * (BT / 64);
+      k_inputs<64><<<(unsigned)(tiles < cap ? tiles : cap), BT, 0, s>>>(I);
+    } else {
+      k_inputs<BT><<<(unsigned)(pl.face_tiles < cap ? pl.face_tiles : cap), BT, 0, s>>>(I);
+    }
   }
   const int32_t* T = F->tris_g;
   // 3. vertex -> corner table, and the bricks counted and numbered

@@ -115,3 +115,27 @@ def test_band_offsets_at_the_store_sizes_of_both_scans():
         got_off, got = scan(n)
         assert got_off == off
         assert all(torch.equal(a, b) for a, b in zip(got, out))
+
+
+def n_bricks(meshes, grids):
+    verts = torch.from_numpy(np.concatenate([v for v, _ in meshes])).cuda()
+    tris = torch.from_numpy(np.concatenate([f for _, f in meshes])).cuda()
+    return int(P.csc_build_features_batched(verts, tris, [v.shape[0] for v, _ in meshes],
+                                            [t.shape[0] for _, t in meshes], grids).info()["n_bricks"])
+
+
+@pytest.mark.parametrize("mesh,grid", [(meshgen.icosphere(0), Grid.unit(100, 3)), (meshgen.icosphere(1), Grid.unit(70, 9)),
+                                       (meshgen.icosphere(3), Grid.unit(33, 1.5)), (meshgen.torus(11, 6), Grid.unit(257, 2))])
+def test_bricks_marked_by_the_block_and_by_the_thread(mesh, grid):
+    """Few faces, whose bricks the block marks together, alone and behind so many faces
+    that each thread marks its own: the same number of bricks."""
+    many = meshgen.torus(300, 230)
+    assert many[1].shape[0] > 1 << 17
+    print("[case] bricks", mesh[1].shape, tuple(grid.n), flush=True)
+    alone = n_bricks([mesh], [grid])
+    assert alone > 0
+    rest = n_bricks([many], [Grid.unit(32, 2)])
+    assert n_bricks([many, mesh], [Grid.unit(32, 2), grid]) == rest + alone
+    # two meshes of few faces: the descriptor is read per face
+    assert n_bricks([mesh, meshgen.icosphere(2)], [grid, Grid.unit(24, 2)]) == \
+        alone + n_bricks([meshgen.icosphere(2)], [Grid.unit(24, 2)])
