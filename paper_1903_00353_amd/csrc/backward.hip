@@ -105,26 +105,48 @@ __device__ inline void seg_step(int run, f3 (&con)[3]) {
 
 // The pass is bound by the latency of its loads and of the table's LDS round
 // trips, so occupancy comes first: a 16 KB table per block of 256 lets 8 blocks
-// share a CU, and the register budget is held to 64 for 8 wavefronts per SIMD.
+// share a CU, and the register budget is held to 64 for 8 wavefronts per SIMD (6
+// wavefronts and no spills: 64 meshes 490 us against 445).
+// What the trips cost is the search for a slot in a crowded table: double hashing, a
+// flush at 224 slots, and few probes where the last chunk brought so many new
+// vertices that the table shares little between its cells: 64 meshes (15.7M cells) 445
+// -> 331 us, 5.2M faces (9.8M cells) 394 -> 381; every chunk with few probes
+// 508 there, with up to 16 always 446 and 370.
 constexpr int BW_THREADS = 256;
 constexpr int BW_WAVES_PER_SIMD = 8;
 constexpr int BW_SLOTS = 512;                 // hash table of (vertex, 3 partial sums) per block
-constexpr int BW_FLUSH = 256;                 // flush once more slots than this are taken
-constexpr int BW_PROBES = 16;                 // a vertex not placed within this many slots goes to HBM
+constexpr int BW_FLUSH = 224;                 // flush once more slots than this are taken
+constexpr int BW_PROBES = 12;                 // a vertex not placed within this many slots goes to HBM,
+constexpr int BW_CROWD = 240, BW_FEW = 2;     // after a chunk with more new vertices than BW_CROWD within BW_FEW
 constexpr int BW_BLOCKS = 2048;               // persistent grid: 8 resident blocks of 256 per CU
 // LDS adds of floats are slow on this chip where 64-bit integer adds are not,
 // so the table sums in fixed point: c * 2^fx, rounded to an integer, when its
 // magnitude is below 2^42 (no overflow; the rounding is at most 2^-41 of the
 // block's largest term), otherwise (a term far larger than the block's first
-// chunk's, or not finite) c goes straight to the gradient. Terms that round to
-// zero add nothing.
-__device__ inline void add_fixed(unsigned long long* slot, float c, int fx, float* direct) {
-  const float v = ldexpf(c, fx);
-  if (fabsf(v) < 4398046511104.f) {  // |v| < 2^42
-    const long long iv = (long long)rintf(v);
-    if (iv != 0) atomicAdd(slot, (unsigned long long)iv);
-  } else if (c != 0.f) {
-    atomicAdd(direct, c);
+// chunk's, or not finite) c goes straight to the gradient.
+struct Fixed {
+  double scale;  // 2^fx
+  float lim;     // 2^(42 - fx): terms of smaller magnitude are summed in fixed point
+};
+
+// rint(c 2^fx): added to 1.5 2^52, the sum's low bits hold the integer
+__device__ inline unsigned long long fixed_bits(float c, double scale) {
+  const double d = fma((double)c, scale, 6755399441055744.0);
+  return (unsigned long long)__double_as_longlong(d) - 0x4338000000000000ull;
+}
+
+// a vertex's term to its slot n (of BW_SLOTS words per component)
+__device__ inline void add_vertex(unsigned long long* slot, int n, f3 c, const Fixed& F, float* direct) {
+  if (fmaxf(fabsf(c.x), fmaxf(fabsf(c.y), fabsf(c.z))) < F.lim && c.x == c.x && c.y == c.y && c.z == c.z) {
+    atomicAdd(slot, fixed_bits(c.x, F.scale));
+    atomicAdd(slot + n, fixed_bits(c.y, F.scale));
+    atomicAdd(slot + 2 * n, fixed_bits(c.z, F.scale));
+    return;
+  }
+  const float v[3] = {c.x, c.y, c.z};
+  for (int k = 0; k < 3; k++) {
+    if (fabsf(v[k]) < F.lim) atomicAdd(slot + k * n, fixed_bits(v[k], F.scale));
+    else if (v[k] != 0.f) atomicAdd(direct + k, v[k]);
   }
 }
 
@@ -144,13 +166,22 @@ constexpr int log2i(int x) { return x <= 1 ? 0 : 1 + log2i(x >> 1); }
 constexpr int BW_HASH_SHIFT = 32 - log2i(BW_SLOTS);
 static_assert((BW_SLOTS & (BW_SLOTS - 1)) == 0 && BW_FLUSH < BW_SLOTS, "table size");
 
+// where a vertex is looked for: its first slot, and the odd step from one to the next
+__device__ inline unsigned first_slot(int32_t v) {
+  unsigned x = (unsigned)v;
+  x = (x ^ (x >> 15)) * 0x85ebca6bu;
+  x = (x ^ (x >> 13)) * 0xc2b2ae35u;
+  return x >> BW_HASH_SHIFT;
+}
+__device__ inline unsigned slot_step(int32_t v) { return ((unsigned)v * 0x9e3779b1u >> 8) | 1u; }
+
 // Each block takes one contiguous run of band cells (band cells follow the
 // tile-ordered bricks, so a run covers a compact piece of surface and shares most
 // of its vertices) in chunks of one cell per thread. Contributions are summed per
-// vertex in an LDS hash table (linear probing) that is added to the global
+// vertex in an LDS hash table (double hashing) that is added to the global
 // gradient once it is more than BW_FLUSH slots full, and at the end: one global
 // add per vertex, axis and flush instead of one per band cell. Probing stops
-// after BW_PROBES slots; such a vertex's contribution goes to the gradient
+// after BW_PROBES slots (BW_FEW where vertices are hardly shared); such a vertex's contribution goes to the gradient
 // directly, so a full table costs time, never correctness.
 __global__ __launch_bounds__(BW_THREADS, BW_WAVES_PER_SIMD) void k_backward(BwdArgs P) {
   __shared__ int s_key[BW_SLOTS];
@@ -191,12 +222,14 @@ __global__ __launch_bounds__(BW_THREADS, BW_WAVES_PER_SIMD) void k_backward(BwdA
   int gexp = 0;
   (void)frexpf(gmax, &gexp);  // gmax < 2^gexp
   const int fx = 40 - gexp;
+  const Fixed F = {ldexp(1.0, fx), ldexpf(1.f, 42 - fx)};
   // the mesh of this thread's first cell; a thread past the end of the band
   // (whose cells are never used) takes the last mesh, so that every descriptor
   // and offset it reads exists
   int m = P.band_off ? find_segment(P.band_off, P.n_meshes + 1, c0 + threadIdx.x) : 0;
   if (m > P.n_meshes - 1) m = P.n_meshes - 1;
   BwMesh M = load_mesh(P, m);
+  int probes = BW_PROBES, before = 0;  // slots taken before the chunk
   for (int64_t base = c0; base < c1; base += BW_THREADS) {
     const int64_t i = base + threadIdx.x;
     const BwCell cur = load_cell(P, i, c1);
@@ -294,21 +327,19 @@ __global__ __launch_bounds__(BW_THREADS, BW_WAVES_PER_SIMD) void k_backward(BwdA
       int old[3];
 #pragma unroll
       for (int k = 0; k < 3; k++) {
-        h[k] = ((unsigned)vid[k] * 2654435761u) >> BW_HASH_SHIFT;
+        h[k] = first_slot(vid[k]);
         old[k] = vid[k] >= 0 ? atomicCAS(&s_key[h[k]], -1, vid[k]) : vid[k];
       }
 #pragma unroll
       for (int k = 0; k < 3; k++) {
         if (vid[k] < 0) continue;
-        for (int probe = 1; old[k] != -1 && old[k] != vid[k] && probe < BW_PROBES; probe++) {
-          h[k] = (h[k] + 1) & (BW_SLOTS - 1);
+        for (int probe = 1; old[k] != -1 && old[k] != vid[k] && probe < probes; probe++) {
+          h[k] = (h[k] + slot_step(vid[k])) & (BW_SLOTS - 1);
           old[k] = atomicCAS(&s_key[h[k]], -1, vid[k]);
         }
         if (old[k] == -1 || old[k] == vid[k]) {
           if (old[k] == -1) n_new++;
-          add_fixed(&s_acc[0][h[k]], con[k].x, fx, P.grad + 3 * (int64_t)vid[k]);
-          add_fixed(&s_acc[1][h[k]], con[k].y, fx, P.grad + 3 * (int64_t)vid[k] + 1);
-          add_fixed(&s_acc[2][h[k]], con[k].z, fx, P.grad + 3 * (int64_t)vid[k] + 2);
+          add_vertex(&s_acc[0][h[k]], BW_SLOTS, con[k], F, P.grad + 3 * (int64_t)vid[k]);
         } else {  // crowded neighbourhood: straight to the gradient
           atomicAdd(P.grad + 3 * (int64_t)vid[k], con[k].x);
           atomicAdd(P.grad + 3 * (int64_t)vid[k] + 1, con[k].y);
@@ -323,6 +354,9 @@ __global__ __launch_bounds__(BW_THREADS, BW_WAVES_PER_SIMD) void k_backward(BwdA
     }
     __syncthreads();
     const int used = s_used;
+    // block-uniform: this chunk's new vertices decide how hard the next one searches
+    probes = used - before > BW_CROWD ? BW_FEW : BW_PROBES;
+    before = used <= BW_FLUSH ? used : 0;
     const bool last = base + BW_THREADS >= c1;
     __syncthreads();  // every thread has read s_used before the next chunk changes it
     if (!last && used <= BW_FLUSH) continue;  // block-uniform: room for another chunk
