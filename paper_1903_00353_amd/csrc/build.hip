@@ -244,6 +244,72 @@ __device__ inline void sort_corners(int32_t* a, int n) {
   }
 }
 
+// Twins around one vertex: corner i's out-edge to N(i) pairs with the one in-edge
+// from P(k) = N(i); matched(k, i) hears of every such pair. Returns the error bits.
+template <class C, class N, class P, class M>
+__device__ inline uint32_t match_fan(int d, C c, N n, P p, M matched, int32_t* twin) {
+  uint32_t e = 0;
+  for (int i = 0; i < d; i++) {
+    const int32_t w = n(i);
+    int32_t match = -1, nmatch = 0;
+    for (int k = 0; k < d; k++) {
+      if (k != i && n(k) == w) e |= ERR_ORIENT;
+      if (p(k) == w) {
+        nmatch++;
+        match = prev_corner(c(k));
+        matched(k, i);
+      }
+    }
+    if (nmatch != 1) e |= ERR_NONMANIFOLD;
+    twin[c(i)] = nmatch == 1 ? match : -1;
+  }
+  return e;
+}
+
+// pseudonormal and tests of a vertex at pv whose corners' next and previous vertices
+// lie at xn(k), xp(k)
+template <class XN, class XP>
+__device__ inline VertexTest test_fan(int d, d3 pv, XN xn, XP xp) {
+  VertexAccum acc;
+  for (int k = 0; k < d; k++) acc.add_face(pv, xn(k), xp(k));
+  VertexTest vt;
+  vt.init(acc.n_alpha);
+  for (int k = 0; k < d; k++) {
+    const d3 p1 = xn(k), p2 = xp(k);
+    vt.neighbour(pv, p1);
+    vt.normal(pv, p1, p2);
+  }
+  return vt;
+}
+
+struct VertexOut {
+  int ruff_mode, saddle_mode, force_both;
+  const int32_t* vert_mesh;
+  const MeshDesc* md;
+  int n_meshes;
+  float absorb;
+  float4* vinfo;
+  uint32_t* vbits;
+};
+
+// class, cone and slack of vertex v of degree d; returns its side bits
+__device__ inline int put_vertex(const VertexOut& O, int64_t v, int d, const VertexTest& vt) {
+  VertexClass cl = vt.finish(O.ruff_mode, O.saddle_mode, O.force_both);
+  if (d == 0) cl.bits = 0;  // isolated vertex: no feature
+  // a nearly flat vertex hands its region to the prisms of its faces (side slack
+  // band * sin(2 theta), theta the cone aperture): see vertex_slack
+  const uint8_t q = O.absorb > 0.f && !O.force_both
+                        ? vertex_slack(cl, O.md[O.n_meshes > 1 ? O.vert_mesh[v] : 0].band, O.absorb)
+                        : 0;
+  if (q) cl.bits = (cl.bits & ~(V_POS | V_NEG)) | V_ABSORBED | ((uint32_t)q << V_SLACK_SHIFT);
+  float cf = (float)cl.cos_t;
+  if ((double)cf > cl.cos_t) cf = nextafterf(cf, -2.f);  // the stored cone contains the exact one
+  O.vinfo[v] = make_float4((float)cl.axis.x, (float)cl.axis.y, (float)cl.axis.z, cf);
+  O.vbits[v] = cl.bits;
+  return (int)(cl.bits & (V_POS | V_NEG));
+}
+static_assert(V_POS == 1u && V_NEG == 2u, "side bits of the class word");
+
 // Per vertex u, over its fan of corners in ascending order (staged in LDS, then
 // replaced there by the positions of the neighbours: each is read once, six loads
 // in flight together, where reading both far corners of every triangle again in
@@ -260,11 +326,7 @@ __device__ inline void sort_corners(int32_t* a, int n) {
 // FP64 arithmetic (4 wavefronts per SIMD, LDS-bound).
 __global__ __launch_bounds__(VK_THREADS) void k_vertex(const float* __restrict__ V, const int32_t* __restrict__ T,
                                                       int64_t nv, const int32_t* __restrict__ off, int32_t* vc,
-                                                      int ruff_mode, int saddle_mode, int force_both,
-                                                      const int32_t* __restrict__ vert_mesh,
-                                                      const MeshDesc* __restrict__ md, int n_meshes, float absorb,
-                                                      int32_t* twin, float4* vinfo, uint32_t* vbits, int32_t* polys,
-                                                      int64_t* stats) {
+                                                      VertexOut O, int32_t* twin, int32_t* polys, int64_t* stats) {
   __shared__ int32_t s_c[VK_MAXD][VK_THREADS], s_n[VK_MAXD][VK_THREADS], s_p[VK_MAXD][VK_THREADS];
   __shared__ int s_polys[VK_THREADS / 64];
   const int t = threadIdx.x;
@@ -329,21 +391,9 @@ __global__ __launch_bounds__(VK_THREADS) void k_vertex(const float* __restrict__
     auto C_ = [&](int k) { return staged ? s_c[k][t] : vc[s0 + k]; };
     auto N_ = [&](int k) { return staged ? s_n[k][t] : T[next_corner(vc[s0 + k])]; };
     auto P_ = [&](int k) { return staged ? s_p[k][t] : T[prev_corner(vc[s0 + k])]; };
-    uint32_t e = 0;
-    for (int i = 0; i < d; i++) {
-      const int32_t w = N_(i);
-      int32_t match = -1, nmatch = 0;
-      for (int k = 0; k < d; k++) {
-        if (k != i && N_(k) == w) e |= ERR_ORIENT;
-        if (P_(k) == w) {
-          nmatch++;
-          match = prev_corner(C_(k));
-          if (staged) place = (place & ~(15ull << (4 * k))) | ((uint64_t)i << (4 * k));
-        }
-      }
-      if (nmatch != 1) e |= ERR_NONMANIFOLD;
-      twin[C_(i)] = nmatch == 1 ? match : -1;
-    }
+    const uint32_t e = match_fan(d, C_, N_, P_, [&](int k, int i) {
+      if (staged) place = (place & ~(15ull << (4 * k))) | ((uint64_t)i << (4 * k));
+    }, twin);
     if (e) atomicOr(err_word(stats), e);
     if (staged && d > 0) {
       // positions of the next vertices in place of the ids (a corner whose previous
@@ -368,28 +418,7 @@ __global__ __launch_bounds__(VK_THREADS) void k_vertex(const float* __restrict__
     };
     auto XN = [&](int k) { return staged ? at(k) : vload_d(V, N_(k)); };
     auto XP = [&](int k) { return staged ? at((int)(place >> (4 * k)) & 15) : vload_d(V, P_(k)); };
-    const d3 pv = vload_d(V, v);
-    VertexAccum acc;
-    for (int k = 0; k < d; k++) acc.add_face(pv, XN(k), XP(k));
-    VertexTest vt;
-    vt.init(acc.n_alpha);
-    for (int k = 0; k < d; k++) {
-      const d3 p1 = XN(k), p2 = XP(k);
-      vt.neighbour(pv, p1);
-      vt.normal(pv, p1, p2);
-    }
-    VertexClass cl = vt.finish(ruff_mode, saddle_mode, force_both);
-    if (d == 0) cl.bits = 0;  // isolated vertex: no feature
-    // a nearly flat vertex hands its region to the prisms of its faces (side slack
-    // band * sin(2 theta), theta the cone aperture): see vertex_slack
-    const uint8_t q =
-        absorb > 0.f && !force_both ? vertex_slack(cl, md[n_meshes > 1 ? vert_mesh[v] : 0].band, absorb) : 0;
-    if (q) cl.bits = (cl.bits & ~(V_POS | V_NEG)) | V_ABSORBED | ((uint32_t)q << V_SLACK_SHIFT);
-    float cf = (float)cl.cos_t;
-    if ((double)cf > cl.cos_t) cf = nextafterf(cf, -2.f);  // the stored cone contains the exact one
-    vinfo[v] = make_float4((float)cl.axis.x, (float)cl.axis.y, (float)cl.axis.z, cf);
-    vbits[v] = cl.bits;
-    sides = (int)(cl.bits & (V_POS | V_NEG));
+    sides = put_vertex(O, v, d, test_fan(d, vload_d(V, v), XN, XP));
   }
   const int n = __popcll(__ballot((sides & 1) != 0)) + __popcll(__ballot((sides & 2) != 0));
   if ((t & 63) == 0) s_polys[t >> 6] = n;
@@ -400,7 +429,128 @@ __global__ __launch_bounds__(VK_THREADS) void k_vertex(const float* __restrict__
     polys[tile] = sum;
   }
 }
-static_assert(V_POS == 1u && V_NEG == 2u, "side bits of the class word");
+// The same for meshes of few vertices: VF_LANES lanes to a vertex, one to a corner, so
+// that a fan takes one angle and one test where a thread takes them one after
+// another, and a mesh of few vertices fills more of the chip. The faces' shares of the
+// pseudonormal are still added in corner order. Vertices of more corners are left to
+// their first lane. polys: cleared by k_inputs. (Build of 642 vertices 43 -> 33 us, 10,242
+// vertices 50 -> 45, 35,000 63 -> 56; from some 100,000 on a lane per vertex keeps the
+// chip busy by itself: 180,000 vertices 108 us and with fans 123, 2.6M 1213 and 1395.)
+constexpr int VF_LANES = 8, VF_THREADS = 256, VF_WAVE = 64 / VF_LANES;
+__global__ __launch_bounds__(VF_THREADS) void k_vertex_fan(const float* __restrict__ V, const int32_t* __restrict__ T,
+                                                          int64_t nv, const int32_t* __restrict__ off, int32_t* vc,
+                                                          VertexOut O, int32_t* twin, int32_t* polys, int64_t* stats) {
+  struct Fan {
+    int32_t c[VF_LANES], n[VF_LANES], p[VF_LANES], at[VF_LANES];  // at: the corner whose next vertex is this one's previous one
+    float x[VF_LANES][3];
+    double share[VF_LANES][4];  // face normal, angle / length (0: no normal)
+  };
+  __shared__ Fan s_fan[VF_THREADS / VF_LANES];
+  const int sub = threadIdx.x & (VF_LANES - 1);
+  const int64_t v = (blockIdx.x * (int64_t)VF_THREADS + threadIdx.x) / VF_LANES;
+  Fan& S = s_fan[threadIdx.x / VF_LANES];
+  const int32_t s0 = v < nv ? off[v] : 0, d = v < nv ? off[v + 1] - s0 : 0;
+  const bool fan = d <= VF_LANES, mine = fan && sub < d;
+  int32_t c = mine ? vc[s0 + sub] : INT32_MAX;
+  // corners in ascending order: each lane's place among the fan's
+  S.c[sub] = c;
+  S.at[sub] = 0;
+  wave_sync_lds();
+  int place = 0;
+#pragma unroll
+  for (int k = 0; k < VF_LANES; k++) place += S.c[k] < c ? 1 : 0;
+  wave_sync_lds();
+  if (mine) S.c[place] = c;
+  wave_sync_lds();
+  c = S.c[sub];
+  if (mine) {
+    const int32_t* row = T + (c - c % 3);
+    const int32_t a0 = row[0], a1 = row[1], a2 = row[2];
+    const int j = c % 3;
+    S.n[sub] = j == 0 ? a1 : (j == 1 ? a2 : a0);
+    S.p[sub] = j == 0 ? a2 : (j == 1 ? a0 : a1);
+  }
+  wave_sync_lds();
+  uint32_t e = 0;
+  const d3 pv = vload_d(V, v < nv ? v : 0);
+  d3 p1 = pv;
+  if (mine) {
+    const int32_t w = S.n[sub];
+    const f3 x = vload_f(V, w);
+    int32_t match = -1, nmatch = 0;
+    for (int k = 0; k < d; k++) {
+      if (k != sub && S.n[k] == w) e |= ERR_ORIENT;
+      if (S.p[k] == w) {
+        nmatch++;
+        match = prev_corner(S.c[k]);
+        S.at[k] = sub;
+      }
+    }
+    if (nmatch != 1) e |= ERR_NONMANIFOLD;
+    twin[c] = nmatch == 1 ? match : -1;
+    S.x[sub][0] = x.x;
+    S.x[sub][1] = x.y;
+    S.x[sub][2] = x.z;
+    p1 = mkd(x.x, x.y, x.z);
+  }
+  if (e) atomicOr(err_word(stats), e);
+  wave_sync_lds();
+  d3 n = mkd(0, 0, 0);
+  double ln = 0;
+  if (mine) {
+    const float* y = S.x[S.at[sub]];
+    const d3 e1 = p1 - pv, e2 = mkd(y[0], y[1], y[2]) - pv;
+    n = cross(e1, e2);
+    ln = len(n);
+    S.share[sub][0] = n.x;
+    S.share[sub][1] = n.y;
+    S.share[sub][2] = n.z;
+    S.share[sub][3] = ln > 0 ? atan2(ln, dot(e1, e2)) / ln : 0.0;
+  }
+  wave_sync_lds();
+  VertexAccum acc;
+  if (fan)
+    for (int k = 0; k < d; k++) {
+      const double q = S.share[k][3];
+      if (q != 0.0) acc.n_alpha = acc.n_alpha + mkd(S.share[k][0], S.share[k][1], S.share[k][2]) * q;
+    }
+  VertexTest vt;
+  vt.init(acc.n_alpha);
+  if (mine) {
+    vt.neighbour(pv, p1);
+    if (ln > 0) {
+      const double q = dot(n, vt.axis) / ln;
+      if (q > 0) vt.cos_t = q < vt.cos_t ? q : vt.cos_t;
+      else vt.nonpos_normal = 1;
+    }
+  }
+  // the lanes' tests together
+#pragma unroll
+  for (int o = 1; o < VF_LANES; o <<= 1) {
+    vt.pos += __shfl_xor(vt.pos, o, 64);
+    vt.neg += __shfl_xor(vt.neg, o, 64);
+    vt.unc += __shfl_xor(vt.unc, o, 64);
+    vt.nonpos_normal |= __shfl_xor(vt.nonpos_normal, o, 64);
+    const double q = __shfl_xor(vt.cos_t, o, 64);
+    vt.cos_t = q < vt.cos_t ? q : vt.cos_t;
+  }
+  int sides = 0;
+  if (sub == 0 && v < nv) {
+    if (!fan) {
+      sort_corners(vc + s0, d);
+      auto C = [&](int k) { return vc[s0 + k]; };
+      auto N = [&](int k) { return T[next_corner(vc[s0 + k])]; };
+      auto P = [&](int k) { return T[prev_corner(vc[s0 + k])]; };
+      const uint32_t err = match_fan(d, C, N, P, [](int, int) {}, twin);
+      if (err) atomicOr(err_word(stats), err);
+      vt = test_fan(d, pv, [&](int k) { return vload_d(V, N(k)); }, [&](int k) { return vload_d(V, P(k)); });
+    }
+    sides = put_vertex(O, v, d, vt);
+  }
+  const int sum = __popcll(__ballot((sides & 1) != 0)) + __popcll(__ballot((sides & 2) != 0));
+  if ((threadIdx.x & 63) == 0 && sum) atomicAdd(&polys[v / VK_THREADS], sum);
+}
+static_assert(VK_THREADS % VF_WAVE == 0, "a wavefront's vertices lie in one tile");
 
 // The extrusion lists: item i (an edge or a vertex) has 0-2 polyhedra, bit 0 of its
 // side mask the outward one (entry i << 1) and bit 1 the inward one ((i << 1) | 1);
@@ -608,6 +758,8 @@ struct InputArgs {
   int32_t* bucket_count; // null: corners are not dealt into buckets
   int64_t* stats;
   int32_t* owned;        // per wavefront of 64 faces
+  int32_t* vpolys;       // per tile of vertices: cleared
+  int64_t vertex_tiles;
   int64_t nv, nf, face_tiles;
   int n_meshes, bucket_shift, buckets;
 };
@@ -717,6 +869,7 @@ __global__ __launch_bounds__(BT) void k_inputs(InputArgs P) {
     }
   }
   const int64_t step = (int64_t)gridDim.x * BT;
+  for (int64_t i = blockIdx.x * (int64_t)BT + t; i < P.vertex_tiles; i += step) P.vpolys[i] = 0;
   for (int64_t i = blockIdx.x * (int64_t)BT + t; i < 3 * P.nv; i += step)
     if (!isfinite(P.V[i])) atomicOr(err_word(P.stats), ERR_NONFINITE);
   if (P.n_meshes > 1)
@@ -1195,6 +1348,7 @@ constexpr int64_t DEAL_BIG = 1 << 23;  // corners from which the long tiles are 
 // Blocks of the input pass: each adds its corner counts to every bucket once at its end
 // (a batch of 64 meshes: build 427 us with 1024, 414 with 2048; 5.2M faces 1212, 1207).
 constexpr int64_t INPUT_BLOCKS = 2048;
+constexpr int64_t VERTEX_FANS = 1 << 16;   // vertices up to which a vertex takes a lane per corner (k_vertex_fan)
 constexpr int64_t INPUT_SHARED = 1 << 17;  // faces up to which a block shares its faces' bricks (k_inputs)
 struct Plan {
   int shift = 0, buckets = 0;
@@ -1525,6 +1679,8 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
     I.bucket_count = pl.buckets > 0 ? zi + z.count : nullptr;
     I.stats = F->d_stats;
     I.owned = owned;
+    I.vpolys = vpolys;
+    I.vertex_tiles = tv <= VERTEX_FANS ? pl.vertex_tiles : 0;
     I.nv = tv;
     I.nf = tf;
     I.face_tiles = pl.face_tiles;
@@ -1593,10 +1749,14 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
     k_bricks<<<(unsigned)(bases.tiles + pl.brick_tiles), BT, 0, s>>>(bricks, bases, 1);
   }
   // 4. per vertex: twins, pseudonormal, class, cone
-  k_vertex<<<(unsigned)pl.vertex_tiles, VK_THREADS, 0, s>>>(verts_d, T, tv, F->vtx_off, F->vtx_corners, o.ruff_mode,
-                                                            o.saddle_mode, o.force_both_sides, F->vert_mesh, F->d_mesh,
-                                                            n_meshes, absorb, twin, F->vinfo, F->vbits, vpolys,
-                                                            F->d_stats);
+  const VertexOut O = {o.ruff_mode, o.saddle_mode, o.force_both_sides, F->vert_mesh, F->d_mesh,
+                       n_meshes,    absorb,        F->vinfo,           F->vbits};
+  if (tv <= VERTEX_FANS)
+    k_vertex_fan<<<grid_1d(tv, VF_THREADS / VF_LANES), VF_THREADS, 0, s>>>(verts_d, T, tv, F->vtx_off, F->vtx_corners, O,
+                                                                           twin, vpolys, F->d_stats);
+  else
+    k_vertex<<<(unsigned)pl.vertex_tiles, VK_THREADS, 0, s>>>(verts_d, T, tv, F->vtx_off, F->vtx_corners, O, twin, vpolys,
+                                                              F->d_stats);
   // 5. edges with their classes and extrusion sides; the vertex list
   {
     EdgeArgs E;

@@ -139,3 +139,21 @@ def test_bricks_marked_by_the_block_and_by_the_thread(mesh, grid):
     # two meshes of few faces: the descriptor is read per face
     assert n_bricks([mesh, meshgen.icosphere(2)], [grid, Grid.unit(24, 2)]) == \
         alone + n_bricks([meshgen.icosphere(2)], [Grid.unit(24, 2)])
+
+
+@pytest.mark.parametrize("n", [3, 6, 7, 8, 9, 12, 13, 40])
+def test_fans_by_lanes_and_by_threads(n):
+    """A mesh of few vertices alone, its fans taken by lanes, and behind so many vertices
+    that a thread takes each: the same band, bit for bit."""
+    many = meshgen.torus(300, 230)
+    v, f = meshgen.bipyramid(n)
+    g = Grid.unit(40, 3)
+    assert v.shape[0] <= 1 << 16 < many[0].shape[0]
+    print("[case] fans", n, flush=True)
+    alone, behind = P.Batch([(v, f)], [g]), P.Batch([many, (v, f)], [Grid.unit(32, 2), g])
+    for b in (alone, behind):
+        b.step()
+        b.check()
+    got, want = alone.band(0), behind.band(1)
+    assert want[0].numel() > 0
+    assert all(torch.equal(x, y) for x, y in zip(got, want))
