@@ -1143,14 +1143,12 @@ __device__ inline void count_vertex_class(uint32_t b, int (&loc)[11]) {
   loc[10] += (b & V_ABSORBED) != 0;
 }
 
-__global__ __launch_bounds__(256) void k_class_stats(const uint8_t* __restrict__ ecls, int64_t ne,
-                                                     const uint32_t* __restrict__ vbits, int64_t nv, int64_t* stats) {
-  __shared__ int h[16];
-  if (threadIdx.x < 16) h[threadIdx.x] = 0;
-  __syncthreads();
-  const int64_t t0 = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, stride = (int64_t)gridDim.x * blockDim.x;
+// the classes of all edges and vertices into the block's h[11]: thread t0 of `stride`
+__device__ inline void count_classes(const uint8_t* __restrict__ ecls, int64_t ne, const uint32_t* __restrict__ vbits,
+                                     int64_t nv, int64_t t0, int64_t stride, int* h) {
   int loc[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   const uint4* e16 = reinterpret_cast<const uint4*>(ecls);
+#pragma unroll 2
   for (int64_t i = t0; i < ne / 16; i += stride) {
     const uint4 x = e16[i];
     const uint32_t wv[4] = {x.x, x.y, x.z, x.w};
@@ -1161,6 +1159,7 @@ __global__ __launch_bounds__(256) void k_class_stats(const uint8_t* __restrict__
   }
   for (int64_t i = ne / 16 * 16 + t0; i < ne; i += stride) count_edge_class(ecls[i], loc);
   const uint4* v4 = reinterpret_cast<const uint4*>(vbits);
+#pragma unroll 2
   for (int64_t i = t0; i < nv / 4; i += stride) {
     const uint4 x = v4[i];
     count_vertex_class(x.x, loc);
@@ -1176,10 +1175,34 @@ __global__ __launch_bounds__(256) void k_class_stats(const uint8_t* __restrict__
     if ((threadIdx.x & 63) == 0 && x) atomicAdd(&h[k], x);
   }
   __syncthreads();
-  const int map[11] = {ST_E_CONVEX, ST_E_CONCAVE, ST_E_FLAT, ST_E_UNKNOWN, ST_V_CONVEX, ST_V_CONCAVE,
-                       ST_V_FLAT,   ST_V_SADDLE,  ST_V_RUFF, ST_E_ABSORBED, ST_V_ABSORBED};
+}
+__constant__ const int CLASS_STAT[11] = {ST_E_CONVEX, ST_E_CONCAVE, ST_E_FLAT, ST_E_UNKNOWN, ST_V_CONVEX, ST_V_CONCAVE,
+                                         ST_V_FLAT,   ST_V_SADDLE,  ST_V_RUFF, ST_E_ABSORBED, ST_V_ABSORBED};
+
+__global__ __launch_bounds__(256) void k_class_stats(const uint8_t* __restrict__ ecls, int64_t ne,
+                                                     const uint32_t* __restrict__ vbits, int64_t nv, int64_t* stats) {
+  __shared__ int h[16];
+  if (threadIdx.x < 16) h[threadIdx.x] = 0;
+  __syncthreads();
+  count_classes(ecls, ne, vbits, nv, blockIdx.x * (int64_t)blockDim.x + threadIdx.x, (int64_t)gridDim.x * blockDim.x, h);
   if (threadIdx.x < 11 && h[threadIdx.x])
-    atomicAdd((unsigned long long*)&stats[map[threadIdx.x]], (unsigned long long)h[threadIdx.x]);
+    atomicAdd((unsigned long long*)&stats[CLASS_STAT[threadIdx.x]], (unsigned long long)h[threadIdx.x]);
+}
+
+// The same by one block, which also writes all the statistics to the host's mirror:
+// one launch where few words are read (at most STATS_ONE_BLOCK of 16 bytes), in place of
+// the count and a copy (synchronised rebuild of 642 vertices 76 -> 71 us).
+constexpr int64_t STATS_ONE_BLOCK = 8192;
+__global__ __launch_bounds__(1024) void k_stats_out(const uint8_t* __restrict__ ecls, int64_t ne,
+                                                    const uint32_t* __restrict__ vbits, int64_t nv, int64_t* stats,
+                                                    int64_t* host) {
+  __shared__ int h[16];
+  if (threadIdx.x < 16) h[threadIdx.x] = 0;
+  __syncthreads();
+  count_classes(ecls, ne, vbits, nv, threadIdx.x, 1024, h);
+  if (threadIdx.x < 11) stats[CLASS_STAT[threadIdx.x]] = h[threadIdx.x];
+  __syncthreads();
+  if (threadIdx.x < ST_COUNT) host[threadIdx.x] = stats[threadIdx.x];
 }
 
 struct ListArgs {
@@ -1820,13 +1843,21 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
 extern "C" int csc_features_sync(csc_features* F, void* stream) {
   if (!F || !F->built || !F->h_stats) return CSC_INVALID_ARG;
   hipStream_t s = (hipStream_t)stream;
-  if (!F->classes_counted) {  // once per build: the classes stay until the next one
-    const int64_t items = (F->ne / 16 > F->nv / 4 ? F->ne / 16 : F->nv / 4) + 1;
-    k_class_stats<<<grid_1d(items < 1024 * 256 ? items : 1024 * 256, 256), 256, 0, s>>>(F->edge_cls, F->ne,
-                                                                                       F->vbits, F->nv, F->d_stats);
-    F->classes_counted = true;
+  const int64_t items = (F->ne / 16 > F->nv / 4 ? F->ne / 16 : F->nv / 4) + 1;
+  hipError_t he = hipSuccess;
+  if (!F->classes_counted && items <= STATS_ONE_BLOCK) {
+    void* host = nullptr;
+    he = hipHostGetDevicePointer(&host, F->h_stats, 0);
+    if (he == hipSuccess)
+      k_stats_out<<<1, 1024, 0, s>>>(F->edge_cls, F->ne, F->vbits, F->nv, F->d_stats, (int64_t*)host);
+    if (he == hipSuccess) he = hipGetLastError();
+  } else {
+    if (!F->classes_counted)  // once per build: the classes stay until the next one
+      k_class_stats<<<grid_1d(items < 1024 * 256 ? items : 1024 * 256, 256), 256, 0, s>>>(F->edge_cls, F->ne, F->vbits,
+                                                                                         F->nv, F->d_stats);
+    he = hipMemcpyAsync(F->h_stats, F->d_stats, sizeof(int64_t) * ST_COUNT, hipMemcpyDeviceToHost, s);
   }
-  hipError_t he = hipMemcpyAsync(F->h_stats, F->d_stats, sizeof(int64_t) * ST_COUNT, hipMemcpyDeviceToHost, s);
+  F->classes_counted = true;
   if (he == hipSuccess) he = hipStreamSynchronize(s);
   if (he != hipSuccess) return fail_hip(he);
   const int64_t* st = F->h_stats;
