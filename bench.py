@@ -361,9 +361,8 @@ def stage_averages(fn, steps):
 def forward_span(steps, build, scan, finish):
     """ms of the forward scan as the timed step runs it: HIP events on the
     library's stream (torch's current stream) around the scan-and-sign call of
-    `steps` eager steps without stage timing, so that a batch's edge and vertex
-    kinds run beside its faces on the side stream as in the captured graph
-    (the call joins that stream before it returns)."""
+    `steps` eager steps without stage timing, so that the kinds share their
+    launches as in the captured graph."""
     import statistics
 
     import torch
@@ -817,7 +816,7 @@ def main():
     ap.add_argument("--small-rows", help="fixed schedule faces,edges,vertices instead of the autotuned one")
     ap.add_argument("--scan-grid", type=int, default=2, help="with --small-rows: scan_grid (1, 2, 3)")
     ap.add_argument("--absorb", type=float, default=0.05, help="with --small-rows: absorb_cells (negative: off)")
-    ap.add_argument("--geom-blocks", type=int, default=0, help="with --small-rows: geom_blocks (0: one thread per face)")
+    ap.add_argument("--geom-blocks", type=int, default=0, help="with --small-rows: geom_blocks (0: the library's own grid)")
     ap.add_argument("--face-order", action="store_true", help="single mesh: scan the faces in spatial order")
     ap.add_argument("--input-order", action="store_true", help="batch64: scan the faces in input order")
     ap.add_argument("--timed-only", action="store_true",

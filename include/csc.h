@@ -96,12 +96,10 @@ typedef struct csc_options {
                                striding over the groups of 64; 3 that grid taking the groups from a
                                device counter in the order the wavefronts ask. 0 = default (2). Only
                                the speed depends on it (the autotuner in the binding picks one). */
-  int32_t geom_blocks;      /* schedule of the build's face pass (face records and band bricks), which runs
-                               beside the corner sort: 0 (default) one thread per face; n > 0 a grid of
-                               at most n blocks of 256 striding over the faces, which leaves the sort
-                               compute units of its own (a batch of many small meshes gains, one large
-                               mesh loses). Only the speed depends on it (the binding's autotuner picks
-                               it for a batch). */
+  int32_t geom_blocks;      /* schedule of the build's input pass (checks, face records, band bricks): a
+                               grid of at most n blocks of 256 striding over the faces; 0 (default) the
+                               library's own bound of 2048. Only the speed depends on it (the
+                               binding's autotuner picks it for a batch). */
   int32_t keep_store_empty; /* 1: the caller keeps the key store of the scan workspace empty between
                                scans: the workspace is filled with 0xFF bytes once, before its first
                                scan, and used for nothing else; every scan then skips filling the
@@ -160,9 +158,9 @@ int csc_build_features(const float* verts_d, int64_t nv, const int32_t* tris_d, 
  *     grids and options, so that nothing is allocated or copied from the host:
  *     the call can then be captured into a graph. Errors are read later by
  *     csc_features_sync.
- *   CSC_BUILD_GRAPH_SAFE: accepted for compatibility. Every build now groups
- *     corners with the library's own radix sort (kernels only, no memset
- *     nodes), so every build is safe to capture.
+ *   CSC_BUILD_GRAPH_SAFE: accepted for compatibility. Every build groups
+ *     corners with the library's own kernels (no memset nodes), so every build
+ *     is safe to capture.
  * Errors as csc_build_features.
  */
 #define CSC_BUILD_NO_SYNC 1
@@ -246,10 +244,11 @@ int csc_scan_convert(const csc_features* f, void* workspace_d, size_t ws_bytes, 
  *
  * soup_d: float32 [nf][3][3] device. verts_d: float32 [3*nf][3] device (room for
  * every corner being distinct); the first *nv rows are written. tris_d: int32
- * [nf][3] device. nv: host pointer receiving the vertex count. Allocates
- * temporaries (14 bytes per corner) with
- * hipMallocAsync on `stream` and synchronises it before returning. Triangles that collapse (two corners at
- * one position) are not removed here; csc_build_features rejects them.
+ * [nf][3] device. nv: host pointer receiving the vertex count. Takes its
+ * temporaries (14 bytes per corner) from the memory that the library keeps (see
+ * csc_features_free), or allocates them, and synchronises `stream` before returning.
+ * Triangles that collapse (two corners at one position) are not removed here;
+ * csc_build_features rejects them.
  * Errors: INVALID_ARG (null, nf <= 0, 3*nf >= 2^31, non-finite coordinate),
  * OUT_OF_MEMORY, UNSUPPORTED_DEVICE, HIP_ERROR.
  */
@@ -383,15 +382,15 @@ int csc_fadd_rate(float* grad_d, int64_t nv, int64_t n, void* stream);
  * 0 build_features, 1 init_keys, 2 scan_faces, 3 scan_edges, 4 scan_vertices,
  * 5 brick_count, 6 sign, 7 backward, 8 scan_faces_big, 9 scan_edges_big,
  * 10 scan_vertices_big, 11 interior_fill, 12 scan_wide; stages 2-4 time the
- * one-thread-per-polyhedron launch of each kind, 8-10 the wave-per-polyhedron
- * launch over its overflow list, 12 the three launches (one per kind) over the
+ * one-thread-per-polyhedron launch of each kind, 8-10 the launch over its overflow
+ * list, 12 the three launches (one per kind) over the
  * polyhedra whose box exceeds 32 cells along an axis, whose distances are taken
  * in FP64; every other stage one launch or the whole build). While enabled, every call records a pair
  * of events around each stage; csc_timing_read waits for the recorded events and
  * returns the accumulated milliseconds and call counts of the first n stages.
- * A batch's scan otherwise runs the edge and vertex kinds on a second stream,
- * beside the faces; while timing is enabled the kinds run one after another, so
- * that each stage times one kernel running alone.
+ * The scan otherwise runs the three kinds in one launch of either pass; while timing
+ * is enabled the kinds run one after another, so that each stage times one kernel
+ * running alone.
  * Process-wide; not meant for concurrent callers.
  */
 int csc_timing_enable(int on);

@@ -9,16 +9,15 @@ The scan conversion has three schedule choices, none of which changes a value:
     persistent grid taking groups from a device counter);
   * the largest side slack a face prism takes on to absorb the extrusions of
     nearly flat edges and vertices (``absorb_cells``; negative: none absorbed);
-  * for a batch, the grid of the build's face pass, which runs beside the
-    corner sort (``geom_blocks``: 0 one thread per face, or a capped grid that
-    leaves the sort compute units of its own).
+  * for a batch, the grid of the build's input pass (``geom_blocks``: 0 the
+    library's own bound, or a smaller grid striding over the faces).
 The tuner times candidates on the caller's own workload with the library's stage
 events (HIP events on the working stream): first ``small_rows`` per kind (each
 kind's one-lane launch plus its overflow launch), then ``scan_grid`` and
 ``absorb_cells`` one after the other on the time of the whole forward pass
-(scans and sign; for a batch, whose edge and vertex kinds run on a second
-stream beside the faces, so that stage times do not add up, on the time of
-its whole step, on which a batch's rows per kind are refined as well), then
+(scans and sign; for a batch, whose kinds share one launch, so that stage times
+do not add up, on the time of its whole step, on which a batch's rows per kind
+are refined as well), then
 (batches) ``geom_blocks`` on the build's time. It caches
 the choice as JSON keyed by the device and the workload's shape.
 """
@@ -133,7 +132,7 @@ def _search(measure, base, reps, build=False):
         timings[f"rows={c}"] = measure(_with(base, rows=(c, c, c)), reps)
     rows = tuple(min(CANDIDATES, key=lambda c: _kind_times(timings[f"rows={c}"])[k]) for k in range(3))
     if build:
-        # a batch: its kinds overlap on two streams, so each kind's rows are
+        # a batch: its kinds share one launch, so each kind's rows are
         # refined, one kind after the other, on the whole step
         rows = list(rows)
         for k in range(3):

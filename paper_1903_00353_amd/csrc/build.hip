@@ -14,9 +14,10 @@
 // blocks that need what lies before them, and the bricks and edges are numbered by
 // spare blocks of k_deal and k_bucket, so that no launch only scans. (Coarse sums kept
 // by atomics were slower: atomics on one cache line take 6 to 10 ns each, one after
-// another, 34 us for the 5,625 wavefronts of 360,000 faces.) With a radix sort, separate scans and a second stream the build took 25 launches: a
-// 20,480-face sphere 110 us (now 54), 360,000 faces 204 (107), a batch of 64 meshes
-// with 1.75M faces 509 (406), 5.2M faces 1578 (1207).
+// another, 34 us for the 5,625 wavefronts of 360,000 faces.) With a radix sort,
+// separate scans and a second stream the build took 25 launches: a 20,480-face sphere
+// 110 us (now 45), 360,000 faces 204 (108), a batch of 64 meshes with 1.75M faces 509
+// (405), 5.2M faces 1578 (1213).
 #include <string.h>
 
 #include <new>
