@@ -34,8 +34,8 @@ WORKLOADS = {
     "icosphere5_jitter_256": (2, "jittered icosphere L5: 20,480 triangles, 256^3 grid, band 4, fwd+bwd"),
 }
 PEAK_HBM_GBS = 8000.0
-# stages timed around exactly one kernel launch, and that kernel (a trailing comma: any
-# instance of the template with these first arguments, a single mesh's or a batch's)
+# stages timed around exactly one kernel launch, and that kernel (a trailing comma: the
+# single-mesh or the batch instance of the template, whose last argument is for logging)
 KERNEL_SYMBOL = {"init_keys": "k_init_keys", "scan_faces": "k_scan_small<1,",
                  "scan_edges": "k_scan_small<2,", "scan_vertices": "k_scan_small<4,",
                  "scan_faces_big": "k_scan_over<1,", "scan_edges_big": "k_scan_over<4,",
@@ -593,8 +593,8 @@ def summarize_counters(args):
     for stage, sym in symbol_of.items():
         # a plain kernel name, or any instance of a template of that name (the sign
         # pass: k_sign<true> when the batch keeps its store empty, else k_sign<false>)
-        names = sorted((k for k in fetch if (sym in k if sym.endswith(",") else (sym + "(") in k or (sym + "<") in k)),
-                       key=lambda k: -write.get(k, 0.0))
+        ends = (" true, false>", " false, false>") if sym.endswith(",") else ("(", "<")
+        names = sorted((k for k in fetch if any(sym + e in k for e in ends)), key=lambda k: -write.get(k, 0.0))
         if not names:
             continue
         k = names[0]
