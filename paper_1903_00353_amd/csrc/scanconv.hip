@@ -1241,13 +1241,15 @@ struct SignArgs {
 };
 
 // mesh-local feature id of a global one
-__device__ inline int32_t local_id(const SignArgs& P, const MeshDesc& G, int32_t id) {
+template <class M>
+__device__ inline int32_t local_id(const SignArgs& P, const M& G, int32_t id) {
   return id < P.nf ? id - G.f_off
                    : (id < P.nf + P.ne ? G.nf + (int32_t)(id - P.nf - G.e_off)
                                        : G.nf + G.ne + (int32_t)(id - P.nf - P.ne - G.v_off));
 }
 
-__device__ inline void put_cell(const SignArgs& P, const MeshDesc& G, int64_t out, float sd, int32_t local, int i,
+template <class M>
+__device__ inline void put_cell(const SignArgs& P, const M& G, int64_t out, float sd, int32_t local, int i,
                                 int j, int k) {
   const int32_t lin = i + G.n[0] * (j + G.n[1] * k);
   P.sdf[out] = sd;
@@ -1263,7 +1265,8 @@ __device__ inline f3 xyz(float4 a) { return mk(a.x, a.y, a.z); }
 // recompute the closest point and take the pseudonormal of the feature holding
 // it (only for polyhedra of at most WIDE_CELLS: wide ones decide every sign in
 // the scan, in FP64)
-__device__ inline void sign_open(const SignArgs& P, const MeshDesc& G, unsigned long long key, int i, int j,
+template <class M>
+__device__ inline void sign_open(const SignArgs& P, const M& G, unsigned long long key, int i, int j,
                                        int k, int64_t out) {
   const float d = __uint_as_float((uint32_t)(key >> 32));
   const int32_t id = (int32_t)((uint32_t)key & ID_MASK);
@@ -1305,26 +1308,39 @@ __device__ inline void sign_open(const SignArgs& P, const MeshDesc& G, unsigned 
 // in-brick position order. Most keys carry their sign from the scan; the rest
 // (SIGN_OPEN) are finished after the brick's decided cells. With RESET each set
 // key is stored back as empty once its cell is written, so that the store is
-// empty for the next scan without a pass of its own (its stores take the pass
-// from 70 to 74 registers, hence a kernel of its own).
+// empty for the next scan without a pass of its own.
+// Bound by HBM and by the wait for it: a wavefront takes one brick and ends, since the
+// loads of a next one would wait for this one's stores (vector memory operations
+// complete in order), and the brick's place and mesh come through the scalar cache,
+// which leaves 54 registers (58 with RESET) and 8 wavefronts per SIMD (70 and 74 with the
+// descriptor in vector registers: 7 and 6). 64 meshes (75,000 bricks, 0.62 GB) 190 ->
+// 130 us, 5.2M faces (53,000 bricks) 76 -> 55.
+constexpr unsigned SIGN_BLOCKS = 1 << 16;  // a store of many more bricks than are set would mostly start empty blocks
 template <bool RESET>
 __global__ __launch_bounds__(256) void k_sign(SignArgs P) {
   const int lane = threadIdx.x & 63;
   const int64_t nb = P.stats[ST_NBRICKS] < P.cap ? P.stats[ST_NBRICKS] : P.cap;
   const int64_t nw = (int64_t)gridDim.x * (blockDim.x >> 6);
-  for (int64_t slot = blockIdx.x * (int64_t)(blockDim.x >> 6) + (threadIdx.x >> 6); slot < nb; slot += nw) {
+  for (int64_t slot = blockIdx.x * (int64_t)(blockDim.x >> 6) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+       slot < nb; slot += nw) {
     unsigned long long* kp = P.keys + slot * BRICK_CELLS + lane;
     unsigned long long key[BRICK_ROUNDS];
 #pragma unroll
     for (int r = 0; r < BRICK_ROUNDS; r++) key[r] = kp[64 * r];
-    const MeshDesc& G = P.md[P.brick_mesh[slot]];
+    // the brick's place and mesh through the scalar cache
+    using Const = const __attribute__((address_space(4))) int32_t;
+    MeshConst& G = ((MeshConst*)(uint64_t)(uintptr_t)P.md)[((Const*)(uint64_t)(uintptr_t)P.brick_mesh)[slot]];
     int bx, by, bz;
-    brick_coords(G, P.brick_list[slot], bx, by, bz);
+    const int64_t in_mesh = (int64_t)((Const*)(uint64_t)(uintptr_t)P.brick_list)[slot] - G.brick_base, tile = in_mesh >> 6;
+    const int in_tile = (int)(in_mesh & 63), nt0 = G.nt[0], nt1 = G.nt[1];
+    bx = ((int)tile % nt0) * 4 + (in_tile & 3);
+    by = ((int)tile / nt0 % nt1) * 4 + ((in_tile >> 2) & 3);
+    bz = (int)tile / (nt0 * nt1) * 4 + (in_tile >> 4);
     // cell of round r: in-brick position lane + 64 r
     auto cell_i = [&](int r) { int i, j, k; brick_cell(lane + 64 * r, i, j, k); return bx * BRICK + i; };
     auto cell_j = [&](int r) { int i, j, k; brick_cell(lane + 64 * r, i, j, k); return by * BRICK + j; };
     auto cell_k = [&](int r) { int i, j, k; brick_cell(lane + 64 * r, i, j, k); return bz * BRICK + k; };
-    const int64_t ob = P.boff[slot];
+    const int64_t ob = ((Const*)(uint64_t)(uintptr_t)P.boff)[slot];
     int before = 0;
     unsigned open_bits = 0;
     unsigned long long open_pos = 0;  // 9-bit band ranks within the brick of open cells r = 0..6
@@ -1657,14 +1673,12 @@ int scan_convert_impl(const csc_features* f, void* workspace_d, size_t ws_bytes,
     S.cap = cap;
     S.nf = f->nf;
     S.ne = f->ne;
-    // at most the blocks resident at once (the persistent loop strides over the bricks)
-    const unsigned need = grid_1d(cap, 4);
+    // a wavefront per brick, up to SIGN_BLOCKS (and striding from there on)
+    const unsigned need = grid_1d(cap, 4), blocks = need < SIGN_BLOCKS ? need : SIGN_BLOCKS;
     if (f->opt.keep_store_empty) {
-      static const unsigned resident = resident_blocks(k_sign<true>, 256);
-      k_sign<true><<<need < resident ? need : resident, 256, 0, s>>>(S);
+      k_sign<true><<<blocks, 256, 0, s>>>(S);
     } else {
-      static const unsigned resident = resident_blocks(k_sign<false>, 256);
-      k_sign<false><<<need < resident ? need : resident, 256, 0, s>>>(S);
+      k_sign<false><<<blocks, 256, 0, s>>>(S);
     }
   }
   e = hipGetLastError();
