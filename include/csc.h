@@ -98,7 +98,7 @@ typedef struct csc_options {
                                the speed depends on it (the autotuner in the binding picks one). */
   int32_t geom_blocks;      /* schedule of the build's input pass (checks, face records, band bricks): a
                                grid of at most n blocks of 256 striding over the faces; 0 (default) the
-                               library's own bound of 2048. Only the speed depends on it (the
+                               library's own bound of 32768. Only the speed depends on it (the
                                binding's autotuner picks it for a batch). */
   int32_t keep_store_empty; /* 1: the caller keeps the key store of the scan workspace empty between
                                scans: the workspace is filled with 0xFF bytes once, before its first

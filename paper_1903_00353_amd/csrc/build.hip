@@ -765,7 +765,7 @@ struct InputArgs {
   int n_meshes, bucket_shift, buckets;
 };
 
-// The input passes in one launch, a persistent grid striding over tiles of FACES faces:
+// The input passes in one launch, a block per tile of FACES faces (striding from INPUT_BLOCKS on):
 // finite coordinates; of each face its mesh, index range and repeated-corner
 // checks, global indices (a face with a bad index is replaced by three copies of its
 // mesh's first vertex so that every later access stays in bounds; the build then
@@ -1369,9 +1369,11 @@ enum {
 // 406 and 415, 1.1M corners 107 and 129.
 constexpr int DEAL_TH = 256, DEAL_ITEMS = 8, DEAL_BIG_TH = 1024, DEAL_BIG_ITEMS = 16;
 constexpr int64_t DEAL_BIG = 1 << 23;  // corners from which the long tiles are used
-// Blocks of the input pass: each adds its corner counts to every bucket once at its end
-// (a batch of 64 meshes: build 427 us with 1024, 414 with 2048; 5.2M faces 1212, 1207).
-constexpr int64_t INPUT_BLOCKS = 2048;
+// Blocks of the input pass: a tile each up to 8.4M faces. A block adds its corner
+// counts to every bucket once at its end, which more blocks do more often, but the loads of
+// a block's next tile would wait for its last one's stores (a batch of 64 meshes:
+// build 406 us with 2048 blocks, 397 with a tile each; 5.2M faces 1210, 1188).
+constexpr int64_t INPUT_BLOCKS = 32768;
 constexpr int64_t VERTEX_FANS = 1 << 16;   // vertices up to which a vertex takes a lane per corner (k_vertex_fan)
 constexpr int64_t INPUT_SHARED = 1 << 17;  // faces up to which a block shares its faces' bricks (k_inputs)
 struct Plan {
