@@ -17,7 +17,7 @@
 // another, 34 us for the 5,625 wavefronts of 360,000 faces.) With a radix sort,
 // separate scans and a second stream the build took 25 launches: a 20,480-face sphere
 // 110 us (now 45), 360,000 faces 204 (108), a batch of 64 meshes with 1.75M faces 509
-// (405), 5.2M faces 1578 (1213).
+// (397), 5.2M faces 1578 (1188).
 #include <string.h>
 
 #include <new>

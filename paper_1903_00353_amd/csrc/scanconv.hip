@@ -1313,8 +1313,8 @@ __device__ inline void sign_open(const SignArgs& P, const M& G, unsigned long lo
 // loads of a next one would wait for this one's stores (vector memory operations
 // complete in order), and the brick's place and mesh come through the scalar cache,
 // which leaves 54 registers (58 with RESET) and 8 wavefronts per SIMD (70 and 74 with the
-// descriptor in vector registers: 7 and 6). 64 meshes (75,000 bricks, 0.62 GB) 190 ->
-// 130 us, 5.2M faces (53,000 bricks) 76 -> 55.
+// descriptor in vector registers: 7 and 6). 64 meshes (13M cells, 0.60 GB with the reset)
+// 162 -> 99 us, 6.1 TB/s; 5.2M faces (9.8M cells, 0.35 GB) 76 -> 55 us, 6.4 TB/s.
 constexpr unsigned SIGN_BLOCKS = 1 << 16;  // a store of many more bricks than are set would mostly start empty blocks
 template <bool RESET>
 __global__ __launch_bounds__(256) void k_sign(SignArgs P) {
