@@ -1563,12 +1563,12 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
     else F->built = F->synced = false;
     return code;
   };
-  if (F->face_order && F->face_order_n != tf) {  // an order of another face count is dropped
-    (void)hipStreamSynchronize(s);
-    (void)hipFree(F->face_order);
-    F->face_order = nullptr;
-    F->face_order_n = 0;
-  }
+#define CK(x)                                        \
+  do {                                               \
+    hipError_t e_ = (x);                             \
+    if (e_ != hipSuccess) return fail(fail_hip(e_)); \
+  } while (0)
+
   const Plan pl = plan(tv, tf, tb);
   int sort_bits = 1;
   while (sort_bits < 31 && ((int64_t)1 << sort_bits) < tv) sort_bits++;
@@ -1578,6 +1578,22 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
   const bool config_changed = fresh || !same_config(F, mesh, o) || F->arena_bytes < L.total || F->nv != tv ||
                               F->nf != tf;
   hipError_t he;
+  if (config_changed) {
+    // Descriptors and offset tables change only with the configuration, never inside a
+    // captured replay of the same batch: refused there, before anything of the handle is
+    // touched. From here on the handle holds the tables of no configuration, until the
+    // launches below are known to be queued.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    CK(hipStreamIsCapturing(s, &cap));
+    if (cap != hipStreamCaptureStatusNone) CK(hipErrorStreamCaptureUnsupported);
+    F->mesh.clear();
+  }
+  if (F->face_order && F->face_order_n != tf) {  // an order of another face count is dropped
+    (void)hipStreamSynchronize(s);
+    (void)hipFree(F->face_order);
+    F->face_order = nullptr;
+    F->face_order_n = 0;
+  }
   if (F->arena_bytes < L.total) {
     if (F->arena) {
       (void)hipStreamSynchronize(s);
@@ -1630,21 +1646,8 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
   F->fabsorbed = (uint8_t*)(A + L.off[L_FABS]);
   F->built = F->synced = false;
 
-#define CK(x)                                        \
-  do {                                               \
-    hipError_t e_ = (x);                             \
-    if (e_ != hipSuccess) return fail(fail_hip(e_)); \
-  } while (0)
-
   MeshTables M;
   M.n = 0;
-  if (config_changed) {
-    // descriptors and offset tables change only with the configuration (never
-    // inside a captured replay of the same batch)
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    CK(hipStreamIsCapturing(s, &cap));
-    if (cap != hipStreamCaptureStatusNone) CK(hipErrorStreamCaptureUnsupported);
-  }
   if (config_changed && n_meshes <= TABLE_MESHES) {
     for (int m = 0; m < n_meshes; m++) M.m[m] = mesh[m];
     M.md = F->d_mesh;
@@ -1668,7 +1671,6 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
     CK(hipMemcpy(F->brick_base, tabs.data() + 2 * (n_meshes + 1), sizeof(int32_t) * (n_meshes + 1),
                  hipMemcpyHostToDevice));
   }
-  if (config_changed) F->mesh = mesh;
 
   StageTimer timer(TS_BUILD, s);
   const int64_t nh = 3 * tf, ne = te;
@@ -1835,6 +1837,7 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
   F->classes_counted = false;
   CK(hipGetLastError());
 #undef CK
+  if (config_changed) F->mesh.swap(mesh);
   F->built = true;
   if (no_sync) return CSC_OK;
   int rc = csc_features_sync(F, stream);
