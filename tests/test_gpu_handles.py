@@ -1,4 +1,6 @@
 """Handles while a graph is being captured: what is refused there and what is not."""
+import threading
+
 import pytest
 
 import meshgen
@@ -13,10 +15,6 @@ import paper_1903_00353_amd as P  # noqa: E402
 def mesh(level):
     v, t = meshgen.icosphere(level)
     return torch.from_numpy(v).cuda(), torch.from_numpy(t).cuda()
-
-
-def same(a, b):
-    return all(torch.equal(x, y) for x, y in zip((a.sdf, a.feat, a.cell), (b.sdf, b.feat, b.cell)))
 
 
 @pytest.mark.parametrize("meshes", [1, 5])
@@ -55,3 +53,32 @@ def test_a_changed_configuration_is_refused_under_capture(meshes):
 
     assert f.info() == kept.info()
     assert all(torch.equal(a, b) for a, b in zip(scan(f), scan(kept)))
+
+
+@pytest.mark.parametrize("thread", [False, True])
+@pytest.mark.parametrize("mode", ["relaxed", "thread_local", "global"])
+def test_a_handle_is_freed_during_a_capture(mode, thread):
+    """By the capturing thread or by another: the capture ends well, and a handle that
+    takes the memory over gives its field."""
+    verts, tris = mesh(3)
+    f = P.csc_build_features(verts, tris, Grid.unit(32, 3))
+    want = P.csc_scan_convert(f)
+    x = torch.ones(100, device="cuda")
+    torch.cuda.synchronize()
+    print("[case] free during capture", mode, thread, flush=True)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, capture_error_mode=mode):
+        y = x * 2
+        if thread:
+            t = threading.Thread(target=f.free)
+            t.start()
+            t.join()
+        else:
+            f.free()
+        z = y + 1
+    for _ in range(3):
+        z.zero_()
+        g.replay()
+        assert z[0].item() == 3.0
+    got = P.csc_scan_convert(P.csc_build_features(verts, tris, Grid.unit(32, 3)))
+    assert all(torch.equal(a, b) for a, b in zip((got.sdf, got.feat, got.cell), (want.sdf, want.feat, want.cell)))

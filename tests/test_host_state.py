@@ -82,3 +82,18 @@ def test_a_build_that_runs_out_of_memory_writes_its_tables_the_next_time(sim):
     assert sim.build(16, h)[0] == OK
     assert sim.uploads.value >= 4
     sim.lib.csc_features_free(h)
+
+
+def test_a_handle_freed_during_a_capture_waits_for_the_device_without_ending_it(sim):
+    """hipDeviceSynchronize would end the capture (of any thread); the handle's memory
+    serves the next one all the same."""
+    code, h = sim.build(16)
+    assert code == OK
+    sim.capturing.value = 1
+    sim.lib.csc_features_free(h)
+    sim.capturing.value = 0
+    assert sim.device_waits.value == 0
+    used = sim.used.value
+    code, h = sim.build(16)
+    assert code == OK and sim.used.value == used
+    sim.lib.csc_features_free(h)
