@@ -1115,7 +1115,7 @@ __global__ void k_zero_u64(unsigned long long* p, int n) {
 }
 
 // every key of the allocated bricks (device count, capped) set to empty, 16 bytes per
-// store (keys starts on a 256-byte boundary); block 0 also clears the zn counters at
+// store where the caller's workspace allows it; block 0 also clears the zn counters at
 // zero
 __global__ __launch_bounds__(256) void k_init_keys(unsigned long long* keys, const int64_t* __restrict__ stats,
                                                    int64_t cap, unsigned long long* zero, int zn) {
@@ -1123,9 +1123,13 @@ __global__ __launch_bounds__(256) void k_init_keys(unsigned long long* keys, con
     for (int i = threadIdx.x; i < zn; i += blockDim.x) zero[i] = 0;
   const int64_t nb = stats[ST_NBRICKS] < cap ? stats[ST_NBRICKS] : cap;
   const int64_t n = nb * (BRICK_CELLS / 2);
-  ulonglong2* k2 = reinterpret_cast<ulonglong2*>(keys);
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    k2[i] = make_ulonglong2(EMPTY_KEY, EMPTY_KEY);
+  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+  if (((uintptr_t)keys & 15) == 0) {
+    ulonglong2* k2 = reinterpret_cast<ulonglong2*>(keys);
+    for (int64_t i = t; i < n; i += step) k2[i] = make_ulonglong2(EMPTY_KEY, EMPTY_KEY);
+  } else {
+    for (int64_t i = t; i < 2 * n; i += step) keys[i] = EMPTY_KEY;
+  }
 }
 
 // p[0..n) set to v; 16 bytes per store where p allows it

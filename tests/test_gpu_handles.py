@@ -82,3 +82,17 @@ def test_a_handle_is_freed_during_a_capture(mode, thread):
         assert z[0].item() == 3.0
     got = P.csc_scan_convert(P.csc_build_features(verts, tris, Grid.unit(32, 3)))
     assert all(torch.equal(a, b) for a, b in zip((got.sdf, got.feat, got.cell), (want.sdf, want.feat, want.cell)))
+
+
+@pytest.mark.parametrize("level,n", [(3, 48), (5, 440)])  # one-block and general scan of the store's counts
+def test_a_workspace_on_an_8_byte_boundary(level, n):
+    """The keys are 8 bytes wide and need no more: the same field as from the allocator's
+    own boundary."""
+    verts, tris = mesh(level)
+    f = P.csc_build_features(verts, tris, Grid.unit(n, 12))
+    nbytes, _ = P.csc_scan_convert_workspace(f)
+    print("[case] workspace at 8 bytes", level, n, flush=True)
+    want = P.csc_scan_convert(f, torch.full((nbytes,), 1, dtype=torch.uint8, device="cuda"))
+    got = P.csc_scan_convert(f, torch.full((nbytes + 8,), 1, dtype=torch.uint8, device="cuda")[8:])
+    assert want.n_band > 0
+    assert all(torch.equal(a, b) for a, b in zip((got.sdf, got.feat, got.cell), (want.sdf, want.feat, want.cell)))
