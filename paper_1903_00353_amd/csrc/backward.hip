@@ -104,20 +104,22 @@ __device__ inline void seg_step(int run, f3 (&con)[3]) {
 }
 
 // The pass is bound by the latency of its loads and of the table's LDS round
-// trips, so occupancy comes first: a 16 KB table per block of 256 lets 8 blocks
-// share a CU, and the register budget is held to 64 for 8 wavefronts per SIMD (6
+// trips, so occupancy comes first: a table of 20 KB per block of 256 lets 8 blocks
+// share a CU's 160 KB, and the register budget is held to 64 for 8 wavefronts per SIMD (6
 // wavefronts and no spills: 64 meshes 490 us against 445).
-// What the trips cost is the search for a slot in a crowded table: double hashing, a
-// flush at 224 slots, and few probes where the last chunk brought so many new
-// vertices that the table shares little between its cells: 64 meshes (15.7M cells) 445
-// -> 331 us, 5.2M faces (9.8M cells) 394 -> 381; every chunk with few probes
-// 508 there, with up to 16 always 446 and 370.
+// What the trips cost is the search for a slot in a crowded table: as many slots as the
+// LDS holds, double hashing, and the three vertices of a cell probed together, so that a
+// round of probes waits once. 64 meshes (15.7M cells, 27M terms) 447 us with 512 slots
+// and linear probing of one vertex after another, 397 with 727 slots, 355 probed together;
+// 5.2M faces (9.8M cells) 396, 360, 355. How many terms find no slot and are rounded one by one
+// (0.11 and 0.16% of them before) falls to 0.011 and 0.013%, on a chunk-crowding mesh of
+// 1.3M faces from 0.59 to 0.38%; 16 probes halve that again and take 361 us. (Two probes
+// after a crowded chunk took 326, with 0.45, 0.21 and 5.9% of the terms unplaced.)
 constexpr int BW_THREADS = 256;
 constexpr int BW_WAVES_PER_SIMD = 8;
-constexpr int BW_SLOTS = 512;                 // hash table of (vertex, 3 partial sums) per block
-constexpr int BW_FLUSH = 224;                 // flush once more slots than this are taken
-constexpr int BW_PROBES = 12;                 // a vertex not placed within this many slots goes to HBM,
-constexpr int BW_CROWD = 240, BW_FEW = 2;     // after a chunk with more new vertices than BW_CROWD within BW_FEW
+constexpr int BW_SLOTS = 727;                 // hash table of (vertex, 3 partial sums) per block; prime: any step visits every slot
+constexpr int BW_FLUSH = 320;                 // flush once more slots than this are taken
+constexpr int BW_PROBES = 12;                 // a vertex not placed within this many slots goes to HBM
 constexpr int BW_BLOCKS = 2048;               // persistent grid: 8 resident blocks of 256 per CU
 // LDS adds of floats are slow on this chip where 64-bit integer adds are not,
 // so the table sums in fixed point: c * 2^fx, rounded to an integer, when its
@@ -162,18 +164,20 @@ __device__ inline float wave_max(float v) {
   return v;
 }
 
-constexpr int log2i(int x) { return x <= 1 ? 0 : 1 + log2i(x >> 1); }
-constexpr int BW_HASH_SHIFT = 32 - log2i(BW_SLOTS);
-static_assert((BW_SLOTS & (BW_SLOTS - 1)) == 0 && BW_FLUSH < BW_SLOTS, "table size");
+static_assert(BW_FLUSH < BW_SLOTS && 8 * (BW_SLOTS * 28 + 64) <= (160 << 10), "table size");
 
-// where a vertex is looked for: its first slot, and the odd step from one to the next
+// where a vertex is looked for: its first slot, and the step from one to the next
+// (1 to BW_SLOTS - 1)
 __device__ inline unsigned first_slot(int32_t v) {
   unsigned x = (unsigned)v;
   x = (x ^ (x >> 15)) * 0x85ebca6bu;
   x = (x ^ (x >> 13)) * 0xc2b2ae35u;
-  return x >> BW_HASH_SHIFT;
+  return __umulhi(x, (unsigned)BW_SLOTS);
 }
-__device__ inline unsigned slot_step(int32_t v) { return ((unsigned)v * 0x9e3779b1u >> 8) | 1u; }
+__device__ inline unsigned next_slot(unsigned h, int32_t v) {
+  h += 1u + __umulhi((unsigned)v * 0x9e3779b1u, (unsigned)(BW_SLOTS - 1));
+  return h >= (unsigned)BW_SLOTS ? h - BW_SLOTS : h;
+}
 
 // Each block takes one contiguous run of band cells (band cells follow the
 // tile-ordered bricks, so a run covers a compact piece of surface and shares most
@@ -181,8 +185,8 @@ __device__ inline unsigned slot_step(int32_t v) { return ((unsigned)v * 0x9e3779
 // vertex in an LDS hash table (double hashing) that is added to the global
 // gradient once it is more than BW_FLUSH slots full, and at the end: one global
 // add per vertex, axis and flush instead of one per band cell. Probing stops
-// after BW_PROBES slots (BW_FEW where vertices are hardly shared); such a vertex's contribution goes to the gradient
-// directly, so a full table costs time, never correctness.
+// after BW_PROBES slots; such a vertex's term is added to the gradient as a float of
+// its own, rounded there, where the table's sums are exact until they are flushed.
 __global__ __launch_bounds__(BW_THREADS, BW_WAVES_PER_SIMD) void k_backward(BwdArgs P) {
   __shared__ int s_key[BW_SLOTS];
   __shared__ unsigned long long s_acc[3][BW_SLOTS];  // fixed-point sums, two's complement
@@ -229,7 +233,6 @@ __global__ __launch_bounds__(BW_THREADS, BW_WAVES_PER_SIMD) void k_backward(BwdA
   int m = P.band_off ? find_segment(P.band_off, P.n_meshes + 1, c0 + threadIdx.x) : 0;
   if (m > P.n_meshes - 1) m = P.n_meshes - 1;
   BwMesh M = load_mesh(P, m);
-  int probes = BW_PROBES, before = 0;  // slots taken before the chunk
   for (int64_t base = c0; base < c1; base += BW_THREADS) {
     const int64_t i = base + threadIdx.x;
     const BwCell cur = load_cell(P, i, c1);
@@ -330,13 +333,22 @@ __global__ __launch_bounds__(BW_THREADS, BW_WAVES_PER_SIMD) void k_backward(BwdA
         h[k] = first_slot(vid[k]);
         old[k] = vid[k] >= 0 ? atomicCAS(&s_key[h[k]], -1, vid[k]) : vid[k];
       }
+      // (vid -1 counts as placed)
+      for (int probe = 1; probe < BW_PROBES; probe++) {
+        bool go[3];
+#pragma unroll
+        for (int k = 0; k < 3; k++) {
+          go[k] = old[k] != -1 && old[k] != vid[k];
+          if (go[k]) h[k] = next_slot(h[k], vid[k]);
+        }
+        if (!(go[0] | go[1] | go[2])) break;
+#pragma unroll
+        for (int k = 0; k < 3; k++)
+          if (go[k]) old[k] = atomicCAS(&s_key[h[k]], -1, vid[k]);
+      }
 #pragma unroll
       for (int k = 0; k < 3; k++) {
         if (vid[k] < 0) continue;
-        for (int probe = 1; old[k] != -1 && old[k] != vid[k] && probe < probes; probe++) {
-          h[k] = (h[k] + slot_step(vid[k])) & (BW_SLOTS - 1);
-          old[k] = atomicCAS(&s_key[h[k]], -1, vid[k]);
-        }
         if (old[k] == -1 || old[k] == vid[k]) {
           if (old[k] == -1) n_new++;
           add_vertex(&s_acc[0][h[k]], BW_SLOTS, con[k], F, P.grad + 3 * (int64_t)vid[k]);
@@ -354,9 +366,6 @@ __global__ __launch_bounds__(BW_THREADS, BW_WAVES_PER_SIMD) void k_backward(BwdA
     }
     __syncthreads();
     const int used = s_used;
-    // block-uniform: this chunk's new vertices decide how hard the next one searches
-    probes = used - before > BW_CROWD ? BW_FEW : BW_PROBES;
-    before = used <= BW_FLUSH ? used : 0;
     const bool last = base + BW_THREADS >= c1;
     __syncthreads();  // every thread has read s_used before the next chunk changes it
     if (!last && used <= BW_FLUSH) continue;  // block-uniform: room for another chunk
