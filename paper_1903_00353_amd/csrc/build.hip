@@ -430,84 +430,125 @@ __global__ __launch_bounds__(VK_THREADS) void k_vertex(const float* __restrict__
     polys[tile] = sum;
   }
 }
-// The same for meshes of few vertices: VF_LANES lanes to a vertex, one to a corner, so
+// The same for meshes of few vertices: VF_LANES lanes to a vertex, one to a corner (two
+// from the ninth corner on, up to VF_MAXD), so
 // that a fan takes one angle and one test where a thread takes them one after
 // another, and a mesh of few vertices fills more of the chip. The faces' shares of the
 // pseudonormal are still added in corner order. Vertices of more corners are left to
 // their first lane. polys: cleared by k_inputs. (Build of 642 vertices 43 -> 33 us, 10,242
 // vertices 50 -> 45, 35,000 63 -> 56; from some 100,000 on a lane per vertex keeps the
-// chip busy by itself: 180,000 vertices 108 us and with fans 123, 2.6M 1213 and 1395.)
-constexpr int VF_LANES = 8, VF_THREADS = 256, VF_WAVE = 64 / VF_LANES;
+// chip busy by itself: 180,000 vertices 108 us and with fans 123, 2.6M 1213 and 1395. Delaunay
+// triangles of random points, 4% of the vertices of nine corners and more: with those
+// left to a lane as well 118 us at 1,000 vertices and 237 at 65,000, with two corners a
+// lane 64 and 140, build with its read-back.)
+constexpr int VF_LANES = 8, VF_PER = 2, VF_MAXD = VF_LANES * VF_PER, VF_THREADS = 256, VF_WAVE = 64 / VF_LANES;
 __global__ __launch_bounds__(VF_THREADS) void k_vertex_fan(const float* __restrict__ V, const int32_t* __restrict__ T,
                                                           int64_t nv, const int32_t* __restrict__ off, int32_t* vc,
                                                           VertexOut O, int32_t* twin, int32_t* polys, int64_t* stats) {
   struct Fan {
-    int32_t c[VF_LANES], n[VF_LANES], p[VF_LANES], at[VF_LANES];  // at: the corner whose next vertex is this one's previous one
-    float x[VF_LANES][3];
-    double share[VF_LANES][4];  // face normal, angle / length (0: no normal)
+    union {
+      struct {
+        int32_t c[VF_MAXD], n[VF_MAXD], p[VF_MAXD];
+        int32_t at[VF_MAXD];        // the corner whose next vertex is this one's previous one
+        float x[VF_MAXD][3];
+      };
+      double share[VF_MAXD][4];     // then: face normal, angle / length (0: no normal)
+    };
+    int32_t pad[8];  // a wavefront's eight fans lie in different LDS banks
   };
+  static_assert(sizeof(Fan) % 256 == 32, "fans eight banks apart");
   __shared__ Fan s_fan[VF_THREADS / VF_LANES];
   const int sub = threadIdx.x & (VF_LANES - 1);
   const int64_t v = (blockIdx.x * (int64_t)VF_THREADS + threadIdx.x) / VF_LANES;
   Fan& S = s_fan[threadIdx.x / VF_LANES];
   const int32_t s0 = v < nv ? off[v] : 0, d = v < nv ? off[v + 1] - s0 : 0;
-  const bool fan = d <= VF_LANES, mine = fan && sub < d;
-  int32_t c = mine ? vc[s0 + sub] : INT32_MAX;
-  // corners in ascending order: each lane's place among the fan's
-  S.c[sub] = c;
-  S.at[sub] = 0;
-  wave_sync_lds();
-  int place = 0;
+  const bool fan = d <= VF_MAXD;
+  const int per = __ballot(fan && d > VF_LANES) != 0 ? VF_PER : 1;  // corners of a lane, the same in the wavefront
+  // corners in ascending order: each one's place among the fan's
+  bool mine[VF_PER];
+  int32_t c[VF_PER];
 #pragma unroll
-  for (int k = 0; k < VF_LANES; k++) place += S.c[k] < c ? 1 : 0;
-  wave_sync_lds();
-  if (mine) S.c[place] = c;
-  wave_sync_lds();
-  c = S.c[sub];
-  if (mine) {
-    const int32_t* row = T + (c - c % 3);
-    const int32_t a0 = row[0], a1 = row[1], a2 = row[2];
-    const int j = c % 3;
-    S.n[sub] = j == 0 ? a1 : (j == 1 ? a2 : a0);
-    S.p[sub] = j == 0 ? a2 : (j == 1 ? a0 : a1);
+  for (int h = 0; h < VF_PER; h++) {
+    const int i = sub + h * VF_LANES;
+    mine[h] = h < per && fan && i < d;
+    c[h] = mine[h] ? vc[s0 + i] : INT32_MAX;
+    S.c[i] = c[h];
+    S.at[i] = 0;
   }
+  wave_sync_lds();
+  int place[VF_PER] = {0, 0};
+#pragma unroll
+  for (int h = 0; h < VF_PER; h++)
+    if (h < per)
+#pragma unroll
+      for (int k = 0; k < VF_MAXD; k++)
+        if (k < VF_LANES || per > 1) place[h] += S.c[k] < c[h] ? 1 : 0;
+  wave_sync_lds();
+#pragma unroll
+  for (int h = 0; h < VF_PER; h++)
+    if (mine[h]) S.c[place[h]] = c[h];
+  wave_sync_lds();
+#pragma unroll
+  for (int h = 0; h < VF_PER; h++)
+    if (mine[h]) {
+      const int i = sub + h * VF_LANES;
+      c[h] = S.c[i];
+      const int32_t* row = T + (c[h] - c[h] % 3);
+      const int32_t a0 = row[0], a1 = row[1], a2 = row[2];
+      const int j = c[h] % 3;
+      S.n[i] = j == 0 ? a1 : (j == 1 ? a2 : a0);
+      S.p[i] = j == 0 ? a2 : (j == 1 ? a0 : a1);
+    }
   wave_sync_lds();
   uint32_t e = 0;
   const d3 pv = vload_d(V, v < nv ? v : 0);
-  d3 p1 = pv;
-  if (mine) {
-    const int32_t w = S.n[sub];
-    const f3 x = vload_f(V, w);
-    int32_t match = -1, nmatch = 0;
-    for (int k = 0; k < d; k++) {
-      if (k != sub && S.n[k] == w) e |= ERR_ORIENT;
-      if (S.p[k] == w) {
-        nmatch++;
-        match = prev_corner(S.c[k]);
-        S.at[k] = sub;
+  d3 p1[VF_PER] = {pv, pv};
+#pragma unroll
+  for (int h = 0; h < VF_PER; h++)
+    if (mine[h]) {
+      const int i = sub + h * VF_LANES;
+      const int32_t w = S.n[i];
+      const f3 x = vload_f(V, w);
+      int32_t match = -1, nmatch = 0;
+      for (int k = 0; k < d; k++) {
+        if (k != i && S.n[k] == w) e |= ERR_ORIENT;
+        if (S.p[k] == w) {
+          nmatch++;
+          match = prev_corner(S.c[k]);
+          S.at[k] = i;
+        }
       }
+      if (nmatch != 1) e |= ERR_NONMANIFOLD;
+      twin[c[h]] = nmatch == 1 ? match : -1;
+      S.x[i][0] = x.x;
+      S.x[i][1] = x.y;
+      S.x[i][2] = x.z;
+      p1[h] = mkd(x.x, x.y, x.z);
     }
-    if (nmatch != 1) e |= ERR_NONMANIFOLD;
-    twin[c] = nmatch == 1 ? match : -1;
-    S.x[sub][0] = x.x;
-    S.x[sub][1] = x.y;
-    S.x[sub][2] = x.z;
-    p1 = mkd(x.x, x.y, x.z);
-  }
   if (e) atomicOr(err_word(stats), e);
   wave_sync_lds();
-  d3 n = mkd(0, 0, 0);
-  double ln = 0;
-  if (mine) {
-    const float* y = S.x[S.at[sub]];
-    const d3 e1 = p1 - pv, e2 = mkd(y[0], y[1], y[2]) - pv;
-    n = cross(e1, e2);
-    ln = len(n);
-    S.share[sub][0] = n.x;
-    S.share[sub][1] = n.y;
-    S.share[sub][2] = n.z;
-    S.share[sub][3] = ln > 0 ? atan2(ln, dot(e1, e2)) / ln : 0.0;
-  }
+  d3 p2[VF_PER];
+#pragma unroll
+  for (int h = 0; h < VF_PER; h++)
+    if (mine[h]) {
+      const float* y = S.x[S.at[sub + h * VF_LANES]];
+      p2[h] = mkd(y[0], y[1], y[2]);
+    }
+  wave_sync_lds();  // the shares take the place of what was read above
+  d3 n[VF_PER] = {mkd(0, 0, 0), mkd(0, 0, 0)};
+  double ln[VF_PER] = {0, 0};
+#pragma unroll
+  for (int h = 0; h < VF_PER; h++)
+    if (mine[h]) {
+      const d3 e1 = p1[h] - pv, e2 = p2[h] - pv;
+      n[h] = cross(e1, e2);
+      ln[h] = len(n[h]);
+      double* share = S.share[sub + h * VF_LANES];
+      share[0] = n[h].x;
+      share[1] = n[h].y;
+      share[2] = n[h].z;
+      share[3] = ln[h] > 0 ? atan2(ln[h], dot(e1, e2)) / ln[h] : 0.0;
+    }
   wave_sync_lds();
   VertexAccum acc;
   if (fan)
@@ -517,14 +558,16 @@ __global__ __launch_bounds__(VF_THREADS) void k_vertex_fan(const float* __restri
     }
   VertexTest vt;
   vt.init(acc.n_alpha);
-  if (mine) {
-    vt.neighbour(pv, p1);
-    if (ln > 0) {
-      const double q = dot(n, vt.axis) / ln;
-      if (q > 0) vt.cos_t = q < vt.cos_t ? q : vt.cos_t;
-      else vt.nonpos_normal = 1;
+#pragma unroll
+  for (int h = 0; h < VF_PER; h++)
+    if (mine[h]) {
+      vt.neighbour(pv, p1[h]);
+      if (ln[h] > 0) {
+        const double q = dot(n[h], vt.axis) / ln[h];
+        if (q > 0) vt.cos_t = q < vt.cos_t ? q : vt.cos_t;
+        else vt.nonpos_normal = 1;
+      }
     }
-  }
   // the lanes' tests together
 #pragma unroll
   for (int o = 1; o < VF_LANES; o <<= 1) {
