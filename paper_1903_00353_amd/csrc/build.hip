@@ -225,26 +225,6 @@ constexpr int VK_MAXD = 12;   // fans up to this degree are staged in LDS (18 KB
 constexpr int VK_HALF = 6;    // corners whose loads are in flight together
 static_assert(VK_MAXD == 2 * VK_HALF && VK_MAXD <= 16, "two halves, places in 4 bits");
 
-// ascending order of n corners (heap sort: a fan too long for LDS may be very long)
-__device__ inline void sort_corners(int32_t* a, int n) {
-  auto sift = [&](int root, int end) {
-    const int32_t x = a[root];
-    for (int child; (child = 2 * root + 1) < end; root = child) {
-      if (child + 1 < end && a[child + 1] > a[child]) child++;
-      if (a[child] <= x) break;
-      a[root] = a[child];
-    }
-    a[root] = x;
-  };
-  for (int k = n / 2 - 1; k >= 0; k--) sift(k, n);
-  for (int end = n - 1; end > 0; end--) {
-    const int32_t x = a[0];
-    a[0] = a[end];
-    a[end] = x;
-    sift(0, end);
-  }
-}
-
 // Twins around one vertex: corner i's out-edge to N(i) pairs with the one in-edge
 // from P(k) = N(i); matched(k, i) hears of every such pair. Returns the error bits.
 template <class C, class N, class P, class M>
@@ -283,6 +263,19 @@ __device__ inline VertexTest test_fan(int d, d3 pv, XN xn, XP xp) {
   return vt;
 }
 
+// Twins and tests of a fan of d corners at c (ascending), read from memory again and again,
+// by one lane. Code of its own: one loop for both, choosing between LDS and memory at each
+// read, took 98 ms in place of 62 at a pole of 512 corners behind 240,000 faces.
+__device__ inline VertexTest long_fan(const float* __restrict__ V, const int32_t* __restrict__ T,
+                                      const int32_t* __restrict__ c, int d, d3 pv, int32_t* twin, int64_t* stats) {
+  auto C = [&](int k) { return c[k]; };
+  auto N = [&](int k) { return T[next_corner(c[k])]; };
+  auto P = [&](int k) { return T[prev_corner(c[k])]; };
+  const uint32_t e = match_fan(d, C, N, P, [](int, int) {}, twin);
+  if (e) atomicOr(err_word(stats), e);
+  return test_fan(d, pv, [&](int k) { return vload_d(V, N(k)); }, [&](int k) { return vload_d(V, P(k)); });
+}
+
 struct VertexOut {
   int ruff_mode, saddle_mode, force_both;
   const int32_t* vert_mesh;
@@ -311,7 +304,7 @@ __device__ inline int put_vertex(const VertexOut& O, int64_t v, int d, const Ver
 }
 static_assert(V_POS == 1u && V_NEG == 2u, "side bits of the class word");
 
-// Per vertex u, over its fan of corners in ascending order (staged in LDS, then
+// Per vertex u, over its fan of corners in ascending order (sorted and staged in LDS, then
 // replaced there by the positions of the neighbours: each is read once, six loads
 // in flight together, where reading both far corners of every triangle again in
 // each of the two passes below took four times the loads one after another:
@@ -326,8 +319,8 @@ static_assert(V_POS == 1u && V_NEG == 2u, "side bits of the class word");
 // Bounded by the latency of the gathers of triangle rows and positions and by its
 // FP64 arithmetic (4 wavefronts per SIMD, LDS-bound).
 __global__ __launch_bounds__(VK_THREADS) void k_vertex(const float* __restrict__ V, const int32_t* __restrict__ T,
-                                                      int64_t nv, const int32_t* __restrict__ off, int32_t* vc,
-                                                      VertexOut O, int32_t* twin, int32_t* polys, int64_t* stats) {
+                                                      int64_t nv, const int32_t* __restrict__ off,
+                                                      const int32_t* __restrict__ vc, VertexOut O, int32_t* twin, int32_t* polys, int64_t* stats) {
   __shared__ int32_t s_c[VK_MAXD][VK_THREADS], s_n[VK_MAXD][VK_THREADS], s_p[VK_MAXD][VK_THREADS];
   __shared__ int s_polys[VK_THREADS / 64];
   const int t = threadIdx.x;
@@ -386,16 +379,20 @@ __global__ __launch_bounds__(VK_THREADS) void k_vertex(const float* __restrict__
             s_p[h + k][t] = j == 0 ? a2[k] : (j == 1 ? a0[k] : a1[k]);
           }
       }
-    } else if (!staged) {
-      sort_corners(vc + s0, d);
     }
-    auto C_ = [&](int k) { return staged ? s_c[k][t] : vc[s0 + k]; };
-    auto N_ = [&](int k) { return staged ? s_n[k][t] : T[next_corner(vc[s0 + k])]; };
-    auto P_ = [&](int k) { return staged ? s_p[k][t] : T[prev_corner(vc[s0 + k])]; };
-    const uint32_t e = match_fan(d, C_, N_, P_, [&](int k, int i) {
-      if (staged) place = (place & ~(15ull << (4 * k))) | ((uint64_t)i << (4 * k));
-    }, twin);
-    if (e) atomicOr(err_word(stats), e);
+    const d3 pv = vload_d(V, v);
+    VertexTest vt;
+    if (staged) {
+      auto C_ = [&](int k) { return s_c[k][t]; };
+      auto N_ = [&](int k) { return s_n[k][t]; };
+      auto P_ = [&](int k) { return s_p[k][t]; };
+      const uint32_t e = match_fan(d, C_, N_, P_, [&](int k, int i) {
+        place = (place & ~(15ull << (4 * k))) | ((uint64_t)i << (4 * k));
+      }, twin);
+      if (e) atomicOr(err_word(stats), e);
+    } else {
+      vt = long_fan(V, T, vc + s0, d, pv, twin, stats);
+    }
     if (staged && d > 0) {
       // positions of the next vertices in place of the ids (a corner whose previous
       // vertex is no next vertex, on a surface that is rejected, takes the first's)
@@ -417,9 +414,8 @@ __global__ __launch_bounds__(VK_THREADS) void k_vertex(const float* __restrict__
       return mkd((double)__int_as_float(s_c[k][t]), (double)__int_as_float(s_p[k][t]),
                  (double)__int_as_float(s_n[k][t]));
     };
-    auto XN = [&](int k) { return staged ? at(k) : vload_d(V, N_(k)); };
-    auto XP = [&](int k) { return staged ? at((int)(place >> (4 * k)) & 15) : vload_d(V, P_(k)); };
-    sides = put_vertex(O, v, d, test_fan(d, vload_d(V, v), XN, XP));
+    if (staged) vt = test_fan(d, pv, at, [&](int k) { return at((int)(place >> (4 * k)) & 15); });
+    sides = put_vertex(O, v, d, vt);
   }
   const int n = __popcll(__ballot((sides & 1) != 0)) + __popcll(__ballot((sides & 2) != 0));
   if ((t & 63) == 0) s_polys[t >> 6] = n;
@@ -443,8 +439,8 @@ __global__ __launch_bounds__(VK_THREADS) void k_vertex(const float* __restrict__
 // lane 64 and 140, build with its read-back.)
 constexpr int VF_LANES = 8, VF_PER = 2, VF_MAXD = VF_LANES * VF_PER, VF_THREADS = 256, VF_WAVE = 64 / VF_LANES;
 __global__ __launch_bounds__(VF_THREADS) void k_vertex_fan(const float* __restrict__ V, const int32_t* __restrict__ T,
-                                                          int64_t nv, const int32_t* __restrict__ off, int32_t* vc,
-                                                          VertexOut O, int32_t* twin, int32_t* polys, int64_t* stats) {
+                                                          int64_t nv, const int32_t* __restrict__ off,
+                                                          const int32_t* __restrict__ vc, VertexOut O, int32_t* twin, int32_t* polys, int64_t* stats) {
   struct Fan {
     union {
       struct {
@@ -580,15 +576,7 @@ __global__ __launch_bounds__(VF_THREADS) void k_vertex_fan(const float* __restri
   }
   int sides = 0;
   if (sub == 0 && v < nv) {
-    if (!fan) {
-      sort_corners(vc + s0, d);
-      auto C = [&](int k) { return vc[s0 + k]; };
-      auto N = [&](int k) { return T[next_corner(vc[s0 + k])]; };
-      auto P = [&](int k) { return T[prev_corner(vc[s0 + k])]; };
-      const uint32_t err = match_fan(d, C, N, P, [](int, int) {}, twin);
-      if (err) atomicOr(err_word(stats), err);
-      vt = test_fan(d, pv, [&](int k) { return vload_d(V, N(k)); }, [&](int k) { return vload_d(V, P(k)); });
-    }
+    if (!fan) vt = long_fan(V, T, vc + s0, d, pv, twin, stats);
     sides = put_vertex(O, v, d, vt);
   }
   const int sum = __popcll(__ballot((sides & 1) != 0)) + __popcll(__ballot((sides & 2) != 0));
@@ -992,7 +980,8 @@ __device__ inline void number_bricks(const BrickArgs& P, int64_t tile, int* ws) 
 // counters, a place in the bucket for the tile's share from one atomic per bucket,
 // so that a share's corners lie together. k_bucket takes one bucket per block,
 // counts its vertices in LDS, and places its corners; a vertex's corners come out in
-// any order (k_vertex sorts its fan). The blocks past the tiles and the buckets number
+// any order (k_vertex sorts the fans that it stages), except those of long fans, which the
+// block's wavefronts sort. The blocks past the tiles and the buckets number
 // the band bricks and the edges. Two reads and one write of 8 bytes per corner
 // in all beside the 4-byte indices, where the radix sort read and wrote 16 bytes three
 // times and counted digits in between (5.2M faces, 15.7M corners: k_deal 72 us and k_bucket 124, the edge ids and
@@ -1084,10 +1073,28 @@ __global__ __launch_bounds__(TH) void k_deal(DealArgs P, BrickArgs B, EdgeBase E
       P.pairs[s_base[v[k] >> P.shift] + r[k]] = make_uint2((uint32_t)v[k], (uint32_t)(base + (int64_t)k * TH));
 }
 
+// ascending order of n corners, by one wavefront: each one's place is the number of
+// smaller ones. tmp holds n words. (A heap sort by the one thread that matches the fan took
+// 1.3 of the build's 100 ms at a pole of 512 corners behind 240,000 faces, 20 of its 150 us at one of 17.)
+__device__ inline void sort_fan(int32_t* corners, uint32_t* tmp, int n) {
+  const int lane = threadIdx.x & 63;
+  for (int k = lane; k < n; k += 64) tmp[k] = (uint32_t)corners[k];
+  __threadfence_block();
+  __builtin_amdgcn_wave_barrier();
+  for (int k = lane; k < n; k += 64) {
+    const uint32_t c = tmp[k];
+    int place = 0;
+#pragma unroll 8
+    for (int j = 0; j < n; j++) place += tmp[j] < c ? 1 : 0;
+    corners[place] = (int32_t)c;
+  }
+}
+
 template <int TH>
 __global__ __launch_bounds__(TH) void k_bucket(DealArgs P, BrickArgs B, EdgeBase E) {
   extern __shared__ int s_count[];  // 2^shift
   __shared__ int ws[TH / 64];
+  __shared__ int s_long;            // some fan is not sorted by the vertex pass
   if ((int)blockIdx.x >= P.buckets) {
     const int64_t x = (int64_t)blockIdx.x - P.buckets;
     if (x < E.tiles) edge_bases(E, x);
@@ -1106,6 +1113,7 @@ __global__ __launch_bounds__(TH) void k_bucket(DealArgs P, BrickArgs B, EdgeBase
     return;
   }
   for (int k = t; k < size; k += TH) s_count[k] = 0;
+  if (t == 0) s_long = 0;
   __syncthreads();
   // AHEAD pairs of a thread are loaded together, then used: one at a time, each load
   // waits out the memory latency
@@ -1135,6 +1143,7 @@ __global__ __launch_bounds__(TH) void k_bucket(DealArgs P, BrickArgs B, EdgeBase
     const int i = t * per + k;
     if (i < size) {
       const int c = s_count[i];
+      if (c > VK_MAXD) s_long = 1;
       s_count[i] = at;
       if (v0 + i < P.nv) P.off[v0 + i] = start + at;
       at += c;
@@ -1151,6 +1160,18 @@ __global__ __launch_bounds__(TH) void k_bucket(DealArgs P, BrickArgs B, EdgeBase
 #pragma unroll
     for (int a = 0; a < AHEAD; a++)
       if (k0 + a * TH + t < n) P.corners[start + atomicAdd(&s_count[x[a].x - (uint32_t)v0], 1)] = (int32_t)x[a].y;
+  }
+  if (!s_long) return;  // the same in all threads: last written before the barrier above
+  __syncthreads();
+  // a counter now stands at its vertex's end, the place where the next one's corners
+  // start; the block's pairs are read and serve as scratch
+  for (int i0 = 0; i0 < size; i0 += TH) {
+    const int i = i0 + t, end = i < size ? s_count[i] : 0, first = i > 0 && i < size ? s_count[i - 1] : 0;
+    for (unsigned long long left = __ballot(end - first > VK_MAXD); left != 0; left &= left - 1) {
+      const int l = __ffsll((long long)left) - 1;
+      const int from = __builtin_amdgcn_readlane(first, l), to = __builtin_amdgcn_readlane(end, l);
+      sort_fan(P.corners + start + from, (uint32_t*)(P.pairs + start + from), to - from);
+    }
   }
 }
 

@@ -31,7 +31,7 @@ def shuffled(mesh, seed):
     return v, np.ascontiguousarray(f[np.random.default_rng(seed).permutation(f.shape[0])])
 
 
-CASES = [("bipyramid %d" % n, shuffled(meshgen.bipyramid(n), n)) for n in (8, 9, 10, 15, 16, 17)]
+CASES = [("bipyramid %d" % n, shuffled(meshgen.bipyramid(n), n)) for n in (8, 9, 10, 15, 16, 17, 130)]
 
 
 @pytest.mark.parametrize("name,mesh", CASES + [("random", None)], ids=[n for n, _ in CASES] + ["random"])
@@ -55,3 +55,23 @@ def test_fans_of_more_corners_than_lanes(name, mesh):
     rep = compare(om, g, om.band(g), got[2].cpu().numpy(), got[0].cpu().numpy(), got[1].cpu().numpy())
     print(rep, flush=True)
     assert_parity(rep)
+
+
+@pytest.mark.parametrize("nu,nv", [(300, 230), (1200, 1180)])  # buckets of 256 and of 1024 threads
+def test_fans_that_are_sorted_where_their_corners_are_placed(nu, nv):
+    """Several long fans in one bucket, of fewer and more corners than a wavefront has lanes
+    and of whole multiples: the same fields as each mesh gives alone."""
+    many = meshgen.torus(nu, nv)
+    parts = [shuffled(meshgen.bipyramid(n), n) for n in (13, 63, 64, 65, 100)]
+    g = Grid.unit(40, 3)
+    print("[case] long fans behind", many[1].shape[0], flush=True)
+    behind = P.Batch([many] + parts, [Grid.unit(32, 2)] + [g] * len(parts))
+    behind.step()
+    behind.check()
+    for k, part in enumerate(parts):
+        alone = P.Batch([part], [g])
+        alone.step()
+        alone.check()
+        got, want = behind.band(1 + k), alone.band(0)
+        assert want[0].numel() > 0
+        assert all(torch.equal(x, y) for x, y in zip(got, want))
