@@ -398,6 +398,7 @@ namespace {
 int backward_impl(const csc_features* f, const float* sdf_d, const int32_t* feat_d, const int32_t* cell_d, int64_t n,
                   const int64_t* n_dev, const int64_t* band_off, const float* grad_sdf_d, float* grad_verts_d,
                   hipStream_t s) {
+  queued_on(f, s);
   BwdArgs A;
   A.V = f->verts;
   A.frec = f->face_rec;

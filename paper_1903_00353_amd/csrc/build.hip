@@ -1373,6 +1373,7 @@ using namespace csc;
 extern "C" int csc_features_order_faces(csc_features* F, int32_t enable, void* stream) {
   if (!F || !F->built || (enable != 0 && enable != 1)) return CSC_INVALID_ARG;
   hipStream_t s = (hipStream_t)stream;
+  queued_on(F, stream);
   if (!enable || F->nf == 0) {
     if (F->face_order) {
       (void)hipStreamSynchronize(s);
@@ -1710,6 +1711,7 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
   F->fabsorbed = (uint8_t*)(A + L.off[L_FABS]);
   F->built = F->synced = false;
 
+  queued_on(F, stream);
   MeshTables M;
   M.n = 0;
   if (config_changed && n_meshes <= TABLE_MESHES) {
@@ -1913,6 +1915,7 @@ int build_impl(const float* verts_d, const int32_t* tris_d, const int64_t* nv, c
 extern "C" int csc_features_sync(csc_features* F, void* stream) {
   if (!F || !F->built || !F->h_stats) return CSC_INVALID_ARG;
   hipStream_t s = (hipStream_t)stream;
+  queued_on(F, stream);
   const int64_t items = (F->ne / 16 > F->nv / 4 ? F->ne / 16 : F->nv / 4) + 1;
   hipError_t he = hipSuccess;
   if (!F->classes_counted && items <= STATS_ONE_BLOCK) {

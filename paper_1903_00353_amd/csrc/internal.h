@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
 #include <vector>
 
 #include "../../include/csc.h"
@@ -241,6 +242,8 @@ struct csc_features {
   int32_t* face_order = nullptr;    // [face_order_n] optional processing order of the face pass (own allocation)
   int64_t face_order_n = 0;
 
+  // set once work on the handle was queued on another stream than the null stream
+  mutable std::atomic<bool> other_streams{false};
   bool built = false;               // device work queued for the current inputs
   bool synced = false;              // counts below read back since the last build
   bool classes_counted = false;     // the class statistics of the last build are in d_stats
@@ -254,7 +257,7 @@ namespace csc {
 // hipHostMalloc and their frees cost 50 us at 16 MB and 0.5 ms at 256 MB (build and
 // free of a 1280-face handle 205 us, from kept memory 79, into a kept handle 76). take: of the
 // current device, from the kept ones or allocated (*got >= bytes); give: back, of
-// device dev, with no work left that uses it (device_idle waits for that). Kept: at
+// device dev, with no work left that uses it (handle_idle waits for that). Kept: at
 // most POOL_BYTES and POOL_BLOCKS per device, nothing that POOL_AGE later gives left
 // unused, and nothing once an allocation here has run out of memory. All of it may be
 // called from any thread.
@@ -266,7 +269,12 @@ hipError_t pool_take(size_t bytes, char** p, size_t* got, int* dev);
 void pool_give(int dev, char* p, size_t bytes);
 hipError_t pinned_take(int64_t** p, int* dev);
 void pinned_give(int dev, int64_t* p);
-bool device_idle(int dev);
+bool handle_idle(const csc_features* f);
+
+// every entry point that queues work on a handle says on which stream
+inline void queued_on(const csc_features* f, const void* stream) {
+  if (stream) f->other_streams.store(true, std::memory_order_relaxed);
+}
 
 // status of a device-side error word
 int status_from_errors(uint64_t err, int64_t ne_found, int64_t ne_expected);

@@ -1629,6 +1629,7 @@ int scan_convert_impl(const csc_features* f, void* workspace_d, size_t ws_bytes,
                       int32_t* cell_d, int64_t* n_band_d, int64_t* band_off_d, float* dense_d, hipStream_t s) {
   WsLayout L;
   if (!cap_from_bytes(f, ws_bytes, L)) return CSC_WORKSPACE_TOO_SMALL;
+  queued_on(f, s);
   const int64_t cap = L.cap;
   char* W = (char*)workspace_d;
   unsigned long long* keys = (unsigned long long*)(W + L.keys);
@@ -1729,6 +1730,7 @@ extern "C" int csc_scan_convert_count(const csc_features* f, void* workspace_d, 
   WsLayout L;
   if (!cap_from_bytes(f, ws_bytes, L)) return CSC_WORKSPACE_TOO_SMALL;
   hipStream_t s = (hipStream_t)stream;
+  queued_on(f, stream);
   char* W = (char*)workspace_d;
   unsigned long long* ctr = (unsigned long long*)(W + L.ctr);
   k_zero_u64<<<1, 64, 0, s>>>(ctr, 6);
@@ -1751,6 +1753,7 @@ extern "C" int csc_scan_record_atomics(const csc_features* f, void* workspace_d,
   WsLayout L;
   if (!cap_from_bytes(f, ws_bytes, L)) return CSC_WORKSPACE_TOO_SMALL;
   hipStream_t s = (hipStream_t)stream;
+  queued_on(f, stream);
   char* W = (char*)workspace_d;
   unsigned long long* ctr = (unsigned long long*)(W + L.ctr);
   k_zero_u64<<<1, 64, 0, s>>>(ctr, 8);

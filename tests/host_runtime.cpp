@@ -111,7 +111,9 @@ hipError_t hipDeviceSynchronize(void) {
   sim_device_waits++;
   return sim_capturing ? hipErrorStreamCaptureUnsupported : hipSuccess;
 }
-hipError_t hipStreamSynchronize(hipStream_t) { return sim_capturing ? hipErrorStreamCaptureUnsupported : hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s) {  // the null stream is never captured
+  return s && sim_capturing ? hipErrorStreamCaptureUnsupported : hipSuccess;
+}
 hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st) {
   *st = sim_capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
   return hipSuccess;

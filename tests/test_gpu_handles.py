@@ -96,3 +96,31 @@ def test_a_workspace_on_an_8_byte_boundary(level, n):
     got = P.csc_scan_convert(f, torch.full((nbytes + 8,), 1, dtype=torch.uint8, device="cuda")[8:])
     assert want.n_band > 0
     assert all(torch.equal(a, b) for a, b in zip((got.sdf, got.feat, got.cell), (want.sdf, want.feat, want.cell)))
+
+
+def test_a_handle_freed_with_work_on_another_stream():
+    """Built on one stream, scanned on another behind some milliseconds of other work, then
+    freed: its memory serves the next handle only once that scan is done."""
+    verts, tris = mesh(4)
+    g = Grid.unit(64, 3)
+    want = P.csc_scan_convert(P.csc_build_features(verts, tris, g))
+    other = P.csc_build_features(verts * 0.5, tris, g)
+    other.free()
+    side = torch.cuda.Stream()
+    a = torch.rand(4096, 4096, device="cuda")
+    f = P.csc_build_features(verts, tris, g)
+    nbytes, mx = P.csc_scan_convert_workspace(f)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+    out = (torch.zeros(mx, device="cuda"), torch.zeros(mx, dtype=torch.int32, device="cuda"),
+           torch.zeros(mx, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int64, device="cuda"))
+    torch.cuda.synchronize()
+    print("[case] freed behind another stream", flush=True)
+    with torch.cuda.stream(side):
+        for _ in range(10):
+            b = a @ a
+        P.csc_scan_convert(f, ws, out, sync_count=False)
+    f.free()
+    P.csc_build_features(verts * 0.5, tris, g)  # takes the memory over
+    torch.cuda.synchronize()
+    assert b.shape == a.shape and int(out[3].item()) == want.n_band
+    assert all(torch.equal(x[:want.n_band], y) for x, y in zip(out, (want.sdf, want.feat, want.cell)))

@@ -27,7 +27,7 @@ class Sim:
     def __getattr__(self, name):  # a variable of the stand-in
         return (C.c_size_t if name in ("limit", "used") else C.c_int).in_dll(self.lib, "sim_" + name)
 
-    def build(self, n, out=None, meshes=5, nv=6, nf=8):
+    def build(self, n, out=None, meshes=5, nv=6, nf=8, stream=None):
         """(status, handle) of `meshes` equal meshes on grids of n^3 cells; five meshes
         have their tables copied, four or fewer as kernel arguments."""
         out = C.c_void_p() if out is None else out
@@ -37,7 +37,7 @@ class Sim:
             g.h, g.band_cells = 1.0 / n, 2.0
         data = C.c_void_p(0x1000)  # handed to kernels only
         code = self.lib.csc_build_features_batched(data, data, (C.c_int64 * meshes)(*[nv] * meshes),
-                                                   (C.c_int64 * meshes)(*[nf] * meshes), grids, meshes, None, 0, None,
+                                                   (C.c_int64 * meshes)(*[nf] * meshes), grids, meshes, None, 0, stream,
                                                    C.byref(out))
         return code, out
 
@@ -84,15 +84,19 @@ def test_a_build_that_runs_out_of_memory_writes_its_tables_the_next_time(sim):
     sim.lib.csc_features_free(h)
 
 
-def test_a_handle_freed_during_a_capture_waits_for_the_device_without_ending_it(sim):
-    """hipDeviceSynchronize would end the capture (of any thread); the handle's memory
-    serves the next one all the same."""
-    code, h = sim.build(16)
+@pytest.mark.parametrize("stream", [None, 0x10])
+def test_a_handle_freed_during_a_capture_is_waited_for_without_ending_it(sim, stream):
+    """hipDeviceSynchronize would end the capture (of any thread); hipFree, which waits for
+    the device too, is called where the handle was used on another than the null stream.
+    The handle's memory serves the next one all the same."""
+    code, h = sim.build(16, stream=stream)
     assert code == OK
+    frees = sim.frees.value
     sim.capturing.value = 1
     sim.lib.csc_features_free(h)
     sim.capturing.value = 0
     assert sim.device_waits.value == 0
+    assert (sim.frees.value > frees) == (stream is not None)
     used = sim.used.value
     code, h = sim.build(16)
     assert code == OK and sim.used.value == used
