@@ -398,11 +398,18 @@ int csc_timing_reset(void);
 int csc_timing_read(double* ms, int64_t* calls, int32_t n);
 const char* csc_timing_stage_name(int32_t stage);
 
-/* Release a handle and its device memory, after the work queued on its device has
- * ended. Up to 256 MiB per device of released memory are kept for the process's next
- * handles and welds, and given back when they stay unused or an allocation runs out
- * of memory. NULL is accepted. */
+/* Release a handle and its device memory, after the work queued on it has ended (the
+ * call waits for that; a capture that is in progress goes on). Up to 256 MiB per device
+ * of released memory, in at most 16 blocks, are kept for the process's next handles and
+ * welds: a block is given back once 64 later releases have left it unused, and all of
+ * them when an allocation of the library runs out of memory, or by
+ * csc_release_memory. NULL is accepted. */
 void csc_features_free(csc_features* f);
+
+/* Give back all device memory (and pinned host memory) kept from released handles and
+ * welds, on every device: for a program whose own allocator needs it. Handles in use
+ * are not touched. Waits for the devices that hold any. */
+void csc_release_memory(void);
 
 /* Static, human-readable text of a status code. */
 const char* csc_error_string(int code);

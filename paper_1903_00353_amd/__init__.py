@@ -66,7 +66,7 @@ EXPORTS = ["csc_build_features", "csc_features_info", "csc_scan_convert_workspac
            "csc_features_sync", "csc_scan_convert_batched", "csc_sdf_backward_batched", "csc_interior_fill",
            "csc_weld_soup", "csc_scan_record_atomics", "csc_atomic_replay", "csc_fadd_rate",
            "csc_weld_soup_noalloc", "csc_weld_soup_noalloc_max_faces", "csc_scan_convert_workspace_for",
-           "csc_features_order_faces"]
+           "csc_features_order_faces", "csc_release_memory"]
 CSC_BUILD_NO_SYNC = 1
 CSC_BUILD_GRAPH_SAFE = 2
 N_STAGES = 13
@@ -133,6 +133,8 @@ def lib():
     L.csc_fadd_rate.argtypes = [P, C.c_int64, C.c_int64, P]
     L.csc_features_free.restype = None
     L.csc_features_free.argtypes = [P]
+    L.csc_release_memory.restype = None
+    L.csc_release_memory.argtypes = []
     L.csc_error_string.restype = C.c_char_p
     L.csc_error_string.argtypes = [C.c_int]
     L.csc_last_hip_error.restype = C.c_char_p
@@ -283,12 +285,10 @@ def csc_scan_convert(f: Features, workspace=None, out=None, dense=None, stream=N
     nbytes, mx = csc_scan_convert_workspace(f)
     dev = f.verts.device
     if workspace is None:
-        workspace = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=dev)
+        workspace = _new(max(nbytes, 1), torch.uint8, dev)
     if out is None:
-        out = (torch.empty(max(mx, 1), dtype=torch.float32, device=dev),
-               torch.empty(max(mx, 1), dtype=torch.int32, device=dev),
-               torch.empty(max(mx, 1), dtype=torch.int32, device=dev),
-               torch.zeros(1, dtype=torch.int64, device=dev))
+        out = (_new(max(mx, 1), torch.float32, dev), _new(max(mx, 1), torch.int32, dev),
+               _new(max(mx, 1), torch.int32, dev), torch.zeros(1, dtype=torch.int64, device=dev))
     sdf, feat, cell, nb = out
     code = lib().csc_scan_convert(f.handle, _ptr(workspace), workspace.numel(), _ptr(sdf), _ptr(feat), _ptr(cell),
                                   _ptr(nb), _ptr(dense), _stream(stream))
@@ -321,7 +321,7 @@ def csc_scan_convert_count(f: Features, workspace=None, stream=None):
     import torch
     nbytes, _ = csc_scan_convert_workspace(f)
     if workspace is None:
-        workspace = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=f.verts.device)
+        workspace = _new(max(nbytes, 1), torch.uint8, f.verts.device)
     counts = (C.c_int64 * 6)()
     _check(lib().csc_scan_convert_count(f.handle, _ptr(workspace), workspace.numel(), counts, _stream(stream)),
            "csc_scan_convert_count")
@@ -476,10 +476,9 @@ class Batch:
         nb = int(self.f.info()["n_bricks"])
         nbytes, mx = csc_scan_convert_workspace_for(self.f, int(nb * float(headroom)) + 1)
         # every key empty (all ones) before the first scan; each scan's sign pass leaves it so
-        self.workspace = torch.full((max(nbytes, 1),), 255, dtype=torch.uint8, device=device)
-        self.out = (torch.empty(max(mx, 1), dtype=torch.float32, device=device),
-                    torch.empty(max(mx, 1), dtype=torch.int32, device=device),
-                    torch.empty(max(mx, 1), dtype=torch.int32, device=device))
+        self.workspace = _new(max(nbytes, 1), torch.uint8, device).fill_(255)
+        self.out = (_new(max(mx, 1), torch.float32, device), _new(max(mx, 1), torch.int32, device),
+                    _new(max(mx, 1), torch.int32, device))
         self.band_off = torch.zeros(len(self.grids) + 1, dtype=torch.int64, device=device)
         self.backward = backward
         self.grad_verts = torch.zeros_like(self.verts)
@@ -553,6 +552,22 @@ def csc_features_free(f: Features):
     f.free()
 
 
+def csc_release_memory():
+    """Give back the device memory that the library keeps from freed handles and welds."""
+    lib().csc_release_memory()
+
+
+def _new(size, dtype, device):
+    """torch.empty, tried again without the memory that the library keeps where there is
+    not enough for both."""
+    import torch
+    try:
+        return torch.empty(size, dtype=dtype, device=device)
+    except torch.OutOfMemoryError:
+        csc_release_memory()
+        return torch.empty(size, dtype=dtype, device=device)
+
+
 def csc_classify_edge(a, b, c1, c2) -> int:
     arrs = [np.ascontiguousarray(x, dtype=np.float32) for x in (a, b, c1, c2)]
     return int(lib().csc_classify_edge(*[x.ctypes.data_as(C.c_void_p) for x in arrs]))
@@ -578,8 +593,8 @@ def csc_weld_soup(soup, stream=None):
     if soup.dtype != torch.float32:
         raise TypeError("soup must be float32")
     nf = int(soup.shape[0])
-    verts = torch.empty(3 * nf, 3, dtype=torch.float32, device=soup.device)
-    tris = torch.empty(nf, 3, dtype=torch.int32, device=soup.device)
+    verts = _new((3 * nf, 3), torch.float32, soup.device)
+    tris = _new((nf, 3), torch.int32, soup.device)
     nv = C.c_int64(0)
     _check(lib().csc_weld_soup(_ptr(soup), nf, _ptr(verts), _ptr(tris), C.byref(nv), _stream(stream)),
            "csc_weld_soup")
@@ -616,7 +631,7 @@ def sdf(verts, tris, grid, options=None, dense=False, fill_interior=False):
     d = None
     if dense or fill_interior:
         dense = True
-        d = torch.empty(int(grid.n[2]) * int(grid.n[1]) * int(grid.n[0]), dtype=torch.float32, device=verts.device)
+        d = _new(int(grid.n[2]) * int(grid.n[1]) * int(grid.n[0]), torch.float32, verts.device)
     band = csc_scan_convert(f, dense=d)
     if fill_interior:
         csc_interior_fill(f, d)

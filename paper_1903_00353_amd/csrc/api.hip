@@ -56,19 +56,36 @@ struct CaptureRelaxed {
   }
 };
 
-// every kept block of a device given back
-void pool_empty(int dev) {
-  std::vector<Block> all;
-  {
-    std::lock_guard<std::mutex> lk(pools()->mu);
-    all.swap(pools()->dev[dev].blocks);
-    pools()->dev[dev].bytes = 0;
-  }
-  for (const Block& b : all) (void)hipFree(b.p);
-}
 }  // namespace
 
 namespace csc {
+
+void pool_empty(int dev) {
+  if (!pools() || dev < 0 || dev >= 64) return;
+  std::vector<Block> all;
+  std::vector<int64_t*> words;
+  {
+    std::lock_guard<std::mutex> lk(pools()->mu);
+    all.swap(pools()->dev[dev].blocks);
+    words.swap(pools()->dev[dev].pinned);
+    pools()->dev[dev].bytes = 0;
+  }
+  CaptureRelaxed relaxed;
+  for (const Block& b : all) (void)hipFree(b.p);
+  for (int64_t* w : words) (void)hipHostFree(w);
+}
+
+hipError_t device_alloc(size_t bytes, void** p, int dev) {
+  CaptureRelaxed relaxed;
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory) {
+    (void)hipGetLastError();
+    pool_empty(dev);
+    e = hipMalloc(p, bytes);
+  }
+  if (e != hipSuccess) *p = nullptr;
+  return e;
+}
 
 int fail_hip(hipError_t e) {
   const char* s = hipGetErrorString(e);
@@ -120,16 +137,14 @@ hipError_t pool_take(size_t bytes, char** p, size_t* got, int* dev) {
   size_t step = 4096;
   while (step * 16 <= bytes) step *= 2;
   const size_t round = pooled ? (bytes + step - 1) / step * step : bytes;
-  e = hipMalloc((void**)p, round);
-  *got = round;
-  if (e == hipErrorOutOfMemory && pooled) {
+  if (round > bytes) {  // without the rounding where that does not fit
+    e = hipMalloc((void**)p, round);
+    *got = round;
+    if (e != hipErrorOutOfMemory) return e;
     (void)hipGetLastError();
-    pool_empty(*dev);
-    e = hipMalloc((void**)p, bytes);
-    *got = bytes;
   }
-  if (e != hipSuccess) *p = nullptr;
-  return e;
+  *got = bytes;
+  return device_alloc(bytes, (void**)p, *dev);
 }
 
 void pool_give(int dev, char* p, size_t bytes) {
@@ -274,6 +289,12 @@ extern "C" void csc_features_free(csc_features* f) {
     else (void)hipHostFree(f->h_stats);
   }
   delete f;
+}
+
+extern "C" void csc_release_memory(void) {
+  int devices = 0;
+  if (hipGetDeviceCount(&devices) != hipSuccess) return;
+  for (int dev = 0; dev < devices; dev++) pool_empty(dev);
 }
 
 extern "C" int csc_classify_edge(const float a[3], const float b[3], const float c1[3], const float c2[3]) {

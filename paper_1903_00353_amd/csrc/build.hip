@@ -1393,15 +1393,12 @@ extern "C" int csc_features_order_faces(csc_features* F, int32_t enable, void* s
   if (sort_bytes == 0) return CSC_INVALID_ARG;
   const size_t key_bytes = ((size_t)nf * sizeof(uint32_t) + 255) & ~(size_t)255;
   if (!F->face_order) {
-    hipError_t he = hipMalloc((void**)&F->face_order, sizeof(int32_t) * (size_t)nf);
-    if (he != hipSuccess) {
-      F->face_order = nullptr;
-      return he == hipErrorOutOfMemory ? CSC_OUT_OF_MEMORY : fail_hip(he);
-    }
+    hipError_t he = device_alloc(sizeof(int32_t) * (size_t)nf, (void**)&F->face_order, F->device);
+    if (he != hipSuccess) return he == hipErrorOutOfMemory ? CSC_OUT_OF_MEMORY : fail_hip(he);
   }
   F->face_order_n = 0;  // not valid until the sort below has run
   char* tmp = nullptr;
-  hipError_t he = hipMalloc((void**)&tmp, 2 * key_bytes + sort_bytes);
+  hipError_t he = device_alloc(2 * key_bytes + sort_bytes, (void**)&tmp, F->device);
   if (he != hipSuccess) return he == hipErrorOutOfMemory ? CSC_OUT_OF_MEMORY : fail_hip(he);
   uint32_t* key = (uint32_t*)tmp;
   uint32_t* key_sorted = (uint32_t*)(tmp + key_bytes);

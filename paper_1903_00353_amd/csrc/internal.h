@@ -259,8 +259,9 @@ namespace csc {
 // current device, from the kept ones or allocated (*got >= bytes); give: back, of
 // device dev, with no work left that uses it (handle_idle waits for that). Kept: at
 // most POOL_BYTES and POOL_BLOCKS per device, nothing that POOL_AGE later gives left
-// unused, and nothing once an allocation here has run out of memory. All of it may be
-// called from any thread.
+// unused, and nothing once an allocation of the library has run out of memory (every one
+// goes through device_alloc, which then gives all back with pool_empty and tries again). All of it
+// may be called from any thread.
 constexpr size_t POOL_BYTES = (size_t)256 << 20;
 constexpr int POOL_BLOCKS = 16;
 constexpr uint64_t POOL_AGE = 64;
@@ -270,6 +271,8 @@ void pool_give(int dev, char* p, size_t bytes);
 hipError_t pinned_take(int64_t** p, int* dev);
 void pinned_give(int dev, int64_t* p);
 bool handle_idle(const csc_features* f);
+void pool_empty(int dev);
+hipError_t device_alloc(size_t bytes, void** p, int dev);  // on the current device, dev
 
 // every entry point that queues work on a handle says on which stream
 inline void queued_on(const csc_features* f, const void* stream) {

@@ -17,6 +17,7 @@ size_t sim_limit = (size_t)1 << 40;     // bytes of device memory
 // read by the test
 size_t sim_used = 0;                    // bytes of device memory allocated
 int sim_allocs = 0, sim_frees = 0, sim_device_waits = 0;
+int sim_ordered_allocs = 0;             // of those, in stream order
 int sim_uploads = 0;                    // host-to-device copies since the last device allocation
 }
 
@@ -85,8 +86,14 @@ hipError_t hipFree(void* p) {
   sim_frees++;
   return hipSuccess;
 }
-hipError_t hipMallocAsync(void** p, size_t bytes, hipStream_t) { return hipMalloc(p, bytes); }
-hipError_t hipFreeAsync(void* p, hipStream_t) { return hipFree(p); }
+hipError_t hipMallocAsync(void** p, size_t bytes, hipStream_t) {
+  sim_ordered_allocs++;
+  return hipMalloc(p, bytes);
+}
+hipError_t hipFreeAsync(void* p, hipStream_t) {
+  sim_frees--;  // waits for nothing
+  return hipFree(p);
+}
 hipError_t hipHostMalloc(void** p, size_t bytes, unsigned) {
   *p = calloc(1, bytes);
   return hipSuccess;
@@ -121,6 +128,10 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus* st) {
 hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode*) { return hipSuccess; }
 hipError_t hipGetDevice(int* d) {
   *d = 0;
+  return hipSuccess;
+}
+hipError_t hipGetDeviceCount(int* n) {
+  *n = 1;
   return hipSuccess;
 }
 hipError_t hipSetDevice(int) { return hipSuccess; }

@@ -124,3 +124,19 @@ def test_a_handle_freed_with_work_on_another_stream():
     torch.cuda.synchronize()
     assert b.shape == a.shape and int(out[3].item()) == want.n_band
     assert all(torch.equal(x[:want.n_band], y) for x, y in zip(out, (want.sdf, want.feat, want.cell)))
+
+
+def test_kept_memory_is_given_back_on_request():
+    v, t = meshgen.icosphere(7)
+    verts, tris = torch.from_numpy(v).cuda(), torch.from_numpy(t).cuda()
+    f = P.csc_build_features(verts, tris, Grid.unit(64, 3))
+    P.csc_release_memory()
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    print("[case] release", flush=True)
+    f.free()
+    assert torch.cuda.mem_get_info()[0] - free < 4 << 20  # kept
+    P.csc_release_memory()
+    assert torch.cuda.mem_get_info()[0] - free > 64 << 20  # the arena of 328,000 faces
+    got = P.csc_scan_convert(P.csc_build_features(verts, tris, Grid.unit(64, 3)))
+    assert got.n_band > 0

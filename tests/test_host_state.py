@@ -23,6 +23,7 @@ class Sim:
         self.lib.csc_build_features_batched.argtypes = P.lib().csc_build_features_batched.argtypes
         self.lib.csc_features_order_faces.argtypes = [C.c_void_p, C.c_int32, C.c_void_p]
         self.lib.csc_features_free.argtypes = [C.c_void_p]
+        self.lib.csc_weld_soup.argtypes = P.lib().csc_weld_soup.argtypes
 
     def __getattr__(self, name):  # a variable of the stand-in
         return (C.c_size_t if name in ("limit", "used") else C.c_int).in_dll(self.lib, "sim_" + name)
@@ -101,3 +102,29 @@ def test_a_handle_freed_during_a_capture_is_waited_for_without_ending_it(sim, st
     code, h = sim.build(16)
     assert code == OK and sim.used.value == used
     sim.lib.csc_features_free(h)
+
+
+def test_kept_memory_serves_every_allocation_that_runs_out(sim):
+    """With no room left but what a freed handle's memory takes, the face order gets its
+    memory all the same."""
+    code, h = sim.build(16)
+    code2, kept = sim.build(64)
+    assert code == OK and code2 == OK
+    sim.lib.csc_features_free(kept)
+    sim.limit.value = sim.used.value
+    assert sim.lib.csc_features_order_faces(h, 1, None) == OK
+    sim.lib.csc_features_free(h)
+
+
+def test_kept_memory_is_given_back_on_request(sim):
+    handles = [sim.build(n, stream=s)[1] for n in (16, 64) for s in (None, 0x10)]
+    live, h = sim.used.value, handles.pop()
+    for x in handles:
+        sim.lib.csc_features_free(x)
+    assert live // 2 < sim.used.value <= live + 64  # kept (and the one small allocation)
+    sim.lib.csc_release_memory()
+    one = sim.used.value
+    assert 0 < one < live // 2  # what the handle in use takes
+    sim.lib.csc_features_free(h)
+    sim.lib.csc_release_memory()
+    assert sim.used.value <= 64
