@@ -246,7 +246,8 @@ int csc_scan_convert(const csc_features* f, void* workspace_d, size_t ws_bytes, 
  * every corner being distinct); the first *nv rows are written. tris_d: int32
  * [nf][3] device. nv: host pointer receiving the vertex count. Takes its
  * temporaries (14 bytes per corner) from the memory that the library keeps (see
- * csc_features_free), or allocates them, and synchronises `stream` before returning.
+ * csc_features_free), or allocates them (in stream order above 256 MiB), and
+ * synchronises `stream` before returning.
  * Triangles that collapse (two corners at one position) are not removed here;
  * csc_build_features rejects them.
  * Errors: INVALID_ARG (null, nf <= 0, 3*nf >= 2^31, non-finite coordinate),

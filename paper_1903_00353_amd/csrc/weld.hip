@@ -236,19 +236,37 @@ extern "C" int csc_weld_soup(const float* soup_d, int64_t nf, float* verts_d, in
   int64_t* pinned = nullptr;
   size_t bytes = 0;
   int dev = 0;
-  hipError_t e = pool_take(L.total, &W, &bytes, &dev);
+  // scratch too large to be kept comes and goes on the stream: its free waits for
+  // nobody else's work
+  const bool keep = L.total <= POOL_BYTES;
+  hipError_t e;
+  if (keep) {
+    e = pool_take(L.total, &W, &bytes, &dev);
+  } else {
+    e = hipGetDevice(&dev);
+    if (e == hipSuccess) e = hipMallocAsync((void**)&W, L.total, s);
+    if (e == hipErrorOutOfMemory) {
+      (void)hipGetLastError();
+      pool_empty(dev);
+      e = hipMallocAsync((void**)&W, L.total, s);
+    }
+  }
   if (e != hipSuccess) return e == hipErrorOutOfMemory ? CSC_OUT_OF_MEMORY : fail_hip(e);
   e = pinned_take(&pinned, &dev);
   static_assert(sizeof(WeldCount) <= sizeof(int64_t) * PINNED_WORDS, "the report fits the pinned words");
   if (e == hipSuccess) e = weld_queue(soup_d, nf, verts_d, tris_d, W, L, (WeldCount*)pinned, s);
+  if (!keep) {
+    const hipError_t ef = hipFreeAsync(W, s);
+    if (e == hipSuccess) e = ef;
+  }
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) {  // queued work may still use them: freed, which waits for it
-    (void)hipFree(W);
+    if (keep) (void)hipFree(W);
     if (pinned) (void)hipHostFree(pinned);
     return fail_hip(e);
   }
   const WeldCount h = *(const WeldCount*)pinned;
-  pool_give(dev, W, bytes);
+  if (keep) pool_give(dev, W, bytes);
   pinned_give(dev, pinned);
   if (h.bad) return CSC_INVALID_ARG;
   *nv = h.nv;

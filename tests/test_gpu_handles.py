@@ -140,3 +140,33 @@ def test_kept_memory_is_given_back_on_request():
     assert torch.cuda.mem_get_info()[0] - free > 64 << 20  # the arena of 328,000 faces
     got = P.csc_scan_convert(P.csc_build_features(verts, tris, Grid.unit(64, 3)))
     assert got.n_band > 0
+
+
+@pytest.mark.parametrize("nu,nv", [(400, 300), (2048, 1600)])  # scratch kept; above 256 MiB
+def test_a_weld_waits_for_no_other_stream(nu, nv):
+    i = torch.arange(nu, device="cuda").repeat_interleave(nv)
+    j = torch.arange(nv, device="cuda").repeat(nu)
+    ip, jp = (i + 1) % nu, (j + 1) % nv
+    a, b, c, d = i * nv + j, ip * nv + j, ip * nv + jp, i * nv + jp
+    tris = torch.cat([torch.stack([a, b, c], 1), torch.stack([a, c, d], 1)])
+    pos = torch.stack([torch.arange(nu * nv, device="cuda") % 4096, torch.arange(nu * nv, device="cuda") // 4096,
+                       torch.zeros(nu * nv, device="cuda", dtype=torch.long)], 1).float()
+    soup = pos[tris].contiguous()
+    del i, j, ip, jp, a, b, c, d
+    P.csc_weld_soup(soup)  # the binding's outputs are in the allocator's cache from here on
+    side, done = torch.cuda.Stream(), torch.cuda.Event()
+    m = torch.rand(8192, 8192, device="cuda")
+    out = torch.empty_like(m)
+    with torch.cuda.stream(side):
+        torch.mm(m, m, out=out)  # the library is loaded
+    torch.cuda.synchronize()
+    print("[case] weld beside another stream", tris.shape[0], flush=True)
+    with torch.cuda.stream(side):
+        for _ in range(40):  # some 300 ms
+            torch.mm(m, m, out=out)
+        done.record()
+    verts, got = P.csc_weld_soup(soup)
+    waited = done.query()
+    torch.cuda.synchronize()
+    assert verts.shape[0] == nu * nv and torch.equal(verts[got.long()], soup)
+    assert not waited

@@ -128,3 +128,15 @@ def test_kept_memory_is_given_back_on_request(sim):
     sim.lib.csc_features_free(h)
     sim.lib.csc_release_memory()
     assert sim.used.value <= 64
+
+
+@pytest.mark.parametrize("nf,ordered", [(1 << 16, False), (7 << 20, True)])
+def test_scratch_too_large_to_keep_is_allocated_in_stream_order(sim, nf, ordered):
+    """The scratch of a weld of 7.3M faces passes 256 MiB: it is not freed by hipFree, which
+    would wait for the work of other streams. A smaller one is kept."""
+    data, nv = C.c_void_p(0x1000), C.c_int64()
+    for _ in range(2):
+        assert sim.lib.csc_weld_soup(data, nf, data, data, C.byref(nv), None) == OK
+    assert sim.ordered_allocs.value == (2 if ordered else 0) and sim.frees.value == 0
+    assert sim.allocs.value == (2 if ordered else 1)
+    assert (sim.used.value == 0) == ordered
