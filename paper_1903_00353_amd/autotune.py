@@ -11,14 +11,13 @@ The scan conversion has three schedule choices, none of which changes a value:
     nearly flat edges and vertices (``absorb_cells``; negative: none absorbed);
   * for a batch, the grid of the build's input pass (``geom_blocks``: 0 the
     library's own bound, or a smaller grid striding over the faces).
-The tuner times candidates on the caller's own workload with the library's stage
-events (HIP events on the working stream): first ``small_rows`` per kind (each
-kind's one-lane launch plus its overflow launch), then ``scan_grid`` and
-``absorb_cells`` one after the other on the time of the whole forward pass
-(scans and sign; for a batch, whose kinds share one launch, so that stage times
-do not add up, on the time of its whole step, on which a batch's rows per kind
-are refined as well), then
-(batches) ``geom_blocks`` on the build's time. It caches
+The tuner times candidates on the caller's own workload: first ``small_rows`` per
+kind with the library's stage events (HIP events on the working stream; each
+kind's one-lane launch plus its overflow launch). Stage timing runs the kinds one
+after another, where an untimed call runs all three in one launch, so the rows are
+then refined, and ``scan_grid`` and ``absorb_cells`` chosen, one after the other on
+the time of untimed calls (of the scan and sign of one mesh, of a batch's whole
+step). Last (batches) comes ``geom_blocks``, on the build's time. It caches
 the choice as JSON keyed by the device and the workload's shape.
 """
 from __future__ import annotations
@@ -51,7 +50,7 @@ def signature(nf_list, grids) -> str:
     tri_cells = faces / max(1.0, cells ** (2.0 / 3.0))  # triangles per cell of surface area (rough)
     return (f"{getattr(dev, 'gcnArchName', dev.name)}|n={len(grids)}|F=2^{round(math.log2(max(faces, 1)))}"
             f"|cells=2^{round(math.log2(max(cells, 1)))}|band={band:g}|tpc=2^{round(math.log2(max(tri_cells, 1e-9)))}"
-            f"|v6")
+            f"|v7")  # changes with the kernels that the choice was made for
 
 
 def load(sig: str):
@@ -107,7 +106,7 @@ def _forward_time(t):
 
 
 def _score(t):
-    # a batch's measurements carry its whole step's time (kinds overlapped)
+    # the time of untimed calls (kinds in one launch), where the measurement carries it
     return t["step"] if "step" in t else _forward_time(t)
 
 
@@ -131,9 +130,9 @@ def _search(measure, base, reps, build=False):
     for c in CANDIDATES:
         timings[f"rows={c}"] = measure(_with(base, rows=(c, c, c)), reps)
     rows = tuple(min(CANDIDATES, key=lambda c: _kind_times(timings[f"rows={c}"])[k]) for k in range(3))
-    if build:
-        # a batch: its kinds share one launch, so each kind's rows are
-        # refined, one kind after the other, on the whole step
+    if "step" in timings[f"rows={CANDIDATES[0]}"]:
+        # the kinds share one launch, so each kind's rows are refined, one kind
+        # after the other, on the untimed call
         rows = list(rows)
         for k in range(3):
             best_t = None
@@ -186,7 +185,7 @@ def tune_batch(batch, reps=3, use_cache=True):
         def measure(opt, reps):
             rebuild(opt)
             t = _stage_times(batch.step, reps)
-            t["step"] = _step_time(batch.step, max(40, reps))  # stage timing off: kinds overlapped
+            t["step"] = _step_time(batch.step, max(40, reps))
             return t
         choice, timings = _search(measure, base, reps, build=True)
         save(sig, choice, timings)
@@ -212,7 +211,10 @@ def tune_single(verts, tris, grid, options=None, reps=3, use_cache=True):
                    torch.empty(mx, dtype=torch.int32, device=verts.device),
                    torch.empty(mx, dtype=torch.int32, device=verts.device),
                    torch.zeros(1, dtype=torch.int64, device=verts.device))
-            t = _stage_times(lambda: P.csc_scan_convert(f, ws, out, sync_count=False), reps)
+            def scan():
+                P.csc_scan_convert(f, ws, out, sync_count=False)
+            t = _stage_times(scan, reps)
+            t["step"] = _step_time(scan, max(40, reps))
             f.free()
             return t
         choice, timings = _search(measure, base, reps)
