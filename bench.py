@@ -41,6 +41,14 @@ KERNEL_SYMBOL = {"init_keys": "k_init_keys", "scan_faces": "k_scan_small<1,",
                  "scan_faces_big": "k_scan_over<1,", "scan_edges_big": "k_scan_over<4,",
                  "scan_vertices_big": "k_scan_over<16,", "sign": "k_sign", "backward": "k_backward"}
 SINGLE_KERNEL_STAGES = list(KERNEL_SYMBOL)
+
+
+def kernel_name(stage):
+    """The stage's kernel as the bench line names it: k_scan_small<1> is its faces' instance."""
+    sym = KERNEL_SYMBOL[stage]
+    return sym[:-1] + ">" if sym.endswith(",") else sym
+
+
 # scan launches and their tags in csc_scan_record_atomics, with their index in the atomic counts
 SCAN_LAUNCHES = {"scan_faces": 0, "scan_edges": 1, "scan_vertices": 2, "scan_faces_big": 3, "scan_edges_big": 4,
                  "scan_vertices_big": 5}
@@ -208,7 +216,7 @@ def rooflines(avg, per_step, atomics, rates, alg_bytes, fwd_bytes, fwd_span_ms=N
                 "unit": "G atomics/s"}
     else:
         main = {"bound": "hbm", "achieved": d["hbm_GBs"], "peak": PEAK_HBM_GBS, "unit": "GB/s"}
-    main.update({"kernel": KERNEL_SYMBOL[dom], "frac": d["frac"], "avg_ms": d["ms"],
+    main.update({"kernel": kernel_name(dom), "frac": d["frac"], "avg_ms": d["ms"],
                  "algorithmic_bytes": d["algorithmic_bytes"], "hbm_frac": d["hbm_frac"],
                  "atomic_frac": d.get("atomic_frac")})
     t_stages = sum(per_step.get(st, 0.0) for st in FORWARD_STAGES)
@@ -223,7 +231,7 @@ def rooflines(avg, per_step, atomics, rates, alg_bytes, fwd_bytes, fwd_span_ms=N
     fwd["frac"] = fwd["t_roof_ms"] / t_fwd if t_fwd > 0 else None
     fwd["bound"] = "atomic" if fwd.get("t_atomic_ms", 0.0) > fwd["t_hbm_ms"] else "hbm"
     main["forward_frac"] = fwd["frac"]
-    main["slowest_kernel"] = {"kernel": KERNEL_SYMBOL[slowest], "ms": per[slowest]["ms"], "frac": per[slowest]["frac"],
+    main["slowest_kernel"] = {"kernel": kernel_name(slowest), "ms": per[slowest]["ms"], "frac": per[slowest]["frac"],
                               "bound": per[slowest]["bound"]}
     return main, per, dom, fwd
 

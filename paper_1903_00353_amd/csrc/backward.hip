@@ -166,8 +166,9 @@ __device__ inline float wave_max(float v) {
 
 static_assert(BW_FLUSH < BW_SLOTS && 8 * (BW_SLOTS * 28 + 64) <= (160 << 10), "table size");
 
-// where a vertex is looked for: its first slot, and the step from one to the next
-// (1 to BW_SLOTS - 1)
+// Where a vertex is looked for: its first slot (by the 32-bit finaliser of MurmurHash3, A.
+// Appleby, without its last shift), and the step from one to the next (1 to BW_SLOTS - 1, by
+// Knuth's multiplicative hash).
 __device__ inline unsigned first_slot(int32_t v) {
   unsigned x = (unsigned)v;
   x = (x ^ (x >> 15)) * 0x85ebca6bu;

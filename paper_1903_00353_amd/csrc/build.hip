@@ -196,7 +196,7 @@ __global__ void k_offsets(const uint32_t* __restrict__ key, int64_t nh, int64_t 
 // Flat features (theta = 0) already get none. Ruff vertices and hemispheres,
 // and edges of unknown class, keep their polyhedra. The vertex pass keeps its
 // slack code in the vertex's class word, the edge pass in a byte per edge (both
-// written by the thread that owns the feature), and k_face_slack gives every
+// written by the thread that owns the feature), and k_lists gives every
 // face the largest code of its three edges and three vertices.
 
 __device__ inline uint8_t slack_code(double cells, float absorb) {
@@ -317,7 +317,8 @@ static_assert(V_POS == 1u && V_NEG == 2u, "side bits of the class word");
 //    Section 8.3), cone aperture and ruff test from the normals (Section 3.3,
 //    Section 4.2), all in double precision; number of vertex polyhedra.
 // Bounded by the latency of the gathers of triangle rows and positions and by its
-// FP64 arithmetic (4 wavefronts per SIMD, LDS-bound).
+// FP64 arithmetic (4 wavefronts per SIMD, LDS-bound). Fans of more than VK_MAXD corners,
+// sorted by k_bucket, are walked in memory (long_fan).
 __global__ __launch_bounds__(VK_THREADS) void k_vertex(const float* __restrict__ V, const int32_t* __restrict__ T,
                                                       int64_t nv, const int32_t* __restrict__ off,
                                                       const int32_t* __restrict__ vc, VertexOut O, int32_t* twin, int32_t* polys, int64_t* stats) {
@@ -431,11 +432,10 @@ __global__ __launch_bounds__(VK_THREADS) void k_vertex(const float* __restrict__
 // that a fan takes one angle and one test where a thread takes them one after
 // another, and a mesh of few vertices fills more of the chip. The faces' shares of the
 // pseudonormal are still added in corner order. Vertices of more corners are left to
-// their first lane. polys: cleared by k_inputs. (Build of 642 vertices 43 -> 33 us, 10,242
-// vertices 50 -> 45, 35,000 63 -> 56; from some 100,000 on a lane per vertex keeps the
-// chip busy by itself: 180,000 vertices 108 us and with fans 123, 2.6M 1213 and 1395. Delaunay
+// their first lane. polys: cleared by k_inputs. (Build of 642 vertices 43 us with a thread
+// per vertex, 33 with lanes; see VERTEX_FANS for larger ones. Delaunay
 // triangles of random points, 4% of the vertices of nine corners and more: with those
-// left to a lane as well 118 us at 1,000 vertices and 237 at 65,000, with two corners a
+// left to one lane 118 us at 1,000 vertices and 237 at 65,000, with two corners a
 // lane 64 and 140, build with its read-back.)
 constexpr int VF_LANES = 8, VF_PER = 2, VF_MAXD = VF_LANES * VF_PER, VF_THREADS = 256, VF_WAVE = 64 / VF_LANES;
 __global__ __launch_bounds__(VF_THREADS) void k_vertex_fan(const float* __restrict__ V, const int32_t* __restrict__ T,
@@ -809,8 +809,8 @@ struct InputArgs {
 // after another: a mesh of few faces fills more of the chip, and a face of hundreds
 // of bricks among small ones holds up nobody (12 faces over 64^3 cells 45 -> 8 us; a wide
 // band of 25,984 faces 97 -> 40; 70,000 faces 29 -> 19). A thread's own loop has less to
-// read and no barrier, and is the faster from some 200,000 faces on (360,000: build 108
-// us and shared 121; 64 meshes, 1.75M: 405 and 508).
+// read and no barrier, and is the faster for many faces (64 meshes, 1.75M: build 405 us and
+// shared 508; see INPUT_SHARED).
 template <int FACES>
 __global__ __launch_bounds__(BT) void k_inputs(InputArgs P) {
   constexpr bool SHARE = FACES < BT;
@@ -1427,8 +1427,9 @@ enum {
 // How the corner table is made: buckets of 2^shift vertices, or (no buckets) the
 // radix sort, for more vertices than MAX_BUCKETS of the largest buckets hold. Large
 // inputs take long tiles (few shares per bucket), small ones short tiles (more blocks).
-// Build with short and with long tiles: 15.7M corners 1519 and 1207 us, 5.3M corners
-// 406 and 415, 1.1M corners 107 and 129.
+// Build of tori with short and with long tiles: 4.2M corners 243 and 247 us, 6.5M 392 and 368,
+// 8.4M 492 and 479, 10.8M 617 and 598, 16.2M 962 and 881; of 64 meshes with 5.3M corners
+// 406 and 415.
 constexpr int DEAL_TH = 256, DEAL_ITEMS = 8, DEAL_BIG_TH = 1024, DEAL_BIG_ITEMS = 16;
 constexpr int64_t DEAL_BIG = 1 << 23;  // corners from which the long tiles are used
 // Blocks of the input pass: a tile each up to 8.4M faces. A block adds its corner
@@ -1436,8 +1437,19 @@ constexpr int64_t DEAL_BIG = 1 << 23;  // corners from which the long tiles are 
 // a block's next tile would wait for its last one's stores (a batch of 64 meshes:
 // build 406 us with 2048 blocks, 397 with a tile each; 5.2M faces 1210, 1188).
 constexpr int64_t INPUT_BLOCKS = 32768;
-constexpr int64_t VERTEX_FANS = 1 << 16;   // vertices up to which a vertex takes a lane per corner (k_vertex_fan)
-constexpr int64_t INPUT_SHARED = 1 << 17;  // faces up to which a block shares its faces' bricks (k_inputs)
+// Vertices up to which a vertex takes a lane per corner (k_vertex_fan). Build of tori (six
+// corners everywhere) with a thread per vertex and with lanes: 30,000 vertices 51 and 49
+// us, 64,800 72 and 76, 80,000 67 and 71, 120,000 73 and 85, 180,000 93 and 110; of random points'
+// triangles (4 to 13 corners, where a wavefront of threads waits for its longest fan) 30,000
+// vertices 147 and 68, 65,000 193 and 116, 180,000 231 and 177. The line lies where the
+// regular ones lose 5%.
+constexpr int64_t VERTEX_FANS = 1 << 16;
+// Faces up to which a block shares its faces' bricks (k_inputs). Build of tori with a
+// thread's own loop and shared, at bands of 3, 8 and 20 cells: 34,848 faces 69 and 58, 141 and 83 us
+// at the two wider ones; 100,000 67 and 72, 82 and 79, 167 and 136; 129,600 71 and 76, 85 and 84, 170 and 153; 192,000
+// 69 and 75, 85 and 86, 177 and 183; 360,000 94 and 109, 115 and 124, 279 and 297. The line lies
+// where the band of 8 breaks even.
+constexpr int64_t INPUT_SHARED = 1 << 17;
 struct Plan {
   int shift = 0, buckets = 0;
   bool big = false;

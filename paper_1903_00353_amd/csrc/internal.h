@@ -15,7 +15,7 @@ namespace csc {
 // 2 band / (2 band + b): 4-cell bricks hold more set keys, which shrinks the key
 // initialisation and the brick count (-35%, -25% measured), but each small
 // triangle then marks about 8 times as many bricks (the face pass ran 2-3 times
-// longer, its scattered stores slowing the sort beside it) and the sign pass
+// longer, by its scattered stores) and the sign pass
 // holds one key per lane instead of eight (+75%): 8-cell bricks stay the default.
 #ifndef CSC_BRICK_SHIFT
 #define CSC_BRICK_SHIFT 3
