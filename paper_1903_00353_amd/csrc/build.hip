@@ -1392,6 +1392,11 @@ extern "C" int csc_features_order_faces(csc_features* F, int32_t enable, void* s
   const size_t sort_bytes = sort_pairs_tmp_bytes(nf, bits);
   if (sort_bytes == 0) return CSC_INVALID_ARG;
   const size_t key_bytes = ((size_t)nf * sizeof(uint32_t) + 255) & ~(size_t)255;
+  // the sort's scratch is gone when a captured one would run
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  hipError_t ce = hipStreamIsCapturing(s, &cap);
+  if (ce == hipSuccess && cap != hipStreamCaptureStatusNone) ce = hipErrorStreamCaptureUnsupported;
+  if (ce != hipSuccess) return fail_hip(ce);
   if (!F->face_order) {
     hipError_t he = device_alloc(sizeof(int32_t) * (size_t)nf, (void**)&F->face_order, F->device);
     if (he != hipSuccess) return he == hipErrorOutOfMemory ? CSC_OUT_OF_MEMORY : fail_hip(he);

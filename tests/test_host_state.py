@@ -116,6 +116,19 @@ def test_kept_memory_serves_every_allocation_that_runs_out(sim):
     sim.lib.csc_features_free(h)
 
 
+def test_a_face_order_is_refused_under_capture(sim):
+    """Before anything is allocated, freed or queued."""
+    code, h = sim.build(16)
+    assert code == OK
+    allocs, frees = sim.allocs.value, sim.frees.value
+    sim.capturing.value = 1
+    assert sim.lib.csc_features_order_faces(h, 1, 0x10) == HIP_ERROR
+    sim.capturing.value = 0
+    assert (sim.allocs.value, sim.frees.value) == (allocs, frees)
+    assert sim.lib.csc_features_order_faces(h, 1, None) == OK
+    sim.lib.csc_features_free(h)
+
+
 def test_kept_memory_is_given_back_on_request(sim):
     handles = [sim.build(n, stream=s)[1] for n in (16, 64) for s in (None, 0x10)]
     live, h = sim.used.value, handles.pop()
