@@ -233,6 +233,11 @@ extern "C" int csc_weld_soup(const float* soup_d, int64_t nf, float* verts_d, in
   int rc = check_device();
   if (rc != CSC_OK) return rc;
   hipStream_t s = (hipStream_t)stream;
+  // the call synchronises s: refused while s is captured, before scratch is taken
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  hipError_t ce = hipStreamIsCapturing(s, &cap);
+  if (ce == hipSuccess && cap != hipStreamCaptureStatusNone) ce = hipErrorStreamCaptureUnsupported;
+  if (ce != hipSuccess) return fail_hip(ce);
   const WeldLayout L = weld_layout(3 * nf);
   char* W = nullptr;
   int64_t* pinned = nullptr;

@@ -55,6 +55,29 @@ def test_a_changed_configuration_is_refused_under_capture(meshes):
     assert all(torch.equal(a, b) for a, b in zip(scan(f), scan(kept)))
 
 
+def test_calls_refused_under_capture_leave_it_alone():
+    """A weld, which synchronises, and a face order: refused, and the capture goes on."""
+    verts, tris = mesh(3)
+    f = P.csc_build_features(verts, tris, Grid.unit(32, 3))
+    soup = verts[tris.long()].contiguous()
+    P.csc_weld_soup(soup)
+    x = torch.ones(100, device="cuda")
+    torch.cuda.synchronize()
+    print("[case] refused calls", flush=True)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        y = x * 2
+        for call in (lambda: P.csc_features_order_faces(f), lambda: P.csc_weld_soup(soup)):
+            with pytest.raises(P.CscError) as e:
+                call()
+            assert e.value.code == 7
+        z = y + 1
+    g.replay()
+    assert z[0].item() == 3.0
+    P.csc_features_order_faces(f)
+    assert P.csc_weld_soup(soup)[0].shape == verts.shape
+
+
 @pytest.mark.parametrize("thread", [False, True])
 @pytest.mark.parametrize("mode", ["relaxed", "thread_local", "global"])
 def test_a_handle_is_freed_during_a_capture(mode, thread):

@@ -143,6 +143,16 @@ def test_kept_memory_is_given_back_on_request(sim):
     assert sim.used.value <= 64
 
 
+def test_a_weld_is_refused_under_capture(sim):
+    """Before it takes scratch memory, whose free could fail there."""
+    data, nv = C.c_void_p(0x1000), C.c_int64()
+    sim.capturing.value = 1
+    assert sim.lib.csc_weld_soup(data, 1 << 16, data, data, C.byref(nv), 0x10) == HIP_ERROR
+    sim.capturing.value = 0
+    assert sim.allocs.value == 0 and sim.used.value == 0
+    assert sim.lib.csc_weld_soup(data, 1 << 16, data, data, C.byref(nv), 0x10) == OK
+
+
 @pytest.mark.parametrize("nf,ordered", [(1 << 16, False), (7 << 20, True)])
 def test_scratch_too_large_to_keep_is_allocated_in_stream_order(sim, nf, ordered):
     """The scratch of a weld of 7.3M faces passes 256 MiB: it is not freed by hipFree, which
